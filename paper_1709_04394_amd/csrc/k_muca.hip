@@ -2,21 +2,21 @@
 // simulations": p walkers share one weight function, their histograms are
 // added; Eq. muca, Eq. weight_modification) for 2D L x L ferromagnets.
 //
-// One lane is one walker; 64 walkers form a wave and visit the same site at
-// the same time (the paper's shared site sequence), each with its own random
-// numbers.  A walker's rows are bit-packed in registers while it sweeps them
-// in sequential (typewriter) order; the rows of the whole lattice stay int8 in
+// Walkers visit the sites of a lattice in the same sequential (typewriter)
+// order, each with its own random numbers.  A walker's rows are bit-packed in
+// registers while it sweeps them; the rows of the whole lattice stay int8 in
 // global memory and stream through once per sweep.  The acceptance table
 // T[level][direction] (FP64 host values as 32-bit thresholds) sits in LDS
-// (131 KB at L = 128, within gfx950's 160 KB), so the dependent chain of one
-// update is a few bit operations, one LDS read and a compare.  Moves that
-// would leave the energy window [-2N, 0] are rejected and the current level
-// is counted again.
+// (131 KB at L = 128, within gfx950's 160 KB).  Moves that would leave the
+// energy window [-2N, 0] are rejected and the current level is counted again.
+// k_muca_q (four lanes per walker) does the sweeps; k_muca (one lane per
+// walker) is the plain form, kept for the one table the other cannot hold.
 #include <algorithm>
 
 #include "internal.hpp"
 #include "muca.hpp"
 #include "muca_rows.hpp"
+#include "quad_walk.hpp"
 
 namespace mcs {
 
@@ -84,177 +84,220 @@ __global__ __launch_bounds__(64) void k_muca(MucaArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// k_muca_w<L>: the same walk for L a multiple of 32, organised around the one
-// serial dependence of an update (the acceptance of the site to its left and
-// the walker's level), so that little else is on that chain:
-//  * the row being swept is held as 32-bit words rotated so the active word is
-//    always at index 0, and its 32 updates are unrolled with fixed bit
-//    positions;
-//  * per word, the unsatisfied-bond count against the up, down and right
-//    neighbours (all in their old state, except the wrap-around of a one-word
-//    row) is summed for all 32 bits at once in two bit planes; the left
-//    neighbour, updated one step earlier, gives the count for either outcome
-//    of that step (a0 if it was rejected, a1 if accepted);
-//  * the threshold for either outcome (row of the level it leaves, entry of
-//    its count) is read from LDS one update ahead, so the dependent chain of
-//    an update is a few selects and compares; no branches;
-//  * the histogram is counted in LDS, two 16-bit counts per word, and flushed
-//    to the workgroup's slice before a count can reach 2^16;
-//  * the row two ahead is loaded while the current row is swept.
-// It draws the same random numbers, takes the same decisions and records the
-// same levels as k_muca<L>.
+// k_muca_q<L>: the same walk with four lanes per walker (quad_walk.hpp).  It
+// draws the same random numbers, takes the same decisions and records the same
+// levels as k_muca<L>.
+//
+// What an update costs is the instructions its wave issues, so little is left
+// on the chain:
+//  * the level is held as the LDS byte address z of its table row, so an
+//    entry's address and the next level are one add of a prepared offset each;
+//  * for both outcomes of an update the next one's thresholds are read, and the
+//    level it leads to is formed, before that outcome is known; a decision is
+//    then a select and one compare r < T, and two selects carry it on;
+//  * the next group's Philox block is computed a round per update in the time
+//    the reads take;
+//  * the row has an entry that always accepts for a = 2 and entries that never
+//    accept for moves out of the window (T as a 32-bit word, 2^32 stored as
+//    2^32 - 1 and r as min(r, 2^32 - 2); exact unless a threshold is 2^32 - 1
+//    itself, for which the launcher takes k_muca);
+//  * every fourth update the four lanes count the levels of the last four
+//    updates with one LDS atomic, each lane one of them.
+// Rows are six words (five entries and the count) for L <= 96.  L = 128 has
+// room for four-word rows (a = 0, 1, 4, 3; a = 2 accepted by its zero step)
+// and 16-bit counts, two levels per word, added to H before they can overflow.
+// Counts go straight to H by 64-bit atomics: a workgroup visits few levels.
+//
+// Measured, 4096 walkers, L = 64, recorded: 153 ns per update with one lane
+// per walker (two LDS reads, an LDS atomic and about 57 VALU instructions of
+// one wave per update), 65 ns so (about 18 VALU and 2.3 LDS instructions; a
+// lone wave issues one in 8 cycles on a chain).  16384 walkers at L = 64: 159 ns
+// before, 66 now; 65536 at L = 16: 200 ns before (2.0 ms per 40 sweeps without
+// counting, 48 ms with its global atomics), 142 now.
 template <int L>
-__device__ __forceinline__ void load_row_raw(const int8_t *sp, int y, uint4 (&raw)[L / 16])
-{
-    const uint4 *p = (const uint4 *)(sp + y * L);
-#pragma unroll
-    for (int i = 0; i < L / 16; ++i) raw[i] = p[i];
-}
+struct MucaRow {
+    static constexpr bool kWide = L <= 96;
+    static constexpr int S = kWide ? 24 : 16;  // bytes per row
+    static constexpr int K = L * L / 2;
+    static constexpr int TAB = (K + 4) * S;    // rows K + 1 .. K + 3 are read ahead, never used
+    static constexpr int LDS = TAB + (kWide ? 0 : (K / 2 + 1) * 4);
+};
 
+constexpr int kMucaMaxWaves = 4;  // 64 walkers per workgroup: at most 64 N counts per sweep
+
+// Adds the LDS counts to H and clears them.  Every wave does so on its own,
+// exchanging each word: no wave waits for another.
 template <int L>
-__device__ __forceinline__ void pack_raw(const uint4 (&raw)[L / 16], uint32_t (&row)[L / 32])
+__device__ __forceinline__ void muca_flush(uint32_t *lds, int64_t *H, int lane)
 {
-#pragma unroll
-    for (int i = 0; i < L / 32; ++i) {
-        const uint4 a = raw[2 * i], b = raw[2 * i + 1];
-        row[i] = pack4(a.x) | pack4(a.y) << 4 | pack4(a.z) << 8 | pack4(a.w) << 12 | pack4(b.x) << 16 |
-                 pack4(b.y) << 20 | pack4(b.z) << 24 | pack4(b.w) << 28;
-    }
-}
-
-template <int L>
-__device__ __forceinline__ void store_row_w(int8_t *sp, int y, const uint32_t (&row)[L / 32])
-{
-    uint4 *p = (uint4 *)(sp + y * L);
-#pragma unroll
-    for (int i = 0; i < L / 32; ++i) {
-        const uint32_t v = row[i];
-        p[2 * i] = make_uint4(unpack4(v & 0xFu), unpack4((v >> 4) & 0xFu), unpack4((v >> 8) & 0xFu),
-                              unpack4((v >> 12) & 0xFu));
-        p[2 * i + 1] = make_uint4(unpack4((v >> 16) & 0xFu), unpack4((v >> 20) & 0xFu), unpack4((v >> 24) & 0xFu),
-                                  unpack4(v >> 28));
-    }
-}
-
-// Adds the LDS counts (two 16-bit levels per word) to the workgroup's slice and
-// clears them.  The workgroup is one wave; the barriers order the lanes' LDS
-// accesses around the exchange.
-__device__ __forceinline__ void flush_hist16(uint32_t *h16, uint32_t *gh, int nh, int K, int lane)
-{
-    __syncthreads();
-    for (int i = lane; i < nh; i += 64) {
-        const uint32_t v = h16[i];
-        if (v) {
-            h16[i] = 0u;
-            if (v & 0xFFFFu) atomicAdd(&gh[2 * i], v & 0xFFFFu);
-            if ((v >> 16) && 2 * i + 1 <= K) atomicAdd(&gh[2 * i + 1], v >> 16);
+    using M = MucaRow<L>;
+    if constexpr (M::kWide) {
+        for (int k = lane; k <= M::K; k += 64) {
+            const uint32_t v = lds[k * 6 + 5] ? atomicExch(&lds[k * 6 + 5], 0u) : 0u;
+            if (v) atomicAdd((unsigned long long *)&H[k], (unsigned long long)v);
+        }
+    } else {
+        uint32_t *h16 = lds + M::TAB / 4;
+        for (int i = lane; i <= M::K / 2; i += 64) {
+            const uint32_t v = h16[i] ? atomicExch(&h16[i], 0u) : 0u;
+            if (v & 0xFFFFu) atomicAdd((unsigned long long *)&H[2 * i], (unsigned long long)(v & 0xFFFFu));
+            if (v >> 16) atomicAdd((unsigned long long *)&H[2 * i + 1], (unsigned long long)(v >> 16));
         }
     }
-    __syncthreads();
-}
-
-// Table entry of an update with unsatisfied-bond count a (dl = 2 - a):
-// entries 0..3 are dl = -2, -1, +1, +2, i.e. a = 4, 3, 1, 0 (a = 2 is always
-// accepted; its entry is never used).
-__device__ __forceinline__ int entry_of(int a)
-{
-    return 3 - a + ((a + 5) >> 3);
 }
 
 template <int L>
-__global__ __launch_bounds__(64) void k_muca_w(MucaArgs a)
+__global__ __launch_bounds__(64 * kMucaMaxWaves) void k_muca_q(MucaArgs a)
 {
-    static_assert(L % 32 == 0, "whole 32-bit words per row");
-    constexpr int N = L * L, NW = L / 32, K = N / 2, NH = K / 2 + 1;
-    // rows between flushes: 64 walkers x L updates per row, below 2^16 per level
-    constexpr int FL = 65535 / (64 * L);
-    static_assert(FL >= 1, "flush interval");
+    using R = QuadRow<L>;
+    using M = MucaRow<L>;
+    constexpr int N = L * L, K = N / 2, NW = R::NW, CB = R::CB, S = M::S;
     extern __shared__ __align__(16) uint32_t lds[];
-    const uint32_t *tab = lds;  // [K + 1][4] thresholds minus one for dl = -2, -1, +1, +2
-    uint32_t *h16 = lds + 4 * (K + 1);
-    const int lane = threadIdx.x;
-    for (int i = lane; i < 4 * (K + 1); i += 64) lds[i] = a.table[i];
-    for (int i = lane; i < NH; i += 64) h16[i] = 0u;
+    const int tid = threadIdx.x, nt = blockDim.x, q = tid & 3;
+    // thresholds: word c of row k (wide: c = a; else c = 0, 1, 2, 3 for
+    // a = 0, 1, 4, 3); entries 0..3 of a.table are steps -2, -1, +1, +2
+    for (int i = tid; i < (K + 1) * 4; i += nt) {
+        const int k = i >> 2, e = i & 3, step = e < 2 ? e - 2 : e - 1;
+        const uint32_t v = a.table[i];
+        const uint32_t T = k + step > K ? 0u : v == ~0u ? ~0u : v + 1u;
+        if constexpr (M::kWide) lds[k * 6 + 2 - step] = T;
+        else lds[k * 4 + (step == -2 ? 2 : 2 - step)] = T;
+    }
+    if constexpr (M::kWide) {
+        for (int k = tid; k <= K; k += nt) {
+            lds[k * 6 + 2] = ~0u;
+            lds[k * 6 + 5] = 0u;
+        }
+    } else {
+        for (int i = tid; i <= K / 2; i += nt) lds[M::TAB / 4 + i] = 0u;
+    }
     __syncthreads();
-    // lanes past the last walker follow walker W - 1 without storing anything,
-    // so the wave stays whole for the histogram flushes
-    const int wr = blockIdx.x * 64 + lane;
+    // lanes past the last walker follow walker W - 1 (in the same wave, in step
+    // with it) without storing anything; a wave with no walker has nothing to do
+    const int wr = blockIdx.x * (nt >> 2) + (tid >> 2);
+    if ((int)(blockIdx.x * (nt >> 2) + ((tid & ~63) >> 2)) >= a.W) return;
     const bool live = wr < a.W;
     const int w = live ? wr : a.W - 1;
     int8_t *sp = a.spins + (int64_t)w * N;
-    uint32_t *gh = a.hist + (int64_t)blockIdx.x * (K + 1);
     const uint32_t rec = (a.record && live) ? 1u : 0u;
-    // chain state: level before the previous update (kp), its dl and acceptance
-    int kp = (int)((a.E[w] + 2 * N) / 4), dlp = 0;
-    bool accp = false;
+    // 16-bit counts: between two exchanges of a word, whichever wave makes them,
+    // each of the workgroup's waves adds at most kFlushRows rows of 16 walkers
+    constexpr int kFlushRows = 65535 / (16 * kMucaMaxWaves * L) > 0 ? 65535 / (16 * kMucaMaxWaves * L) : 1;
+    // z: LDS address of the level's row, plus 8 where the row is indexed by -4 step
+    const int zb = lds_addr(lds) + (M::kWide ? 8 : 0);
+    int z = S * (int)((a.E[w] + 2 * N) / 4) + zb;
     for (int t = 0; t < a.nsweeps; ++t) {
         const uint64_t sweep = a.sweep0 + (uint64_t)t;
         const uint32_t w3 = ctr_w3(kTagMuca, 0, sweep);
-        uint32_t U[NW], C[NW], D[NW], R0[NW];
-        uint4 raw[L / 16];
-        load_row_raw<L>(sp, L - 1, raw);
-        pack_raw<L>(raw, U);
-        load_row_raw<L>(sp, 0, raw);
-        pack_raw<L>(raw, C);
-        load_row_raw<L>(sp, 1, raw);
-        pack_raw<L>(raw, D);
+        uint4 blk = make_uint4(0u, 0u, 0u, 0u);
+        if (R::kAhead) blk = philox(make_uint4((uint32_t)q, (uint32_t)w, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
+        uint32_t U[NW], C[NW], D[NW], R0[NW], raw[R::RD];
+        quad_load<L>(sp, L - 1, q, raw);
+        quad_pack<L>(raw, U);
+        quad_load<L>(sp, 0, q, raw);
+        quad_pack<L>(raw, C);
+        quad_load<L>(sp, 1, q, raw);
+        quad_pack<L>(raw, D);
         int rows_since_flush = 0;
         for (int y = 0; y < L; ++y) {
             const bool pre = y + 2 < L;
-            if (pre) load_row_raw<L>(sp, y + 2, raw);
+            if (pre) quad_load<L>(sp, y + 2, q, raw);
             for (int wi = 0; wi < NW; ++wi) {
                 const uint32_t c0 = C[0], u = U[0], d = D[0];
-                const uint32_t lb = C[NW - 1] >> 31;  // site x - 1 of bit 0 (final value)
-                const uint32_t rb = NW > 1 ? (C[NW > 1 ? 1 : 0] & 1u) : 0u;
-                const uint32_t X = c0 ^ u, Y = c0 ^ d, Z = c0 ^ ((c0 >> 1) | (rb << 31));
-                const uint32_t p0 = X ^ Y ^ Z, p1 = (X & Y) | (X & Z) | (Y & Z);
-                const uint32_t lw = c0 ^ ((c0 << 1) | lb);
-                const uint32_t ctr0 = (uint32_t)(L * y + 32 * wi) >> 2;
+                QuadPlanes P = quad_planes<CB>(c0, u, d, C[NW - 1] >> (CB - 1),
+                                                     C[NW > 1 ? 1 : 0] & 1u);
                 uint32_t F = 0u;
-                uint4 blk = make_uint4(0u, 0u, 0u, 0u);
-                // counts of bit 0 (its left neighbour is final: one outcome)
-                int a0 = (int)((p0 & 1u) + ((p1 & 1u) << 1) + (lw & 1u)), a1 = a0;
-                // thresholds of bit 0 for both outcomes of the previous update
-                uint32_t T0 = tab[4 * kp + entry_of(a0)];
-                const int kq = kp + dlp;
-                uint32_t T1 = tab[4 * (kq < K ? kq : K) + entry_of(a1)];
+                bool acc = false;  // previous update's outcome (resolved before a word)
+                for (int g = 0; g < (CB + 15) / 16; ++g) {  // one group, or two of a 32-bit word
+                    // this lane's share of the group: four random words and counts
+                    const int sh = 16 * g + 4 * q;
+                    const uint32_t ctr0 = (uint32_t)(L * y + CB * wi + sh) >> 2;
+                    if (!R::kAhead)
+                        blk = philox(make_uint4(ctr0, (uint32_t)w, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
+                    PhiloxRounds ahead;
+                    ahead.c = make_uint4(ctr0 + 4u, (uint32_t)w, (uint32_t)sweep, w3);
+                    const uint32_t r4[4] = {min(blk.x, 0xFFFFFFFEu), min(blk.y, 0xFFFFFFFEu), min(blk.z, 0xFFFFFFFEu),
+                                            min(blk.w, 0xFFFFFFFEu)};
+                    const QuadCounts qc = quad_counts(P, sh);
+                    // i0, i1: table offset for a rejected / accepted previous
+                    // update; s0, s1: the step in bytes
+                    int i0[4], i1[4], s0[4], s1[4];
 #pragma unroll
-                for (int b = 0; b < 32; ++b) {
-                    if ((b & 3) == 0)
-                        blk = philox(make_uint4(ctr0 + (uint32_t)(b >> 2), (uint32_t)w, (uint32_t)sweep, w3), a.seed_lo,
-                                     a.seed_hi);
-                    const uint32_t r = (b & 3) == 0 ? blk.x : (b & 3) == 1 ? blk.y : (b & 3) == 2 ? blk.z : blk.w;
-                    // both outcomes of the previous update, off the chain
-                    const int kA = kp + dlp;
-                    const bool ab0 = (a0 == 2) || (kp + 2 - a0 <= K && r <= T0);
-                    const bool ab1 = (a1 == 2) || (kA + 2 - a1 <= K && r <= T1);
-                    // on the chain: the previous update's acceptance selects
-                    const int kb = accp ? kA : kp;
-                    const bool ab = accp ? ab1 : ab0;
-                    const int dlb = 2 - (accp ? a1 : a0);
-                    const int kn = kb + dlb;
-                    // counts of the next bit for both outcomes of this update, and
-                    // their thresholds (read now, used next step)
-                    if (b < 31) {
-                        int Pn;
-                        if (NW == 1 && b + 1 == 31) {
-                            // one-word row: the right neighbour of bit 31 is bit 0, already updated
-                            Pn = (int)((X >> 31) + (Y >> 31) + ((c0 >> 31) ^ ((c0 ^ F) & 1u)));
+                    for (int i = 0; i < 4; ++i) {
+                        const int a0 = qc.n3[i] + qc.l[i], a1 = qc.n3[i] + 1 - qc.l[i];
+                        if constexpr (M::kWide) {
+                            i0[i] = 4 * a0 - 8;
+                            i1[i] = 4 * a1 - 8;
                         } else {
-                            Pn = (int)(((p0 >> (b + 1)) & 1u) + (((p1 >> (b + 1)) & 1u) << 1));
+                            i0[i] = 4 * a0 - ((a0 >> 2) << 3);
+                            i1[i] = 4 * a1 - ((a1 >> 2) << 3);
                         }
-                        const int ln = (int)((lw >> (b + 1)) & 1u);
-                        a0 = Pn + ln;
-                        a1 = Pn + 1 - ln;
-                        T0 = tab[4 * kb + entry_of(a0)];
-                        T1 = tab[4 * (kn < K ? kn : K) + entry_of(a1)];
+                        s0[i] = __mul24(a0, -S) + 2 * S;
+                        s1[i] = __mul24(a1, -S) + 2 * S;
                     }
-                    const int ka = ab ? kn : kb;
-                    atomicAdd(&h16[ka >> 1], rec << ((ka & 1) << 4));
-                    F |= ab ? (1u << b) : 0u;
-                    kp = kb;
-                    dlp = dlb;
-                    accp = ab;
+                    // zn: the level the update leads to; T0, T1: its threshold for a
+                    // rejected / accepted previous update
+                    uint32_t T0, T1;
+                    const int x0 = z + (int)quad_get((uint32_t)i0[0], 0), x1 = z + (int)quad_get((uint32_t)i1[0], 0);
+                    const int v0 = z + (int)quad_get((uint32_t)s0[0], 0), v1 = z + (int)quad_get((uint32_t)s1[0], 0);
+                    T0 = T1 = lds_read(acc ? x1 : x0);
+                    int zn = acc ? v1 : v0, zc = z;
+                    uint32_t Fg = 0u;
+                    bool ok0 = false;
+#pragma unroll
+                    for (int b = 0; b < 16; ++b) {
+                        if (b >= CB) break;
+                        const int Q = b >> 2, I = b & 3, Qn = (b + 1) >> 2, In = (b + 1) & 3;
+                        // next update, for both outcomes of this one: where it leads
+                        // and its thresholds
+                        uint32_t N0 = 0u, N1 = 0u;
+                        int p0 = 0, p1 = 0;
+                        if (b < 15) {
+                            N0 = lds_read(z + (int)quad_get((uint32_t)i0[In], Qn));
+                            N1 = lds_read(zn + (int)quad_get((uint32_t)i1[In], Qn));
+                            p0 = z + (int)quad_get((uint32_t)s0[In], Qn);
+                            p1 = zn + (int)quad_get((uint32_t)s1[In], Qn);
+                        }
+                        // the reads go out before the decision waits for the last ones
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (R::kAhead && b < 10) {
+                            ahead.round(b, a.seed_lo, a.seed_hi);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        uint32_t r = quad_get(r4[I], Q);
+                        if (!M::kWide) r = zn == z ? 0u : r;  // a = 2: any threshold accepts
+                        const bool ok = r < (acc ? T1 : T0);
+                        z = ok ? zn : z;
+                        zn = ok ? p1 : p0;
+                        Fg = shift_in(Fg, __ballot(ok));
+                        zc = q == I ? z : zc;
+                        if (I == 3 && a.record) {
+                            if constexpr (M::kWide) {
+                                lds_add(zc + 12, rec);
+                            } else {
+                                const int kc = zc - zb;  // 16 k: word k / 2, half k mod 2
+                                lds_add(zb + M::TAB + ((kc >> 3) & ~3), rec << (kc & 16));
+                            }
+                        }
+                        if (b == 0) ok0 = ok;
+                        if (NW == 1 && CB <= 16 && b == 1) {
+                            // one-word row: the right neighbour of the last site is
+                            // site 0, flipped by now if its update was accepted
+                            const int e = (q == (CB - 1) / 4 && ok0) ? (((P.z >> (CB - 1)) & 1u) ? -1 : 1) : 0;
+                            i0[(CB - 1) & 3] += 4 * e;
+                            i1[(CB - 1) & 3] += 4 * e;
+                            s0[(CB - 1) & 3] -= S * e;
+                            s1[(CB - 1) & 3] -= S * e;
+                        }
+                        acc = ok;
+                        T0 = N0;
+                        T1 = N1;
+                    }
+                    if (R::kAhead) blk = ahead.c;
+                    F |= (__brev(Fg) >> (CB < 16 ? 32 - CB : 16)) << (16 * g);
+                    // one-word row: the last site's right neighbour is site 0
+                    if (NW == 1 && CB > 16)
+                        P = quad_planes<CB>(c0, u, d, c0 >> (CB - 1), (c0 ^ F) & 1u);
                 }
                 // rotate: the processed word goes last, the next word to index 0
                 const uint32_t cn = c0 ^ F;
@@ -268,7 +311,7 @@ __global__ __launch_bounds__(64) void k_muca_w(MucaArgs a)
                 U[NW - 1] = u;
                 D[NW - 1] = d;
             }
-            if (live) store_row_w<L>(sp, y, C);
+            quad_store<L>(sp, y, q, live, C);
             if (y == 0) {
 #pragma unroll
                 for (int i = 0; i < NW; ++i) R0[i] = C[i];
@@ -278,19 +321,19 @@ __global__ __launch_bounds__(64) void k_muca_w(MucaArgs a)
                 U[i] = C[i];
                 C[i] = D[i];
             }
-            if (pre) pack_raw<L>(raw, D);
+            if (pre) quad_pack<L>(raw, D);
             else {
 #pragma unroll
                 for (int i = 0; i < NW; ++i) D[i] = R0[i];
             }
-            if (a.record && (++rows_since_flush == FL || y == L - 1)) {
-                flush_hist16(h16, gh, NH, K, lane);
+            if (!M::kWide && a.record && ++rows_since_flush == kFlushRows) {
+                muca_flush<L>(lds, a.H, tid & 63);
                 rows_since_flush = 0;
             }
         }
     }
-    const int kf = kp + (accp ? dlp : 0);
-    if (live) a.E[w] = 4 * (int64_t)kf - 2 * N;
+    if (a.record) muca_flush<L>(lds, a.H, tid & 63);
+    if (live && q == 0) a.E[w] = 4 * (int64_t)((z - zb) / S) - 2 * N;
 }
 
 // Walker start: hot start keyed by the walker index (already written by the
@@ -332,23 +375,36 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n)
         p[i] = 0u;
 }
 
+// One lane per walker, counts in global slices; taken only when a threshold is
+// 2^32 - 1, which k_muca_q cannot tell from 2^32.
+template <int L>
+static hipError_t launch_muca_edge(const MucaArgs &a, hipStream_t s)
+{
+    constexpr int K = L * L / 2;
+    const int nb = (a.W + 63) / 64;
+    if (a.record) hipLaunchKernelGGL(k_fill_u32, dim3(256), dim3(256), 0, s, a.hist, (int64_t)nb * (K + 1));
+    const size_t lds = (size_t)(K + 1) * 4 * 4;
+    static LdsLimit lim;
+    const hipError_t e = lim.ensure((const void *)k_muca<L>, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_muca<L>, dim3(nb), dim3(64), lds, s, a);
+    if (a.record) hipLaunchKernelGGL(k_muca_merge, dim3((K + 256) / 256), dim3(256), 0, s, a.hist, nb, K + 1, a.H);
+    return hipGetLastError();
+}
+
 template <int L>
 static hipError_t launch_muca_L(const MucaArgs &a, hipStream_t s)
 {
-    constexpr int K = L * L / 2;
-    if constexpr (L % 32 == 0) {
-        const size_t lds = (size_t)(K + 1) * 16 + (size_t)(K / 2 + 1) * 4;
-        static LdsLimit lim;
-        const hipError_t e = lim.ensure((const void *)k_muca_w<L>, (int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_muca_w<L>, dim3((a.W + 63) / 64), dim3(64), lds, s, a);
-    } else {
-        const size_t lds = (size_t)(K + 1) * 4 * 4;
-        static LdsLimit lim;
-        const hipError_t e = lim.ensure((const void *)k_muca<L>, (int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_muca<L>, dim3((a.W + 63) / 64), dim3(64), lds, s, a);
-    }
+    if (a.edge) return launch_muca_edge<L>(a, s);
+    static LdsLimit lim;
+    const hipError_t e = lim.ensure((const void *)k_muca_q<L>, MucaRow<L>::LDS);
+    if (e != hipSuccess) return e;
+    // one wave per workgroup until every CU has one, then up to four waves
+    // sharing a table (at L = 128 a CU holds one table)
+    constexpr int kCUs = 256;
+    const int waves = (a.W + 15) / 16;
+    const int per = std::min(kMucaMaxWaves, std::max(1, (waves + kCUs - 1) / kCUs));
+    hipLaunchKernelGGL(k_muca_q<L>, dim3((waves + per - 1) / per), dim3(64 * per), MucaRow<L>::LDS, s, a);
     return hipGetLastError();
 }
 
@@ -362,26 +418,19 @@ bool muca_L_supported(int L)
 
 hipError_t launch_muca_sweeps(const MucaArgs &a, int L, hipStream_t s)
 {
-    const int nlev = L * L / 2 + 1, nb = (a.W + 63) / 64;
-    if (a.record) hipLaunchKernelGGL(k_fill_u32, dim3(256), dim3(256), 0, s, a.hist, (int64_t)nb * nlev);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     switch (L) {
-    case 4: e = launch_muca_L<4>(a, s); break;
-    case 8: e = launch_muca_L<8>(a, s); break;
-    case 12: e = launch_muca_L<12>(a, s); break;
-    case 16: e = launch_muca_L<16>(a, s); break;
-    case 24: e = launch_muca_L<24>(a, s); break;
-    case 32: e = launch_muca_L<32>(a, s); break;
-    case 48: e = launch_muca_L<48>(a, s); break;
-    case 64: e = launch_muca_L<64>(a, s); break;
-    case 96: e = launch_muca_L<96>(a, s); break;
-    case 128: e = launch_muca_L<128>(a, s); break;
+    case 4: return launch_muca_L<4>(a, s);
+    case 8: return launch_muca_L<8>(a, s);
+    case 12: return launch_muca_L<12>(a, s);
+    case 16: return launch_muca_L<16>(a, s);
+    case 24: return launch_muca_L<24>(a, s);
+    case 32: return launch_muca_L<32>(a, s);
+    case 48: return launch_muca_L<48>(a, s);
+    case 64: return launch_muca_L<64>(a, s);
+    case 96: return launch_muca_L<96>(a, s);
+    case 128: return launch_muca_L<128>(a, s);
     default: return hipErrorInvalidValue;
     }
-    if (e != hipSuccess) return e;
-    if (a.record) hipLaunchKernelGGL(k_muca_merge, dim3((nlev + 255) / 256), dim3(256), 0, s, a.hist, nb, nlev, a.H);
-    return hipGetLastError();
 }
 
 // Level of disorder of walker w of W in the stratified start: the largest c

@@ -92,7 +92,8 @@ int run_muca_sweeps(mc_ctx *ctx, int L, int W, int8_t *spins, int64_t *E, const 
     a.seed_lo = (uint32_t)seed;
     a.seed_hi = (uint32_t)(seed >> 32);
     a.record = record;
-    // per-workgroup 32-bit counts stay below 2^32: at most 64 N sweeps' worth
+    a.edge = std::find(T.begin(), T.end(), 0xFFFFFFFEu) != T.end();
+    // per-workgroup 32-bit counts stay below 2^32: at most 64 walkers share them
     const int chunk = (int)std::max<int64_t>(1, (int64_t)4294967295ll / (64ll * L * L));
     for (int done = 0; done < nsweeps && e == hipSuccess;) {
         const int n = std::min(chunk, nsweeps - done);
