@@ -330,16 +330,12 @@ __global__ __launch_bounds__(256) void k_pa_sweep(PaStep st)
 {
     extern __shared__ uint32_t lds[];
     __shared__ int e_lat[64];
-    __shared__ LdsTieQueue tq;
     int p = 0;
     while (p + 1 < st.npop && (int)blockIdx.x >= st.pop[p + 1].blk0) ++p;
     const PaPop &P = st.pop[p];
-    LdsLattices a;
-    a.L = P.L;
-    a.N = P.N;
-    a.Wb = P.Wb;
-    a.nwr = P.nwr;
+    LdsLattices a = lds_lattices(P.L);
     const int s0 = ((int)blockIdx.x - P.blk0) * P.G;
+    a.ng_max = P.G;
     a.ng = min(P.G, P.R - s0);
     a.rep0 = (uint32_t)p * (uint32_t)P.R + (uint32_t)s0;
     a.sweep0 = (uint64_t)(st.step - 1) * (uint64_t)st.theta;
@@ -347,20 +343,19 @@ __global__ __launch_bounds__(256) void k_pa_sweep(PaStep st)
     a.seed_lo = st.seed_lo;
     a.seed_hi = st.seed_hi;
     const int tid = threadIdx.x, nt = blockDim.x;
-    const int L = a.L, N = a.N, nwr = a.nwr;
+    const int N = P.N;
     if (tid < 64) e_lat[tid] = 0;
 
     // ---- gather the parents and pack
-    const int tasks_ld = a.ng * L * nwr;
+    const int tasks_ld = a.ng * a.P;
     for (int t = tid; t < tasks_ld; t += nt) {
-        const int g = t / (L * nwr), rem = t - g * L * nwr, r = rem / nwr, w = rem - r * nwr;
-        const int slot = s0 + g;
+        const int g = lds_div(t, a.P, a.inv_p), slot = s0 + g;
         const int parent = st.identity ? slot : P.newparent[slot];
-        pack_lattice_rows(lds, a, g, P.cur + (int64_t)parent * N, r, w);
+        pack_lattice_words(lds, a, g, P.cur + (int64_t)parent * N, t - g * a.P);
     }
     __syncthreads();
 
-    sweep_lds_lattices<false>(lds, a, st.t4, st.t8, nullptr, nullptr, tq, e_lat);
+    sweep_lds_lattices<false>(lds, a, lds_thr(st.t4), lds_thr(st.t8), nullptr, nullptr, e_lat);
 
     if (tid < a.ng) {
         const int slot = s0 + tid;
@@ -371,8 +366,8 @@ __global__ __launch_bounds__(256) void k_pa_sweep(PaStep st)
 
     // ---- unpack and store the new population
     for (int t = tid; t < tasks_ld; t += nt) {
-        const int g = t / (L * nwr), rem = t - g * L * nwr, r = rem / nwr, w = rem - r * nwr;
-        unpack_lattice_rows(lds, a, g, P.nxt + (int64_t)(s0 + g) * N, r, w);
+        const int g = lds_div(t, a.P, a.inv_p);
+        unpack_lattice_words(lds, a, g, P.nxt + (int64_t)(s0 + g) * N, t - g * a.P);
     }
 }
 
@@ -387,12 +382,13 @@ hipError_t launch_pa_step(const PaStep &st, int rmax, int sweep_blocks, hipStrea
         hipLaunchKernelGGL(k_pa_place, dim3((rmax + kPlaceChunk - 1) / kPlaceChunk, st.npop), dim3(kPlaceThreads), 0,
                            s, st);
     }
+    const int threads = lds_lattice_threads(sweep_blocks);
     size_t lds = 0;
     for (int p = 0; p < st.npop; ++p) {
-        const size_t b = (size_t)st.pop[p].G * 2 * st.pop[p].L * st.pop[p].nwr * 4;
+        const size_t b = lds_lattice_bytes(st.pop[p].L, st.pop[p].G, threads);
         if (b > lds) lds = b;
     }
-    hipLaunchKernelGGL(k_pa_sweep, dim3(sweep_blocks), dim3(256), lds, s, st);
+    hipLaunchKernelGGL(k_pa_sweep, dim3(sweep_blocks), dim3(threads), lds, s, st);
     return hipGetLastError();
 }
 

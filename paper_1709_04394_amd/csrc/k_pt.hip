@@ -25,38 +25,34 @@ __global__ __launch_bounds__(256) void k_pt_sweep(PtSweepArgs a)
     extern __shared__ uint32_t lds[];
     __shared__ int e_lat[64];
     __shared__ Thr t4s[64], t8s[64];
-    __shared__ LdsTieQueue tq;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int s0 = (int)blockIdx.x * a.G;
-    LdsLattices la;
-    la.L = a.L;
-    la.N = a.L * a.L;
-    la.Wb = a.Wb;
-    la.nwr = a.nwr;
+    LdsLattices la = lds_lattices(a.L);
+    la.ng_max = a.G;
     la.ng = min(a.G, a.count - s0);
     la.rep0 = (uint32_t)s0;  // lattice l = set s, replica r is replica id s n_temps + r = l
     la.sweep0 = a.sweep0;
     la.theta = a.theta;
     la.seed_lo = a.seed_lo;
     la.seed_hi = a.seed_hi;
-    const int L = la.L, N = la.N, nwr = la.nwr;
+    const int N = la.L * la.L;
     if (tid < 64) e_lat[tid] = 0;
     if (tid < la.ng) {
         const int ti = a.temp_of[s0 + tid];
-        t4s[tid] = a.thr[2 * ti];
-        t8s[tid] = a.thr[2 * ti + 1];
+        t4s[tid] = lds_thr(a.thr[2 * ti]);
+        t8s[tid] = lds_thr(a.thr[2 * ti + 1]);
     }
-    const int tasks = la.ng * L * nwr;
+    const int tasks = la.ng * la.P;
     for (int t = tid; t < tasks; t += nt) {
-        const int g = t / (L * nwr), rem = t - g * L * nwr, r = rem / nwr, w = rem - r * nwr;
-        pack_lattice_rows(lds, la, g, a.spins + (int64_t)(s0 + g) * N, r, w);
+        const int g = lds_div(t, la.P, la.inv_p);
+        pack_lattice_words(lds, la, g, a.spins + (int64_t)(s0 + g) * N, t - g * la.P);
     }
     __syncthreads();
-    sweep_lds_lattices<true>(lds, la, Thr{}, Thr{}, t4s, t8s, tq, e_lat);
+    sweep_lds_lattices<true>(lds, la, Thr{}, Thr{}, t4s, t8s, e_lat);
     if (tid < la.ng) a.E[s0 + tid] = e_lat[tid];
     for (int t = tid; t < tasks; t += nt) {
-        const int g = t / (L * nwr), rem = t - g * L * nwr, r = rem / nwr, w = rem - r * nwr;
-        unpack_lattice_rows(lds, la, g, a.spins + (int64_t)(s0 + g) * N, r, w);
+        const int g = lds_div(t, la.P, la.inv_p);
+        unpack_lattice_words(lds, la, g, a.spins + (int64_t)(s0 + g) * N, t - g * la.P);
     }
 }
 
@@ -99,8 +95,8 @@ __global__ __launch_bounds__(1024) void k_pt_exchange(PtExchangeArgs a)
 hipError_t launch_pt_round(const PtSweepArgs &sw, const PtExchangeArgs &ex, int n_sets, hipStream_t s)
 {
     const int blocks = (sw.count + sw.G - 1) / sw.G;
-    const size_t lds = (size_t)sw.G * 2 * sw.L * sw.nwr * 4;
-    hipLaunchKernelGGL(k_pt_sweep, dim3(blocks), dim3(256), lds, s, sw);
+    const int wg = lds_lattice_threads(blocks);
+    hipLaunchKernelGGL(k_pt_sweep, dim3(blocks), dim3(wg), lds_lattice_bytes(sw.L, sw.G, wg), s, sw);
     const int threads = ((ex.n_temps + 63) / 64) * 64;
     hipLaunchKernelGGL(k_pt_exchange, dim3(n_sets), dim3(threads), 0, s, ex);
     return hipGetLastError();

@@ -10,7 +10,6 @@ constexpr int kPaMaxChunks = 1024;  // R <= 64 * 1024 replicas per population
 
 struct PaPop {
     int L, N, R;
-    int Wb, nwr;            // bits per LDS word, words per row and parity
     int G;                  // lattices per workgroup in k_pa_sweep
     int blk0;               // first k_pa_sweep block of this population
     const int8_t *cur;      // population before the step [R][N]

@@ -149,8 +149,6 @@ int mc_pa_anneal(mc_ctx *ctx, const mc_pa_args *a, void *const *pop_spins, doubl
         P.L = a->L[p];
         P.N = P.L * P.L;
         P.R = a->R;
-        P.Wb = std::min(32, P.L / 2);
-        P.nwr = pa_words_per_row(P.L);
         P.G = pa_group_for(ctx, P.L);
         P.blk0 = blocks;
         blocks += (P.R + P.G - 1) / P.G;

@@ -9,7 +9,7 @@ constexpr int kPtMaxTemps = 1024;  // temperatures per set: one exchange workgro
 
 struct PtSweepArgs {
     int8_t *spins;              // [count][L^2], lattice l = set s, replica r at l = s n_temps + r
-    int L, Wb, nwr, G;          // extent, LDS word layout, lattices per workgroup
+    int L, G;                   // extent, lattices per workgroup
     int count;                  // n_sets * n_temps
     const int32_t *temp_of;     // [count] temperature index held by lattice l
     const Thr *thr;             // [n_temps][2] Metropolis thresholds dE = 4, 8

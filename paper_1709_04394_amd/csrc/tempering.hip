@@ -208,8 +208,6 @@ int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of,
     PtSweepArgs sw{};
     sw.spins = spins;
     sw.L = a->L;
-    sw.Wb = std::min(32, a->L / 2);
-    sw.nwr = pa_words_per_row(a->L);
     sw.G = pa_group_for(ctx, a->L);
     sw.count = count;
     sw.temp_of = (const int32_t *)(w + lay.temp_of);
