@@ -22,10 +22,10 @@
 //  * The random top bytes of those 32 sites are eight bit-planes taken straight
 //    from two Philox blocks; r32 < T becomes a bit-serial comparison of the
 //    planes with the threshold's top byte.  Words with ties (a site whose top
-//    byte equals the threshold's, probability 1/256 per site) go to a
-//    workgroup queue in LDS, one item per word, and are settled together at
-//    the end of the half-sweep with one low-24-bit draw per tied site, so a tie
-//    in one lane does not stall the other 63.
+//    byte equals its class's threshold's, probability 1/256 per site) go to a
+//    queue of their wave in LDS, one item per word, and are settled up to 64 at
+//    a time with one low-24-bit draw per tied site, so a tie in one lane does
+//    not stall the other 63 and no wave waits for another's (metro2d.hpp).
 //  * Energy and magnetisation of each sweep come from the odd half-sweep:
 //    every bond has exactly one odd end, and when the odd sites of a row are
 //    updated its even sites are already final, so the band's own rows give E
@@ -35,16 +35,18 @@
 //    (em_slots.hpp).
 //  * Several lattices (each with its own inverse temperature) can share one
 //    launch, which gives taller bands and so less redone halo.
+//
+// What bounds it: VALU issue, about 170 instructions of a wave per 64 words of
+// 32 sites (74 of them Philox) and 55 per settled batch of ties, then the
+// barriers' and the launch's latency.  Three 4096^2 lattices, bands of 16 rows,
+// 2 sweeps per launch, 512 threads, (E, M) every sweep: 15.1 us per sweep
+// against 17.8 with a comparison per class, both sideways words read, and ties
+// settled by the whole workgroup between two barriers.
 #include "em_slots.hpp"
 #include "internal.hpp"
+#include "metro2d.hpp"
 
 namespace mcs {
-
-// Tie-queue items per workgroup (split evenly over its waves).  One item is a
-// word with at least one tied site; a wave expects about
-// 1 - (1 - 0.6/256)^32 ~ 7% of its 32-site words to have one.  A full segment
-// falls back to drawing the ties in place.
-constexpr int kTieQueue = 512;
 
 struct Tile2DArgs {
     const void *src;                // int8 lattices, or packed rows if in_packed
@@ -60,30 +62,12 @@ struct Tile2DArgs {
     EmSlots em;                     // band sums of this launch and the previous one
 };
 
-// Draw the low 24 bits of every tied site of one word (bits of p8 | p4) and
-// return the mask of those that are accepted.
-__device__ __forceinline__ uint32_t settle_ties(uint32_t p8, uint32_t p4, uint32_t blk, uint32_t rep,
-                                                uint32_t sweep_lo, uint32_t w3lo, uint32_t k0, uint32_t k1,
-                                                const Thr &t4, const Thr &t8)
-{
-    uint32_t pend = p8 | p4, acc = 0u;
-    while (pend) {
-        const int b = __builtin_ctz(pend);
-        pend &= pend - 1u;
-        const uint4 lo = philox(make_uint4(16u * blk + (uint32_t)b, rep, sweep_lo, w3lo), k0, k1);
-        if ((lo.x & 0xFFFFFFu) < (((p8 >> b) & 1u) ? t8.low : t4.low)) acc |= 1u << b;
-    }
-    return acc;
-}
-
 template <int K, bool MEASURE>
 __global__ __launch_bounds__(1024) void k_tile2d(Tile2DArgs a)
 {
     extern __shared__ uint32_t lds[];
     __shared__ int red[2][16];
     __shared__ long long red64[2][16];
-    __shared__ uint32_t q_ws[kTieQueue], q_blk[kTieQueue], q_p8[kTieQueue], q_p4[kTieQueue];
-    __shared__ uint32_t q_cnt[16];  // items queued by each wave in this half-sweep
     const int l = blockIdx.y;
     const int y0 = blockIdx.x * a.H;
     const int Hh = min(a.H, a.Ly - y0);
@@ -95,7 +79,7 @@ __global__ __launch_bounds__(1024) void k_tile2d(Tile2DArgs a)
     const uint32_t rep = a.replica0 + (uint32_t)l;
     const Thr t4 = a.t4[a.per_lattice ? l : 0];
     const Thr t8 = a.t8[a.per_lattice ? l : 0];
-    const TopMask m4 = top_mask(t4.top), m8 = top_mask(t8.top);
+    const MetroMasks mm = metro_masks(t4.top, t8.top, true);
     // thread -> (word column, first row, row stride); no division in the loops
     int P, Q, w0, r0;
     if (Wd <= nt) {
@@ -103,7 +87,7 @@ __global__ __launch_bounds__(1024) void k_tile2d(Tile2DArgs a)
         Q = nt / Wd;
         w0 = tid % Wd;
         r0 = tid / Wd;
-        if (r0 >= Q) r0 = 1 << 30;  // surplus threads idle
+        if (r0 >= Q) r0 = 1 << 28;  // surplus threads idle
     } else {
         P = nt;
         Q = 1;
@@ -117,11 +101,8 @@ __global__ __launch_bounds__(1024) void k_tile2d(Tile2DArgs a)
         while (y >= a.Ly) y -= a.Ly;
         return y;
     };
-    // tie queue: wave w owns items [w * wq_cap, (w + 1) * wq_cap); its fill
-    // level wq_n is wave-uniform
     const int wave = tid >> 6, nwaves = nt >> 6;
-    const uint32_t wq_cap = (uint32_t)(kTieQueue / nwaves), wq_base = (uint32_t)wave * wq_cap;
-    uint32_t wq_n = 0;
+    uint4 *const tq = (uint4 *)(lds + ((rows * 2 * Wd + 3) & ~3)) + wave * kTieQueue;
     const int ntile = gridDim.x, nlat = gridDim.y;
     long long pre_e, pre_m;
     em_prefetch(a.em, blockIdx.x, ntile, l, nlat, tid, pre_e, pre_m);
@@ -165,123 +146,107 @@ __global__ __launch_bounds__(1024) void k_tile2d(Tile2DArgs a)
     __syncthreads();
     em_reduce(a.em, blockIdx.x, ntile, l, nlat, tid, nt, pre_e, pre_m, red64);
 
+    const int Qm = Q % a.Ly, iters_w = (Wd + P - 1) / P;
+    int yn = lat_row(r0 < rows ? r0 : 0);  // lattice row of LDS row r0, then of the half-sweep's first row
+    const bool own = r0 < rows;
     for (int s = 0; s < K; ++s) {
         const uint64_t sweep = a.sweep0 + (uint64_t)s;
-        int e_acc = 0, m_acc = 0;  // this thread's share of the band's E and M
+        int n_acc = 0, d_acc = 0;  // anti-aligned bonds and down spins of this thread's own words
         for (int c = 0; c < 2; ++c) {
             const int p = 2 * s + c;
             const int r_lo = p + 1, r_hi = rows - p - 1;
             const uint32_t w3 = ctr_w3(kTagSweep, (uint32_t)c, sweep);
             const uint32_t w3lo = ctr_w3(kTagSweepLo, (uint32_t)c, sweep);
-            for (int r = r_lo + r0; r < r_hi; r += Q) {
-                const int y = lat_row(r);
+            uint32_t qn = 0;
+            auto settle = [&]() {
+                const uint32_t i = tid & 63;
+                if (i < qn) {
+                    const uint4 it = tq[i];
+                    const uint32_t f = metro_settle(it.z, it.w, it.y, rep, (uint32_t)sweep, w3lo, a.seed_lo, a.seed_hi,
+                                                    t4.low, t8.low);
+                    if (f) {
+                        const uint32_t ws = it.x & 0x7FFFFFFFu, old = lds[ws];
+                        lds[ws] = old ^ f;
+                        if (MEASURE && (it.x >> 31)) {
+                            // a flip of class dE = 8 (4) gains four (two) anti-aligned bonds
+                            n_acc += 2 * (int)(__builtin_popcount(f) + __builtin_popcount(f & it.w));
+                            d_acc += (int)__builtin_popcount(f) - 2 * (int)__builtin_popcount(old & f);
+                        }
+                    }
+                }
+                qn = 0;
+            };
+            if (++yn >= a.Ly) yn -= a.Ly;
+            int y = yn;
+            for (int rr = r_lo; rr < r_hi; rr += Q) {
+                const int r = rr + r0;
+                const bool active = own && r < r_hi;
                 const int q = (c + y) & 1;
                 const bool interior = MEASURE && c == 1 && r >= R && r < R + Hh;
                 const uint32_t rowblk = (uint32_t)(a.Lx >> 5) * (uint32_t)y;
-                for (int w = w0; w < Wd; w += P) {
-                    const int ws = widx(r, q, w);
-                    const uint32_t S = lds[ws];
-                    const uint32_t U = lds[widx(r - 1, q, w)], D = lds[widx(r + 1, q, w)];
-                    const uint32_t O = lds[widx(r, 1 - q, w)];
-                    // even sites: left neighbours are the odd sites one to the
-                    // left (carry from the previous odd word); odd sites: right
-                    // neighbours are the even sites one to the right
-                    const int wl = w == 0 ? Wd - 1 : w - 1, wr = w + 1 == Wd ? 0 : w + 1;
-                    const uint32_t Ol = lds[widx(r, 1, wl)], Er = lds[widx(r, 0, wr)];
-                    const uint32_t Sh = q == 0 ? __builtin_amdgcn_alignbit(O, Ol, 31) : __builtin_amdgcn_alignbit(Er, O, 1);
-                    const uint32_t u1 = S ^ U, u2 = S ^ D, u3 = S ^ O, u4 = S ^ Sh;
-                    const uint32_t t1 = u1 | u2, t2 = u3 | u4;
-                    // at least two of four anti-aligned neighbours: dE <= 0
-                    const uint32_t ge2 = MCS_BOP3(u1, u2, MCS_BOP3(u3, u4, t1 & t2, (MCS_A & MCS_B) | MCS_C),
-                                                  (MCS_A & MCS_B) | MCS_C);
-                    const uint32_t c8 = ~(t1 | t2);                      // none: dE = 8
-                    const uint32_t c4 = MCS_BOP3(t1, t2, ge2, (MCS_A | MCS_B) & ~MCS_C);  // one: dE = 4
-                    // random planes of the 32 sites j0 .. j0+31, j0 = 32 w + (Lx/2) y
-                    const uint32_t blk = 2u * (uint32_t)w + rowblk;
-                    const uint4 A = philox(make_uint4(blk, rep, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
-                    const uint4 B = philox(make_uint4(blk + 1u, rep, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
-                    uint32_t X[8];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) X[k] = plane_pair(A, B, k);
-                    uint32_t lt8, eq8, lt4, eq4;
-                    compare_planes(X, m8, lt8, eq8);
-                    compare_planes(X, m4, lt4, eq4);
-                    uint32_t acc = MCS_BOP3(ge2, c8, lt8, MCS_A | (MCS_B & MCS_C)) | (c4 & lt4);
-                    const uint32_t p8 = c8 & eq8, p4 = c4 & eq4;
-                    // words with ties join this wave's queue segment, one item
-                    // per word, offsets from ballot + mbcnt
-                    const uint64_t m = __ballot((p8 | p4) != 0u);
-                    if (m) {
-                        if (p8 | p4) {
-                            const uint32_t pos = wq_n + __builtin_amdgcn_mbcnt_hi(
-                                                            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                            if (pos < wq_cap) {
-                                q_ws[wq_base + pos] = (uint32_t)ws | ((uint32_t)interior << 31);
-                                q_blk[wq_base + pos] = blk;
-                                q_p8[wq_base + pos] = p8;
-                                q_p4[wq_base + pos] = p4;
-                            } else {
-                                acc |= settle_ties(p8, p4, blk, rep, (uint32_t)sweep, w3lo, a.seed_lo, a.seed_hi, t4,
-                                                   t8);
-                            }
+                const int row = r * 2 * Wd;
+                for (int j = 0; j < iters_w; ++j) {
+                    const int w = w0 + j * P;
+                    MetroWord mw;
+                    mw.pend = 0u;
+                    uint32_t blk = 0u, ws = 0u;
+                    if (active) {
+                        const int e = row + w, o = e + Wd;  // even- and odd-x words
+                        const int is = q ? o : e, io = q ? e : o;
+                        // even sites: left neighbours are the odd sites one to the
+                        // left (carry from the previous odd word); odd sites: right
+                        // neighbours are the even sites one to the right
+                        const int side = q ? (w + 1 == Wd ? 1 - Wd : 1) : (w == 0 ? Wd - 1 : -1);
+                        const uint32_t S = lds[is], U = lds[is - 2 * Wd], D = lds[is + 2 * Wd], O = lds[io];
+                        const uint32_t Nb = lds[io + side];
+                        const uint32_t Sh = __builtin_amdgcn_alignbit(q ? Nb : O, q ? O : Nb, q ? 1u : 31u);
+                        // random planes of the 32 sites j0 .. j0+31, j0 = 32 w + (Lx/2) y
+                        blk = 2u * (uint32_t)w + rowblk;
+                        const uint4 A = philox(make_uint4(blk, rep, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
+                        const uint4 B = philox(make_uint4(blk + 1u, rep, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
+                        mw = metro_update(S, U, D, O, Sh, A, B, mm);
+                        lds[is] = mw.S;
+                        ws = (uint32_t)is;
+                        if (interior) {
+                            n_acc += (int)(__builtin_popcount(mw.S ^ U) + __builtin_popcount(mw.S ^ D) +
+                                           __builtin_popcount(mw.S ^ O) + __builtin_popcount(mw.S ^ Sh));
+                            d_acc += (int)(__builtin_popcount(mw.S) + __builtin_popcount(O));
                         }
-                        wq_n = min(wq_cap, wq_n + (uint32_t)__popcll(m));
                     }
-                    const uint32_t Sn = S ^ acc;
-                    lds[ws] = Sn;
-                    if (interior) {
-                        // bonds of the odd sites after their update: 2 (#anti-aligned) - 4 each
-                        e_acc += 2 * (int)(__builtin_popcount(u1 ^ acc) + __builtin_popcount(u2 ^ acc) +
-                                           __builtin_popcount(u3 ^ acc) + __builtin_popcount(u4 ^ acc)) -
-                                 128;
-                        m_acc += 64 - 2 * (int)(__builtin_popcount(Sn) + __builtin_popcount(O));
-                    }
-                }
-            }
-            // lanes that left the row loop early hold an older (smaller) fill
-            // level; the lanes that ran longest hold the final one
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) wq_n = max(wq_n, (uint32_t)__shfl_xor((int)wq_n, off, 64));
-            if ((tid & 63) == 0) q_cnt[wave] = wq_n;
-            __syncthreads();
-            // settle the queued words: item i of the concatenated segments goes
-            // to thread i (mod nt); every item is a different word
-            uint32_t total = 0;
-            for (int sg = 0; sg < nwaves; ++sg) total += q_cnt[sg];
-            for (uint32_t i = tid; i < total; i += nt) {
-                uint32_t sg = 0, k = i;
-                while (k >= q_cnt[sg]) k -= q_cnt[sg++];
-                const uint32_t item = sg * wq_cap + k;
-                const uint32_t p8 = q_p8[item], p4 = q_p4[item], wsm = q_ws[item];
-                const uint32_t acc =
-                    settle_ties(p8, p4, q_blk[item], rep, (uint32_t)sweep, w3lo, a.seed_lo, a.seed_hi, t4, t8);
-                if (acc) {
-                    const uint32_t ws = wsm & 0x7FFFFFFFu, old = lds[ws];
-                    lds[ws] = old ^ acc;
-                    if (MEASURE && (wsm >> 31)) {
-                        e_acc += 8 * __builtin_popcount(acc & p8) + 4 * __builtin_popcount(acc & p4);
-                        m_acc += 2 * (2 * __builtin_popcount(old & acc) - __builtin_popcount(acc));
+                    const uint64_t m = __ballot(mw.pend != 0u);
+                    if (m) {
+                        const uint32_t cnt = (uint32_t)__popcll(m);
+                        if (qn + cnt > (uint32_t)kTieQueue) settle();
+                        if (mw.pend)
+                            tq[qn + wave_rank(m)] =
+                                make_uint4(ws | ((uint32_t)interior << 31), blk, mw.pend, mw.c8);
+                        qn += cnt;
                     }
                 }
+                y += Qm;
+                if (y >= a.Ly) y -= a.Ly;
             }
+            settle();
             if (MEASURE && c == 1) {
-                e_acc = wave_sum_i(e_acc);
-                m_acc = wave_sum_i(m_acc);
-                if ((tid & 63) == 0) {
-                    red[0][wave] = e_acc;
-                    red[1][wave] = m_acc;
+                n_acc = wave_sum_last(n_acc);
+                d_acc = wave_sum_last(d_acc);
+                if ((tid & 63) == 63) {
+                    red[0][wave] = n_acc;
+                    red[1][wave] = d_acc;
                 }
             }
             __syncthreads();
-            wq_n = 0;
         }
         if (MEASURE && tid == 0) {
-            long long te = 0, tm = 0;
+            long long n = 0, d = 0;
             for (int i = 0; i < nwaves; ++i) {
-                te += red[0][i];
-                tm += red[1][i];
+                n += red[0][i];
+                d += red[1][i];
             }
-            *em_slot(a.em.slots, s, l, nlat, blockIdx.x, ntile) = make_longlong2(te, tm);
+            // every bond once: 2 (anti-aligned) - 4 per odd site; M from both parities
+            const long long words = (long long)Hh * Wd;
+            *em_slot(a.em.slots, s, l, nlat, blockIdx.x, ntile) =
+                make_longlong2(2 * n - 128 * words, 64 * words - 2 * d);
         }
     }
 
@@ -327,18 +292,24 @@ bool tile2d_supported(const SweepCall &c, int layout)
 
 size_t tile2d_lds_bytes(int Lx, int H, int K) { return (size_t)(H + 4 * K) * 2 * (size_t)(Lx / 64) * 4; }
 
+// the band's words, then each wave's tie queue
+static size_t tile2d_dynamic_lds(int Lx, int H, int K, int threads)
+{
+    return ((tile2d_lds_bytes(Lx, H, K) + 15) & ~(size_t)15) + (K ? (size_t)(threads / 64) * kTieQueue * 16 : 0);
+}
+
 template <int K>
 static hipError_t launch_k(const Tile2DArgs &a, int count, int threads, hipStream_t s)
 {
     const int tiles = (a.Ly + a.H - 1) / a.H;
-    const size_t lds = tile2d_lds_bytes(a.Lx, a.H, K);
+    const size_t lds = tile2d_dynamic_lds(a.Lx, a.H, K, threads);
     dim3 grid((unsigned)tiles, (unsigned)count);
-    // allow the largest dynamic LDS a plan may ask for (64 KB) next to the
-    // static tie queue, once per device and kernel instance
+    // allow the largest dynamic LDS a plan may ask for (a band of 64 KB and
+    // sixteen queues of 1 KB), once per device and kernel instance
     static LdsLimit lim[2];
     const bool measure = a.em.slots != nullptr;
     const void *f = measure ? (const void *)k_tile2d<K, true> : (const void *)k_tile2d<K, false>;
-    const hipError_t e = lim[measure ? 1 : 0].ensure(f, 65536);
+    const hipError_t e = lim[measure ? 1 : 0].ensure(f, 65536 + 16 * kTieQueue * 16);
     if (e != hipSuccess) return e;
     if (measure) hipLaunchKernelGGL((k_tile2d<K, true>), grid, dim3(threads), lds, s, a);
     else hipLaunchKernelGGL((k_tile2d<K, false>), grid, dim3(threads), lds, s, a);
@@ -364,8 +335,8 @@ hipError_t launch_tile2d(const SweepCall &c, const void *src, int in_packed, voi
     a.per_lattice = c.per_lattice;
     for (int i = 0; i < kMaxTableLattices; ++i) {
         const SweepTables &t = (c.per_lattice && i < c.g.count) ? c.tabs[i] : c.tab;
-        a.t4[i] = t.met[1];
-        a.t8[i] = t.met[2];
+        a.t4[i] = metro_thr(t.met[1]);
+        a.t8[i] = metro_thr(t.met[2]);
     }
     a.em = em;
     if (k == 0) a.em.slots = nullptr;
