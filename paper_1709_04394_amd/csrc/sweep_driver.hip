@@ -43,8 +43,9 @@ size_t fused_workspace_bytes(const Geom &g, int layout)
     return 0;
 }
 
-// Default launch shape of the 2D kernel: enough bands to give every CU work,
-// sweeps per launch limited so the redone halo stays small.
+// Nominal launch shape of a geometry (mc_get_tile_plan's when none is set or
+// tuned): enough bands to give every CU work, sweeps per launch limited so the
+// redone halo stays small.  In 2D a call's launches use call_plan below.
 TilePlan default_tile_plan(const Geom &g)
 {
     TilePlan p;
@@ -107,6 +108,55 @@ static TilePlan plan_for(mc_ctx *ctx, const Geom &g)
     auto it = ctx->tile_plans.find(plan_key(g));
     if (it != ctx->tile_plans.end()) return it->second;
     return default_tile_plan(g);
+}
+
+// Launch shape of a call of n sweeps on 2D lattices without a set or tuned
+// plan: the one with the smallest modelled time.  A launch of K sweeps on bands
+// of H rows costs 6 us (the gap to the next launch, load and store) and per
+// half-sweep 1 us (one word's latency, ties, barrier) plus 0.087 us of VALU
+// issue for every 64 words of the fullest CU, which has ceil(bands / 256) bands
+// of H + 2K - 1 rows on average with the redone halo.  Measured (and modelled),
+// us per sweep of long calls: 4096^2 x 3, H = 16, K = 2 15.5 (15.5), the nominal
+// 48, 2 (258 bands, so two on one CU) 25.3 (23), the chosen 49, 4 14.0 (13.9);
+// 8192^2, 32, 4 17.5 (17.0); 2048^2, 8, 6 4.7 (4.7); 1024^2, 4, 8 3.6 (3.6), the
+// nominal 4, 1 6.4 (8.1).
+static TilePlan call_plan(mc_ctx *ctx, const Geom &g, int n)
+{
+    if (g.dims == 3 || ctx->tile_plans.count(plan_key(g))) return plan_for(ctx, g);
+    constexpr int kCUs = 256;
+    const int Wd = g.Lx / 64;
+    TilePlan p = default_tile_plan(g);
+    double best = 1e300;
+    auto consider = [&](int H) {
+        H = std::min(std::max(H, 4), std::max(g.Ly, 4));
+        const int64_t bands = (int64_t)((g.Ly + H - 1) / H) * g.count, per_cu = (bands + kCUs - 1) / kCUs;
+        for (int K = 1; K <= 8; ++K) {
+            if (tile2d_lds_bytes(g.Lx, std::min(H, g.Ly), K) > 65536) break;
+            const int launches = n == 1 ? 1 : std::max(2, (n + K - 1) / K);
+            const double Ke = (double)n / launches;  // sweeps of the average launch
+            const double words = 2.0 * Ke * (H + 2.0 * Ke - 1.0) * Wd / 64.0;
+            const double t = launches * (6.0 + 2.0 * Ke + 0.087 * words * (double)per_cu);
+            if (t < best * 0.999) {
+                TilePlan q;
+                q.H = H;
+                q.K = K;
+                // one thread per word of a half-sweep, up to 16 waves on a CU
+                const int tasks = (H + 2 * K) * Wd;
+                q.threads = std::min(per_cu > 1 ? 512 : 1024, std::max(64, (tasks + 63) / 64 * 64));
+                while (Wd > q.threads && Wd % q.threads) q.threads += 64;
+                if (!plan_ok(g, q)) continue;
+                best = t;
+                p = q;
+            }
+        }
+    };
+    // band heights that fill the CUs m times over with nothing left over
+    for (int m = 1; m <= 4; ++m) {
+        const int64_t per = (int64_t)m * kCUs / g.count;
+        if (per > 0) consider((int)((g.Ly + per - 1) / per));
+    }
+    for (int H : {8, 16, 32, 64}) consider(H);
+    return p;
 }
 
 // Split n >= 1 sweeps into launches of at most K sweeps, sizes as equal as
@@ -220,7 +270,7 @@ int run_sweeps_betas(mc_ctx *ctx, const SweepCall &c, int8_t *spins, uint64_t sw
 {
     const int p = betas_path(ctx, c, ws != nullptr, ws_bytes);
     if (p == MC_PATH_FUSED_2D || p == MC_PATH_FUSED_3D)
-        return run_fused(ctx, c, plan_for(ctx, c.g), spins, (char *)ws, sweep0, nsweeps, EM, em_stride, s);
+        return run_fused(ctx, c, call_plan(ctx, c.g, nsweeps), spins, (char *)ws, sweep0, nsweeps, EM, em_stride, s);
     for (int l = 0; l < c.g.count; ++l) {
         const int rc = run_sweeps(ctx, single_lattice(c, l), MC_INT8, spins + (int64_t)l * c.g.N, sweep0, nsweeps,
                                   EM ? EM + 2 * l : nullptr, em_stride, nullptr, 0, s);
@@ -240,7 +290,7 @@ int run_sweeps(mc_ctx *ctx, const SweepCall &c, int layout, void *spins, uint64_
     switch (path) {
     case MC_PATH_FUSED_2D:
     case MC_PATH_FUSED_3D:
-        return run_fused(ctx, c, plan_for(ctx, c.g), (int8_t *)spins, (char *)ws, sweep0, nsweeps, EM, em_stride, s);
+        return run_fused(ctx, c, call_plan(ctx, c.g, nsweeps), (int8_t *)spins, (char *)ws, sweep0, nsweeps, EM, em_stride, s);
     case MC_PATH_SMALL_BITS:
         return device_check(ctx, launch_small_bits(c, (int8_t *)spins, sweep0, nsweeps, EM, em_stride, s),
                             "mc_sweep small bit-packed lattice launch");
