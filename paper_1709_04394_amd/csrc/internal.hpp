@@ -159,7 +159,6 @@ int pa_group_for(const mc_ctx *ctx, int L);
 
 // double-checkerboard multi-hit sweeps (k_dcb.hip): one launch updates every
 // tile of one coarse colour of the packed lattices in place
-size_t dcb_lds_bytes(int T);
 // part: this sweep's (E, M) slots [count][(L/T)^2][2], or nullptr; prev: the
 // previous sweep's slots, added up by the first workgroup of each lattice
 hipError_t launch_dcb_phase(uint32_t *packed, int L, int T, int count, int coarse, int hits, uint32_t replica0,

@@ -13,7 +13,13 @@
 // A sweep is two launches (coarse colour 0, then 1).  The per-word update
 // (four neighbour words, Metropolis classes from 3-input bit operations, the
 // random top bytes as eight bit-planes from two Philox blocks, a bit-serial
-// compare, ties settled after the half-step) follows the 2D band kernel.
+// compare, ties settled from a queue of the wave) is the 2D band kernel's
+// (metro2d.hpp).
+//
+// What bounds it: VALU issue from ten hits on (4096^2 x 3, tiles of 128: 3780
+// attempted updates per ns at ten hits, 4650 at a hundred; 3050 and 3700 with a
+// comparison per class and two barriers per half-step), with one hit the
+// launch, the tile's load and the sums (1360 against 1180).
 //
 // Energy and magnetisation of a sweep: every bond lies inside one tile or
 // joins a tile of colour 0 to one of colour 1.  Colour-0 tiles are final
@@ -26,11 +32,11 @@
 #include <algorithm>
 
 #include "internal.hpp"
+#include "metro2d.hpp"
 
 namespace mcs {
 
-constexpr int kDcbTieQueue = 512;
-constexpr int kDcbMaxWaves = 4;  // at most 256 threads per workgroup
+constexpr int kDcbMaxWaves = 16;
 
 struct DcbArgs {
     uint32_t *lat;              // packed lattices, rows of 2 L/64 words (even-x array first)
@@ -54,11 +60,9 @@ __device__ __forceinline__ void dcb_tile(const DcbArgs &a, int b, int &tx, int &
     tx = 2 * (b - ty * half) + ((ty + a.coarse) & 1);
 }
 
-__global__ __launch_bounds__(256) void k_dcb(DcbArgs a)
+__global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
 {
     extern __shared__ uint32_t lds[];
-    __shared__ uint32_t q_ws[kDcbTieQueue], q_blk[kDcbTieQueue], q_p8[kDcbTieQueue], q_p4[kDcbTieQueue];
-    __shared__ uint32_t q_cnt[kDcbMaxWaves];
     __shared__ long long red[2][kDcbMaxWaves];
     __shared__ long long red_prev[2][16];
     const int l = blockIdx.y;
@@ -71,7 +75,7 @@ __global__ __launch_bounds__(256) void k_dcb(DcbArgs a)
     const int tid = threadIdx.x, nt = blockDim.x;
     const int wave = tid >> 6, nwaves = nt >> 6;
     const uint32_t rep = a.replica0 + (uint32_t)l;
-    const int y0 = ty * a.T, wc0 = tx * Wt;
+    const int y0 = ty * a.T, wc0 = tx * Wt, tsh = 31 - __builtin_clz(a.T), wsh = tsh - 6;
     uint32_t *lat = a.lat + (size_t)l * a.L * 2 * Wl;
     // LDS word (r, par, c): tile row r - 1 (r = 0 and T + 1 are halo rows),
     // word column c - 1 of the tile (c = 0 and Wt + 1 are halo columns)
@@ -88,8 +92,8 @@ __global__ __launch_bounds__(256) void k_dcb(DcbArgs a)
         if (w >= Wl) w -= Wl;
         return w;
     };
-    const TopMask m4 = top_mask(a.t4.top), m8 = top_mask(a.t8.top);
-    const uint32_t wq_cap = (uint32_t)(kDcbTieQueue / nwaves), wq_base = (uint32_t)wave * wq_cap;
+    const MetroMasks mm = metro_masks(a.t4.top, a.t8.top, true);
+    uint4 *const tq = (uint4 *)(lds + ((rows * 2 * Ww + 3) & ~3)) + wave * kTieQueue;  // behind the tile
     const int slots_per_lattice = (a.L / a.T) * (a.L / a.T);
     long long pre_e, pre_m;
     em_prefetch(a.prev, blockIdx.x, slots_per_lattice, l, gridDim.y, tid, pre_e, pre_m);
@@ -97,6 +101,7 @@ __global__ __launch_bounds__(256) void k_dcb(DcbArgs a)
     // ---- load the tile and its halo (corner words are not needed), a batch
     // of words per thread in flight at once
     const int ld = rows * 2 * Ww;
+    const uint32_t inv_ww = 0xFFFFFFFFu / (uint32_t)Ww + 1u;  // i / Ww as a high word, exact for i < 2^16
     constexpr int kLoadBatch = 8;
     for (int i0 = tid; i0 < ld; i0 += kLoadBatch * nt) {
         uint32_t v[kLoadBatch];
@@ -105,7 +110,7 @@ __global__ __launch_bounds__(256) void k_dcb(DcbArgs a)
             const int i = i0 + j * nt;
             v[j] = 0u;
             if (i < ld) {
-                const int r = i / (2 * Ww), rem = i - r * 2 * Ww, par = rem / Ww, c = rem - par * Ww;
+                const int rp = (int)__umulhi((uint32_t)i, inv_ww), c = i - rp * Ww, r = rp >> 1, par = rp & 1;
                 const bool corner = (r == 0 || r == rows - 1) && (c == 0 || c == Ww - 1);
                 if (!corner) v[j] = lat[((size_t)gy(r) * 2 + par) * Wl + gw(c)];
             }
@@ -117,99 +122,57 @@ __global__ __launch_bounds__(256) void k_dcb(DcbArgs a)
     __syncthreads();
     em_reduce(a.prev, blockIdx.x, slots_per_lattice, l, gridDim.y, tid, nt, pre_e, pre_m, red_prev);
 
-    const int tasks = a.T * Wt;  // words of one colour: one per (row, column)
-    uint32_t wq_n = 0;
+    const int tasks = a.T * Wt;  // words of one colour: one per (row, column), a multiple of the threads
     for (int h = 0; h < a.hits; ++h) {
         const uint64_t dsweep = a.sweep * (uint64_t)a.hits + (uint64_t)h;
         for (int col = 0; col < 2; ++col) {
             const uint32_t w3 = ctr_w3(kTagSweep, (uint32_t)col, dsweep);
             const uint32_t w3lo = ctr_w3(kTagSweepLo, (uint32_t)col, dsweep);
+            uint32_t qn = 0;
+            auto settle = [&]() {
+                const uint32_t i = tid & 63;
+                if (i < qn) {
+                    const uint4 it = tq[i];
+                    const uint32_t f = metro_settle(it.z, it.w, it.y, rep, (uint32_t)dsweep, w3lo, a.seed_lo, a.seed_hi,
+                                                    a.t4.low, a.t8.low);
+                    if (f) lds[it.x] ^= f;
+                }
+                qn = 0;
+            };
             for (int t = tid; t < tasks; t += nt) {
-                const int r = 1 + t / Wt, c = 1 + (t - (r - 1) * Wt);
+                // words column by column: T is a power of two
+                const int c = 1 + (t >> tsh), r = 1 + (t & (a.T - 1));
                 const int y = y0 + r - 1;
                 const int q = (col + y) & 1;
-                const int ws = widx(r, q, c);
-                const uint32_t S = lds[ws];
-                const uint32_t U = lds[widx(r - 1, q, c)], D = lds[widx(r + 1, q, c)];
-                const uint32_t O = lds[widx(r, 1 - q, c)];
+                const int e = r * 2 * Ww + c, o = e + Ww;  // even- and odd-x words
+                const int is = q ? o : e, io = q ? e : o;
                 // even-x sites: left neighbours are the odd sites one to the
                 // left; odd-x sites: right neighbours are the even sites one
                 // to the right (halo columns at the tile's edges)
-                const uint32_t Sh = q == 0 ? __builtin_amdgcn_alignbit(O, lds[widx(r, 1, c - 1)], 31)
-                                           : __builtin_amdgcn_alignbit(lds[widx(r, 0, c + 1)], O, 1);
-                const uint32_t u1 = S ^ U, u2 = S ^ D, u3 = S ^ O, u4 = S ^ Sh;
-                const uint32_t t1 = u1 | u2, t2 = u3 | u4;
-                const uint32_t ge2 = MCS_BOP3(u1, u2, MCS_BOP3(u3, u4, t1 & t2, (MCS_A & MCS_B) | MCS_C),
-                                              (MCS_A & MCS_B) | MCS_C);
-                const uint32_t c8 = ~(t1 | t2);
-                const uint32_t c4 = MCS_BOP3(t1, t2, ge2, (MCS_A | MCS_B) & ~MCS_C);
+                const uint32_t S = lds[is], U = lds[is - 2 * Ww], D = lds[is + 2 * Ww], O = lds[io];
+                const uint32_t Nb = lds[io + (q ? 1 : -1)];
+                const uint32_t Sh = __builtin_amdgcn_alignbit(q ? Nb : O, q ? O : Nb, q ? 1u : 31u);
                 // random planes of the 32 same-colour sites j0 .. j0+31,
                 // j0 = 32 w + (L/2) y, w the lattice word column
                 const uint32_t blk = 2u * (uint32_t)(wc0 + c - 1) + (uint32_t)(a.L >> 5) * (uint32_t)y;
                 const uint4 A = philox(make_uint4(blk, rep, (uint32_t)dsweep, w3), a.seed_lo, a.seed_hi);
                 const uint4 B = philox(make_uint4(blk + 1u, rep, (uint32_t)dsweep, w3), a.seed_lo, a.seed_hi);
-                uint32_t X[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) X[k] = plane_pair(A, B, k);
-                uint32_t lt8, eq8, lt4, eq4;
-                compare_planes(X, m8, lt8, eq8);
-                compare_planes(X, m4, lt4, eq4);
-                uint32_t acc = MCS_BOP3(ge2, c8, lt8, MCS_A | (MCS_B & MCS_C)) | (c4 & lt4);
-                const uint32_t p8 = c8 & eq8, p4 = c4 & eq4;
-                const uint64_t m = __ballot((p8 | p4) != 0u);
-                if (m) {
-                    if (p8 | p4) {
-                        const uint32_t pos =
-                            wq_n + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                        if (pos < wq_cap) {
-                            q_ws[wq_base + pos] = (uint32_t)ws;
-                            q_blk[wq_base + pos] = blk;
-                            q_p8[wq_base + pos] = p8;
-                            q_p4[wq_base + pos] = p4;
-                        } else {
-                            uint32_t pend = p8 | p4;
-                            while (pend) {
-                                const int b = __builtin_ctz(pend);
-                                pend &= pend - 1u;
-                                const uint4 lo = philox(make_uint4(16u * blk + (uint32_t)b, rep, (uint32_t)dsweep, w3lo),
-                                                        a.seed_lo, a.seed_hi);
-                                if ((lo.x & 0xFFFFFFu) < (((p8 >> b) & 1u) ? a.t8.low : a.t4.low)) acc |= 1u << b;
-                            }
-                        }
-                    }
-                    wq_n = min(wq_cap, wq_n + (uint32_t)__popcll(m));
-                }
-                lds[ws] = S ^ acc;
+                const MetroWord mw = metro_update(S, U, D, O, Sh, A, B, mm);
+                lds[is] = mw.S;
+                const uint64_t m = __ballot(mw.pend != 0u);
+                const uint32_t cnt = (uint32_t)__popcll(m);
+                if (qn + cnt > (uint32_t)kTieQueue) settle();
+                if (mw.pend) tq[qn + wave_rank(m)] = make_uint4((uint32_t)is, blk, mw.pend, mw.c8);
+                qn += cnt;
             }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) wq_n = max(wq_n, (uint32_t)__shfl_xor((int)wq_n, off, 64));
-            if ((tid & 63) == 0) q_cnt[wave] = wq_n;
+            settle();
             __syncthreads();
-            uint32_t total = 0;
-            for (int sg = 0; sg < nwaves; ++sg) total += q_cnt[sg];
-            for (uint32_t i = tid; i < total; i += nt) {
-                uint32_t sg = 0, k = i;
-                while (k >= q_cnt[sg]) k -= q_cnt[sg++];
-                const uint32_t item = sg * wq_cap + k;
-                const uint32_t p8 = q_p8[item], p4 = q_p4[item], blk = q_blk[item];
-                uint32_t pend = p8 | p4, acc = 0u;
-                while (pend) {
-                    const int b = __builtin_ctz(pend);
-                    pend &= pend - 1u;
-                    const uint4 lo = philox(make_uint4(16u * blk + (uint32_t)b, rep, (uint32_t)dsweep, w3lo),
-                                            a.seed_lo, a.seed_hi);
-                    if ((lo.x & 0xFFFFFFu) < (((p8 >> b) & 1u) ? a.t8.low : a.t4.low)) acc |= 1u << b;
-                }
-                if (acc) lds[q_ws[item]] ^= acc;
-            }
-            __syncthreads();
-            wq_n = 0;
         }
     }
 
     // ---- store the tile in place
     for (int i = tid; i < a.T * 2 * Wt; i += nt) {
-        const int r = 1 + i / (2 * Wt), rem = i - (r - 1) * 2 * Wt, par = rem / Wt, c = 1 + rem - par * Wt;
+        const int rp = i >> wsh, c = 1 + (i & (Wt - 1)), r = 1 + (rp >> 1), par = rp & 1;
         lat[((size_t)(y0 + r - 1) * 2 + par) * Wl + wc0 + c - 1] = lds[widx(r, par, c)];
     }
 
@@ -218,7 +181,7 @@ __global__ __launch_bounds__(256) void k_dcb(DcbArgs a)
     long long e_acc = 0, m_acc = 0;
     const bool edges = a.coarse == 1;
     for (int t = tid; t < tasks; t += nt) {
-        const int r = 1 + t / Wt, c = 1 + (t - (r - 1) * Wt);
+        const int c = 1 + (t >> tsh), r = 1 + (t & (a.T - 1));
         const int y = y0 + r - 1;
         // the odd-colour word of row r (x parity q) and its four neighbours
         const int q = (1 + y) & 1;
@@ -277,7 +240,11 @@ __global__ __launch_bounds__(256) void k_dcb(DcbArgs a)
     }
 }
 
-size_t dcb_lds_bytes(int T) { return (size_t)(T + 2) * 2 * (size_t)(T / 64 + 2) * 4; }
+// The tile with its halo, then each wave's tie queue.
+static size_t dcb_lds_bytes(int T, int threads)
+{
+    return (((size_t)(T + 2) * 2 * (size_t)(T / 64 + 2) * 4 + 15) & ~(size_t)15) + (size_t)(threads / 64) * kTieQueue * 16;
+}
 
 hipError_t launch_dcb_phase(uint32_t *packed, int L, int T, int count, int coarse, int hits, uint32_t replica0,
                             uint64_t sweep, uint32_t seed_lo, uint32_t seed_hi, const SweepTables &tab, int64_t *part,
@@ -293,15 +260,20 @@ hipError_t launch_dcb_phase(uint32_t *packed, int L, int T, int count, int coars
     a.sweep = sweep;
     a.seed_lo = seed_lo;
     a.seed_hi = seed_hi;
-    a.t4 = tab.met[1];
-    a.t8 = tab.met[2];
+    a.t4 = metro_thr(tab.met[1]);
+    a.t8 = metro_thr(tab.met[2]);
     a.part = part;
     a.prev = prev;
     if (!prev.red_in) a.prev.red_K = 0;
     const int tiles = (L / T) * (L / T) / 2;
-    // one thread per word of a colour (T^2 / 64 of them), at most 256
-    const int threads = std::min(256, T * T / 64);
-    hipLaunchKernelGGL(k_dcb, dim3((unsigned)tiles, (unsigned)count), dim3(threads), dcb_lds_bytes(T), s, a);
+    // one thread per word of a colour (T^2 / 64 of them), at most 256 while that
+    // gives three waves per SIMD, up to 1024 with fewer tiles.  4096^2 x 3, ten
+    // hits, attempted updates per ns at 256, 512 and 1024 threads: tile 256 3160,
+    // 3250 and 2690; tile 512 1500, 1930 and 2030
+    int threads = std::min(256, T * T / 64);
+    while (threads < std::min(64 * kDcbMaxWaves, T * T / 64) && (int64_t)tiles * count * (threads / 64) < 3072)
+        threads *= 2;
+    hipLaunchKernelGGL(k_dcb, dim3((unsigned)tiles, (unsigned)count), dim3(threads), dcb_lds_bytes(T, threads), s, a);
     return hipGetLastError();
 }
 
