@@ -16,18 +16,25 @@
 //    the six bond words): Metropolis counts unsatisfied bonds a (dE = 12 - 4a,
 //    a >= 3 always accepts); heat-bath counts neighbours with J s_j = -1, d
 //    (h = 6 - 2d).  Each class has its own threshold; per random bit-plane the
-//    threshold bit of every site comes from a multiplexer over the class bits,
-//    and r32 < T is one bit-serial comparison.  Ties (top byte equal) are
-//    queued per word and settled after the half-sweep.
+//    threshold bit of every site comes from a multiplexer over the class bits
+//    (its inputs alternate between scalar and vector registers), and r32 < T is
+//    one bit-serial comparison.  Ties (top byte equal) wait in a queue of their
+//    wave (metro2d.hpp).
 //  * Per-sweep E and M are summed from the odd half-sweep, as in 2D, and
 //    stored per tile in slots that the next launch adds up (em_slots.hpp).
 //  * Between the launches of one call the lattice stays packed in global
 //    scratch.
+//
+// What bounds it: VALU issue (heat-bath about 230 instructions of a wave per 64
+// words of 32 sites, Metropolis 190) with the redone halo (1.4 times at H = 16,
+// K = 2), then the half-sweeps' latency where a CU has one tile.  256^3 x 4
+// heat-bath, 16, 2, 256 threads: 30.0 us per sweep against 38.8 with the
+// thresholds read from LDS for every plane, rows found by division and wrapped
+// in loops, and ties settled between two barriers; 256^3 13.3 against 17.2.
 #include "internal.hpp"
+#include "metro2d.hpp"
 
 namespace mcs {
-
-constexpr int kTieQ3 = 256;  // queued words per workgroup (split over its waves)
 
 struct Tile3DArgs {
     const void *src;
@@ -62,19 +69,25 @@ __device__ __forceinline__ void divmod_small(int t, int n, float inv, int &q, in
     }
 }
 
+// First row of tile t of n over L rows: floor(t L / n) (a 64-bit division is a
+// hundred scalar instructions, four of them a tile's work of a few words).
+__device__ __forceinline__ int tile_cut(int t, int n, int L)
+{
+    if (L < 65536) return (int)((uint32_t)t * (uint32_t)L / (uint32_t)n);
+    return (int)((int64_t)t * L / n);
+}
+
 template <int K, bool MEASURE, bool HB, bool HASJ>
 __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
 {
     extern __shared__ uint32_t lds[];
     __shared__ int red[2][16];
     __shared__ long long red64[2][16];
-    __shared__ uint32_t q_ws[kTieQ3], q_blk[kTieQ3], q_p[kTieQ3], q_c0[kTieQ3], q_c1[kTieQ3], q_c2[kTieQ3];
-    __shared__ uint32_t q_cnt[16];
     __shared__ uint32_t tlow[8];
     const int l = blockIdx.y;
-    const int ty = blockIdx.x % a.nty, tz = blockIdx.x / a.nty;
-    const int y0 = (int)((int64_t)ty * a.Ly / a.nty), y1 = (int)((int64_t)(ty + 1) * a.Ly / a.nty);
-    const int z0 = (int)((int64_t)tz * a.Lz / a.ntz), z1 = (int)((int64_t)(tz + 1) * a.Lz / a.ntz);
+    const int tz = blockIdx.x / a.nty, ty = blockIdx.x - tz * a.nty;
+    const int y0 = tile_cut(ty, a.nty, a.Ly), y1 = tile_cut(ty + 1, a.nty, a.Ly);
+    const int z0 = tile_cut(tz, a.ntz, a.Lz), z1 = tile_cut(tz + 1, a.ntz, a.Lz);
     const int hy = y1 - y0, hz = z1 - z0;
     constexpr int R = 2 * K;
     const int Ry = hy + 2 * R, Rz = hz + 2 * R, rows = Ry * Rz;
@@ -84,11 +97,24 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
     const int li = a.per_lattice ? l : 0;
     if (tid < 8) tlow[tid] = a.low[li][tid];
     uint32_t *Jl = lds + (size_t)rows * 2 * Wd;  // 3 coupling planes of rows
-    // per random plane k and class c the threshold bit as a full mask, kept
-    // in the dynamic LDS array the sweep also writes, so the per-plane reads
-    // stay in the loop (broadcast ds_read_b128) instead of occupying registers
-    uint32_t *tm = lds + (((size_t)rows * 2 * Wd * (HASJ ? 4 : 1) + 3) & ~(size_t)3);
-    if (tid < 64) tm[tid] = ((a.top[li][tid & 7] >> (tid >> 3)) & 1u) ? ~0u : 0u;
+    // behind them: per LDS row its first random block (even), bit 0 the parity
+    // of y + z; then each wave's tie queue
+    uint32_t *rinfo = lds + (size_t)rows * 2 * Wd * (HASJ ? 4 : 1);
+    // per random plane and class the threshold bit as a full mask, those of
+    // classes 0, 2, 4 in vector registers (an instruction reads one scalar)
+    uint32_t tv[8][3], ts[8][4];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+#pragma unroll
+        for (int i = 0; i < (HB ? 3 : 1); ++i) {
+            tv[k][i] = ((a.top[li][2 * i] >> k) & 1u) ? ~0u : 0u;
+            asm volatile("" : "+v"(tv[k][i]));
+        }
+        ts[k][0] = ((a.top[li][1] >> k) & 1u) ? ~0u : 0u;
+        ts[k][1] = ((a.top[li][HB ? 3 : 2] >> k) & 1u) ? ~0u : 0u;
+        ts[k][2] = ((a.top[li][5] >> k) & 1u) ? ~0u : 0u;
+        ts[k][3] = ((a.top[li][6] >> k) & 1u) ? ~0u : 0u;
+    }
     // thread -> (word column, first row, row stride)
     int P, Q, w0, r0;
     if (Wd <= nt) {
@@ -110,8 +136,9 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
         return v;
     };
     const int wave = tid >> 6, nwaves = nt >> 6;
-    const uint32_t wq_cap = (uint32_t)(kTieQ3 / nwaves), wq_base = (uint32_t)wave * wq_cap;
-    uint32_t wq_n = 0;
+    uint4 *const tq = (uint4 *)(lds + (((size_t)rows * (2 * Wd * (HASJ ? 4 : 1) + 1) + 3) & ~(size_t)3)) +
+                      wave * (kTieQueue * 3 / 2);
+    uint2 *const tq2 = (uint2 *)(tq + kTieQueue);
     const int64_t plane_rows = (int64_t)a.Ly * a.Lz;
     const int ntile = gridDim.x, nlat = gridDim.y;
     long long pre_e, pre_m;
@@ -157,12 +184,19 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
             }
         }
     }
+    for (int rr = tid; rr < rows; rr += nt) {
+        int rz, ry;
+        divmod_small(rr, Ry, invRy, rz, ry);
+        const int y = wrap(y0 - R + ry, a.Ly), z = wrap(z0 - R + rz, a.Lz);
+        rinfo[rr] = (uint32_t)(a.Lx >> 5) * (uint32_t)((int64_t)z * a.Ly + y) | ((uint32_t)(y + z) & 1u);
+    }
     __syncthreads();
     em_reduce(a.em, blockIdx.x, ntile, l, nlat, tid, nt, pre_e, pre_m, red64);
 
+    const bool own = r0 < (1 << 28);
     for (int s = 0; s < K; ++s) {
         const uint64_t sweep = a.sweep0 + (uint64_t)s;
-        int e_acc = 0, m_acc = 0;
+        int n_acc = 0, d_acc = 0;  // anti-aligned bonds and down spins of this thread's own words
         for (int c = 0; c < 2; ++c) {
             const int p = 2 * s + c;
             const int ny = Ry - 2 * p - 2, nz = Rz - 2 * p - 2;
@@ -170,40 +204,80 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
             const float invny = 1.0f / (float)ny;
             const uint32_t w3 = ctr_w3(kTagSweep, (uint32_t)c, sweep);
             const uint32_t w3lo = ctr_w3(kTagSweepLo, (uint32_t)c, sweep);
-            for (int rr = r0; rr < nrow; rr += Q) {
-                int iz, iy;
-                divmod_small(rr, ny, invny, iz, iy);
-                const int ry = p + 1 + iy, rz = p + 1 + iz;
-                const int row = rz * Ry + ry;
-                const int y = wrap(y0 - R + ry, a.Ly), z = wrap(z0 - R + rz, a.Lz);
-                const int q = (c + y + z) & 1;
-                const bool interior = MEASURE && c == 1 && ry >= R && ry < R + hy && rz >= R && rz < R + hz;
-                const uint32_t rowblk = (uint32_t)(a.Lx >> 5) * (uint32_t)((int64_t)z * a.Ly + y);
-                for (int w = w0; w < Wd; w += P) {
-                    const int ws = widx(row, q, w);
-                    const uint32_t S = lds[ws];
-                    const uint32_t O = lds[widx(row, 1 - q, w)];
-                    const int wl = w == 0 ? Wd - 1 : w - 1, wr = w + 1 == Wd ? 0 : w + 1;
+            uint32_t qn = 0;
+            auto draw = [&](uint32_t pend, uint32_t blk, uint32_t c0, uint32_t c1, uint32_t c2, int &dn) {
+                uint32_t f = 0u;
+                while (pend) {
+                    const int b = __builtin_ctz(pend);
+                    pend &= pend - 1u;
+                    const uint32_t cls = ((c0 >> b) & 1u) | (((c1 >> b) & 1u) << 1) | (((c2 >> b) & 1u) << 2);
+                    const uint4 lo = philox(make_uint4(16u * blk + (uint32_t)b, rep, (uint32_t)sweep, w3lo), a.seed_lo,
+                                            a.seed_hi);
+                    if ((lo.x & 0xFFFFFFu) < tlow[cls]) {
+                        f |= 1u << b;
+                        // anti-aligned bonds gained: Metropolis 6 - 2a, heat-bath
+                        // (-1 -> +1) 2d - 6
+                        dn += HB ? 2 * (int)cls - 6 : 6 - 2 * (int)cls;
+                    }
+                }
+                return f;
+            };
+            // a queued word: {LDS word | own-row flag, first block, tied sites, and
+            // their class bits}
+            auto settle = [&]() {
+                const uint32_t i = tid & 63;
+                if (i < qn) {
+                    const uint4 it = tq[i];
+                    const uint2 cb = tq2[i];
+                    int dn = 0;
+                    const uint32_t f = draw(it.z, it.y, it.w, cb.x, cb.y, dn);
+                    if (f) {
+                        const uint32_t ws = it.x & 0x7FFFFFFFu, old = lds[ws];
+                        lds[ws] = old ^ f;
+                        if (MEASURE && (it.x >> 31)) {
+                            n_acc += dn;
+                            d_acc += (int)__builtin_popcount(f) - 2 * (int)__builtin_popcount(old & f);
+                        }
+                    }
+                }
+                qn = 0;
+            };
+            // row r0 of the half-sweep's rectangle, advanced by Q rows a step
+            const int Qz = Q / ny, Qy = Q - Qz * ny;
+            int iz = 0, iy = 0;
+            if (own) divmod_small(r0, ny, invny, iz, iy);
+            int row = (p + 1 + iz) * Ry + p + 1 + iy;
+            for (int rr = 0; rr < nrow; rr += Q) {
+                uint32_t pend = 0u, ws = 0u, blk = 0u, c0 = 0u, c1 = 0u, c2 = 0u;
+                const bool interior = MEASURE && c == 1 && (uint32_t)(p + 1 + iy - R) < (uint32_t)hy &&
+                                      (uint32_t)(p + 1 + iz - R) < (uint32_t)hz;
+                if (own && rr + r0 < nrow) {
+                    const uint32_t info = rinfo[row];
+                    const bool q = (c ^ (int)info) & 1;
+                    const int ev = row * 2 * Wd + w0, od = ev + Wd;  // even- and odd-x words
+                    const int is = q ? od : ev, io = q ? ev : od;
+                    const uint32_t S = lds[is], O = lds[io];
                     // x neighbours: even sites (q = 0) have +x in O, -x one odd
                     // site to the left; odd sites the mirror image
-                    const uint32_t Ol = lds[widx(row, 1, wl)], Er = lds[widx(row, 0, wr)];
-                    const uint32_t nxp = q == 0 ? O : __builtin_amdgcn_alignbit(Er, O, 1);
-                    const uint32_t nxm = q == 0 ? __builtin_amdgcn_alignbit(O, Ol, 31) : O;
-                    uint32_t w1 = nxp, w2 = nxm;
-                    uint32_t w3b = lds[widx(row + 1, q, w)], w4 = lds[widx(row - 1, q, w)];
-                    uint32_t w5 = lds[widx(row + Ry, q, w)], w6 = lds[widx(row - Ry, q, w)];
+                    const int side = q ? (w0 + 1 == Wd ? 1 - Wd : 1) : (w0 == 0 ? Wd - 1 : -1);
+                    const uint32_t Nb = lds[io + side];
+                    const uint32_t Sh = __builtin_amdgcn_alignbit(q ? Nb : O, q ? O : Nb, q ? 1u : 31u);
+                    uint32_t w1 = O, w2 = Sh;  // the same place, the shifted one
+                    uint32_t w3b = lds[is + 2 * Wd], w4 = lds[is - 2 * Wd];
+                    uint32_t w5 = lds[is + 2 * Wd * Ry], w6 = lds[is - 2 * Wd * Ry];
                     if (HASJ) {
-                        auto jidx = [&](int d, int rw, int par, int ww) { return ((d * rows + rw) * 2 + par) * Wd + ww; };
-                        const uint32_t Jxp = Jl[jidx(0, row, q, w)];
-                        const uint32_t Jxm = q == 0 ? __builtin_amdgcn_alignbit(Jl[jidx(0, row, 1, w)],
-                                                                                  Jl[jidx(0, row, 1, wl)], 31)
-                                                    : Jl[jidx(0, row, 0, w)];
-                        w1 ^= Jxp;
-                        w2 ^= Jxm;
-                        w3b ^= Jl[jidx(1, row, q, w)];
-                        w4 ^= Jl[jidx(1, row - 1, q, w)];
-                        w5 ^= Jl[jidx(2, row, q, w)];
-                        w6 ^= Jl[jidx(2, row - Ry, q, w)];
+                        // coupling word of direction d at the place of LDS word i
+                        auto J = [&](int d, int i) { return Jl[d * rows * 2 * Wd + i]; };
+                        // bonds to + x belong to the left end: the even site's to
+                        // its own word, the odd site's (+x) to its own word too
+                        const uint32_t Js = J(0, is), Jo = J(0, io);
+                        const uint32_t Jl_ = q ? 0u : J(0, io + side);
+                        w1 ^= q ? Jo : Js;
+                        w2 ^= q ? Js : __builtin_amdgcn_alignbit(Jo, Jl_, 31);
+                        w3b ^= J(1, is);
+                        w4 ^= J(1, is - 2 * Wd);
+                        w5 ^= J(2, is);
+                        w6 ^= J(2, is - 2 * Wd * Ry);
                     }
                     // bit set in wk <=> J s_j = -1 for that bond; Metropolis
                     // counts unsatisfied bonds S ^ wk, heat-bath counts wk
@@ -220,13 +294,14 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
                     const uint32_t k1 = MCS_BOP3(x1, x2, x3, (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
                     const uint32_t s2 = MCS_BOP3(x4, x5, x6, MCS_A ^ MCS_B ^ MCS_C);
                     const uint32_t k2 = MCS_BOP3(x4, x5, x6, (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
-                    const uint32_t c0 = s1 ^ s2, kk = s1 & s2;
-                    const uint32_t c1 = MCS_BOP3(k1, k2, kk, MCS_A ^ MCS_B ^ MCS_C);
-                    const uint32_t c2 = MCS_BOP3(k1, k2, kk, (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
+                    const uint32_t kk = s1 & s2;
+                    c0 = s1 ^ s2;
+                    c1 = MCS_BOP3(k1, k2, kk, MCS_A ^ MCS_B ^ MCS_C);
+                    c2 = MCS_BOP3(k1, k2, kk, (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
                     // Metropolis: a >= 3 accepts without a random number
-                    const uint32_t ge3 = HB ? 0u : (c2 | (c1 & c0));
+                    const uint32_t ge3 = HB ? 0u : MCS_BOP3(c2, c1, c0, MCS_A | (MCS_B & MCS_C));
                     // random planes of the 32 sites
-                    const uint32_t blk = 2u * (uint32_t)w + rowblk;
+                    blk = 2u * (uint32_t)w0 + (info & ~1u);
                     const uint4 A = philox(make_uint4(blk, rep, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
                     const uint4 B = philox(make_uint4(blk + 1u, rep, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
                     // bit-serial r < T(class) from the least significant plane;
@@ -235,130 +310,84 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
                         const uint32_t X = plane_pair(A, B, k);
-                        const uint4 ml = *(const uint4 *)&tm[8 * k];
+                        // mux(s, hi, lo): hi where s is set
+                        auto mux = [](uint32_t sel, uint32_t hi, uint32_t lo) {
+                            return MCS_BOP3(sel, hi, lo, (MCS_A & MCS_B) | (~MCS_A & MCS_C));
+                        };
+                        const uint32_t m01 = mux(c0, ts[k][0], tv[k][0]);
                         uint32_t T;
                         if (HB) {
-                            const uint4 mh = *(const uint4 *)&tm[8 * k + 4];
-                            const uint32_t m01 = (c0 & ml.y) | (~c0 & ml.x);
-                            const uint32_t m23 = (c0 & ml.w) | (~c0 & ml.z);
-                            const uint32_t m45 = (c0 & mh.y) | (~c0 & mh.x);
-                            const uint32_t lo4 = (c1 & m23) | (~c1 & m01);
-                            const uint32_t hi4 = (c1 & mh.z) | (~c1 & m45);
-                            T = (c2 & hi4) | (~c2 & lo4);
+                            const uint32_t lo4 = mux(c1, mux(c0, ts[k][1], tv[k][1]), m01);
+                            const uint32_t hi4 = mux(c1, ts[k][3], mux(c0, ts[k][2], tv[k][2]));
+                            T = mux(c2, hi4, lo4);
                         } else {
-                            const uint32_t m01 = (c0 & ml.y) | (~c0 & ml.x);
-                            T = (c1 & ml.z) | (~c1 & m01);
+                            T = mux(c1, ts[k][1], m01);
                         }
                         lt = MCS_BOP3(X, T, lt, (~MCS_A & MCS_B) | (~MCS_A & MCS_C) | (MCS_B & MCS_C));
                         eq = MCS_BOP3(eq, X, T, MCS_A & ~(MCS_B ^ MCS_C));
                     }
-                    // Metropolis: accept mask (flip); heat-bath: new spin
+                    // Metropolis: flip where accepted; heat-bath: new spin
                     // word, +1 (bit 0) where r < T; ties provisionally -1
-                    uint32_t acc = HB ? ~lt : (ge3 | lt);
-                    const uint32_t pend = HB ? eq : (eq & ~ge3);
-                    const uint64_t m = __ballot(pend != 0u);
-                    if (m) {
-                        if (pend) {
-                            const uint32_t pos = wq_n + __builtin_amdgcn_mbcnt_hi(
-                                                            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                            if (pos < wq_cap) {
-                                const uint32_t it = wq_base + pos;
-                                q_ws[it] = (uint32_t)ws | ((uint32_t)interior << 31);
-                                q_blk[it] = blk;
-                                q_p[it] = pend;
-                                q_c0[it] = c0 & pend;
-                                q_c1[it] = c1 & pend;
-                                q_c2[it] = c2 & pend;
-                            } else {
-                                uint32_t pp = pend, f = 0u;
-                                while (pp) {
-                                    const int b = __builtin_ctz(pp);
-                                    pp &= pp - 1u;
-                                    const uint32_t cls = ((c0 >> b) & 1u) | (((c1 >> b) & 1u) << 1) | (((c2 >> b) & 1u) << 2);
-                                    const uint4 lo = philox(make_uint4(16u * blk + (uint32_t)b, rep, (uint32_t)sweep, w3lo),
-                                                            a.seed_lo, a.seed_hi);
-                                    if ((lo.x & 0xFFFFFFu) < tlow[cls]) f |= 1u << b;
-                                }
-                                acc ^= HB ? f : 0u;
-                                acc |= HB ? 0u : f;
-                            }
-                        }
-                        wq_n = min(wq_cap, wq_n + (uint32_t)__popcll(m));
-                    }
-                    const uint32_t Sn = HB ? acc : (S ^ acc);
-                    lds[ws] = Sn;
+                    const uint32_t Sn = HB ? ~lt : MCS_BOP3(S, ge3, lt, MCS_A ^ (MCS_B | MCS_C));
+                    pend = HB ? eq : (eq & ~ge3);
+                    lds[is] = Sn;
+                    ws = (uint32_t)is;
                     if (interior) {
                         // bonds of the odd sites after their update
-                        const uint32_t b1 = Sn ^ w1, b2 = Sn ^ w2, b3 = Sn ^ w3b, b4 = Sn ^ w4, b5 = Sn ^ w5,
-                                       b6 = Sn ^ w6;
-                        e_acc += 2 * (int)(__builtin_popcount(b1) + __builtin_popcount(b2) + __builtin_popcount(b3) +
-                                           __builtin_popcount(b4) + __builtin_popcount(b5) + __builtin_popcount(b6)) -
-                                 192;
-                        m_acc += 64 - 2 * (int)(__builtin_popcount(Sn) + __builtin_popcount(O));
+                        n_acc += (int)(__builtin_popcount(Sn ^ w1) + __builtin_popcount(Sn ^ w2) +
+                                       __builtin_popcount(Sn ^ w3b) + __builtin_popcount(Sn ^ w4) +
+                                       __builtin_popcount(Sn ^ w5) + __builtin_popcount(Sn ^ w6));
+                        d_acc += (int)(__builtin_popcount(Sn) + __builtin_popcount(O));
                     }
+                }
+                const uint64_t m = __ballot(pend != 0u);
+                if (m) {
+                    const uint32_t cnt = (uint32_t)__popcll(m);
+                    if (qn + cnt > (uint32_t)kTieQueue) settle();
+                    if (pend) {
+                        const uint32_t at = qn + wave_rank(m);
+                        tq[at] = make_uint4(ws | ((uint32_t)interior << 31), blk, pend, c0);
+                        tq2[at] = make_uint2(c1, c2);
+                    }
+                    qn += cnt;
+                }
+                iz += Qz;
+                iy += Qy;
+                row += Qz * Ry + Qy;
+                if (iy >= ny) {
+                    iy -= ny;
+                    ++iz;
+                    row += Ry - ny;
                 }
             }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) wq_n = max(wq_n, (uint32_t)__shfl_xor((int)wq_n, off, 64));
-            if ((tid & 63) == 0) q_cnt[wave] = wq_n;
-            __syncthreads();
-            uint32_t total = 0;
-            for (int sg = 0; sg < nwaves; ++sg) total += q_cnt[sg];
-            for (uint32_t i = tid; i < total; i += nt) {
-                uint32_t sg = 0, k = i;
-                while (k >= q_cnt[sg]) k -= q_cnt[sg++];
-                const uint32_t it = sg * wq_cap + k;
-                const uint32_t wsm = q_ws[it], blk = q_blk[it], pend = q_p[it];
-                const uint32_t c0 = q_c0[it], c1 = q_c1[it], c2 = q_c2[it];
-                uint32_t pp = pend, f = 0u;
-                int de = 0;
-                while (pp) {
-                    const int b = __builtin_ctz(pp);
-                    pp &= pp - 1u;
-                    const uint32_t cls = ((c0 >> b) & 1u) | (((c1 >> b) & 1u) << 1) | (((c2 >> b) & 1u) << 2);
-                    const uint4 lo = philox(make_uint4(16u * blk + (uint32_t)b, rep, (uint32_t)sweep, w3lo), a.seed_lo,
-                                            a.seed_hi);
-                    if ((lo.x & 0xFFFFFFu) < tlow[cls]) {
-                        f |= 1u << b;
-                        // energy change of the flip: Metropolis 12 - 4a,
-                        // heat-bath (-1 -> +1) 4d - 12
-                        de += HB ? 4 * (int)cls - 12 : 12 - 4 * (int)cls;
-                    }
-                }
-                if (f) {
-                    const uint32_t ws = wsm & 0x7FFFFFFFu, old = lds[ws];
-                    lds[ws] = old ^ f;
-                    if (MEASURE && (wsm >> 31)) {
-                        e_acc += de;
-                        m_acc += 2 * (2 * __builtin_popcount(old & f) - __builtin_popcount(f));
-                    }
-                }
-            }
+            settle();
             if (MEASURE && c == 1) {
-                e_acc = wave_sum_i(e_acc);
-                m_acc = wave_sum_i(m_acc);
-                if ((tid & 63) == 0) {
-                    red[0][wave] = e_acc;
-                    red[1][wave] = m_acc;
+                n_acc = wave_sum_last(n_acc);
+                d_acc = wave_sum_last(d_acc);
+                if ((tid & 63) == 63) {
+                    red[0][wave] = n_acc;
+                    red[1][wave] = d_acc;
                 }
             }
             __syncthreads();
-            wq_n = 0;
         }
         if (MEASURE && tid == 0) {
-            long long te = 0, tm = 0;
+            long long n = 0, d = 0;
             for (int i = 0; i < nwaves; ++i) {
-                te += red[0][i];
-                tm += red[1][i];
+                n += red[0][i];
+                d += red[1][i];
             }
-            *em_slot(a.em.slots, s, l, nlat, blockIdx.x, ntile) = make_longlong2(te, tm);
+            // every bond once: 2 (anti-aligned) - 6 per odd site; M from both parities
+            const long long words = (long long)hy * hz * Wd;
+            *em_slot(a.em.slots, s, l, nlat, blockIdx.x, ntile) =
+                make_longlong2(2 * n - 192 * words, 64 * words - 2 * d);
         }
     }
 
     // ---- store the tile's own rows
-    const int own = hy * hz;
+    const int own_rows = hy * hz;
     const float invhy = 1.0f / (float)hy;
-    for (int rr = r0; rr < own; rr += Q) {
+    for (int rr = r0; rr < own_rows; rr += Q) {
         int iz, iy;
         divmod_small(rr, hy, invhy, iz, iy);
         const int row = (R + iz) * Ry + (R + iy);
@@ -414,23 +443,35 @@ bool tile3d_supported(const SweepCall &c, int layout)
            c.g.Lz >= 4 && (!c.per_lattice || c.g.count <= kMaxTableLattices);
 }
 
+// Of the tile's rows (with couplings), the size a plan is checked by.
 size_t tile3d_lds_bytes(int Lx, int H, int K, bool hasJ)
 {
     const size_t side = (size_t)H + 4 * (size_t)K;
     const size_t words = (side * side * 2 * (size_t)(Lx / 64) * (hasJ ? 4 : 1) + 3) & ~(size_t)3;
-    return (words + 64) * 4;  // rows, then the 8 x 8 threshold masks
+    return (words + 64) * 4;
 }
+
+// The rows, a word per row, each wave's tie queue.
+static size_t tile3d_dynamic_lds(int Lx, int H, int K, bool hasJ, int threads)
+{
+    const size_t side = (size_t)H + 4 * (size_t)K, rows = side * side;
+    const size_t words = (rows * (2 * (size_t)(Lx / 64) * (hasJ ? 4 : 1) + 1) + 3) & ~(size_t)3;
+    return words * 4 + (K ? (size_t)(threads / 64) * kTieQueue * 24 : 0);
+}
+// a plan's rows take at most 96 KB, with couplings 4 x 8 bytes and up each
+constexpr int kTile3DMaxLds = 98304 + 98304 / 32 * 4 + 16 * kTieQueue * 24;
+static_assert(kTile3DMaxLds <= 155 * 1024, "next to the static arrays in 160 KB");
 
 template <int K, bool HB, bool HASJ>
 static hipError_t launch3(const Tile3DArgs &a, int H, int count, int threads, hipStream_t s)
 {
-    const size_t lds = tile3d_lds_bytes(a.Lx, H, K, HASJ);
+    const size_t lds = tile3d_dynamic_lds(a.Lx, H, K, HASJ, threads);
     dim3 grid((unsigned)(a.nty * a.ntz), (unsigned)count);
     static LdsLimit lim[2];
     {
         const void *f =
             a.em.slots ? (const void *)k_tile3d<K, true, HB, HASJ> : (const void *)k_tile3d<K, false, HB, HASJ>;
-        const hipError_t e = lim[a.em.slots ? 1 : 0].ensure(f, 98304);
+        const hipError_t e = lim[a.em.slots ? 1 : 0].ensure(f, kTile3DMaxLds);
         if (e != hipSuccess) return e;
     }
     if (a.em.slots) hipLaunchKernelGGL((k_tile3d<K, true, HB, HASJ>), grid, dim3(threads), lds, s, a);
