@@ -259,7 +259,7 @@ int mc_sweep_path(mc_ctx *ctx, const mc_geom *geom, int32_t rule, int32_t has_co
  * only, never results (the determinism contract above).  mc_set_tile_plan
  * fixes it for the geometry (dims, extents, count) on this context;
  * mc_get_tile_plan reports the tuned or set shape, else a nominal default;
- * with neither, a 2D call picks its own shape by its number of sweeps.
+ * with neither, a call picks its own shape by its number of sweeps.
  * Host-only calls.  A plan needs H >= 1, K >= 1 and threads a
  * multiple of 64 in 64..1024; in 2D H >= 4, K <= 8, the Lx/64 words of a row either
  * at most threads or a multiple of it, and (H + 4K) rows of 2 Lx/64 words

@@ -45,7 +45,7 @@ size_t fused_workspace_bytes(const Geom &g, int layout)
 
 // Nominal launch shape of a geometry (mc_get_tile_plan's when none is set or
 // tuned): enough bands to give every CU work, sweeps per launch limited so the
-// redone halo stays small.  In 2D a call's launches use call_plan below.
+// redone halo stays small.  A call's launches use call_plan below.
 TilePlan default_tile_plan(const Geom &g)
 {
     TilePlan p;
@@ -110,6 +110,41 @@ static TilePlan plan_for(mc_ctx *ctx, const Geom &g)
     return default_tile_plan(g);
 }
 
+// Launch shape of a call of n sweeps on 3D lattices without a set or tuned
+// plan: as in 2D (below), with 0.15 us for every 64 words (the class
+// multiplexers) and a tile's halo on both sides in y and z.  Measured (and
+// modelled), us per sweep, heat-bath: 256^3 x 4, H = 16, K = 2 32 (33); 256^3
+// 12.7 (12); 128^3, the chosen 8, 3 6.4 (6.1), the nominal 16, 2 (64 tiles) 9.2
+// (8.8); 64^3, 4, 4 5.2 (4.6), 16, 2 7.6 (7.1).
+static TilePlan call_plan_3d(const Geom &g, int n)
+{
+    constexpr int kCUs = 256;
+    TilePlan p = default_tile_plan(g);
+    double best = 1e300;
+    const int Hmax = std::min(32, std::min(g.Ly, g.Lz));
+    for (int H = std::min(4, Hmax); H <= Hmax; ++H) {
+        const int64_t tiles = (int64_t)((g.Ly + H - 1) / H) * ((g.Lz + H - 1) / H);
+        const int64_t per_cu = (tiles * g.count + kCUs - 1) / kCUs;
+        for (int K = 1; K <= 4; ++K) {
+            TilePlan q;
+            q.H = H;
+            q.K = K;
+            q.threads = per_cu >= 4 ? 256 : per_cu > 1 || H < 16 ? 512 : 768;
+            if (!plan_ok(g, q)) continue;
+            const int launches = n == 1 ? 1 : std::max(2, (n + K - 1) / K);
+            const int Ke = (n + launches - 1) / launches;  // sweeps of the longest launch
+            double rows = 0;
+            for (int h = 0; h < 2 * Ke; ++h) rows += (double)(H + 4 * Ke - 2 * h - 2) * (H + 4 * Ke - 2 * h - 2);
+            const double t = launches * (6.0 + 2.4 * Ke + 0.15 * rows * (g.Lx / 64) / 64.0 * (double)per_cu);
+            if (t < best * 0.999) {
+                best = t;
+                p = q;
+            }
+        }
+    }
+    return p;
+}
+
 // Launch shape of a call of n sweeps on 2D lattices without a set or tuned
 // plan: the one with the smallest modelled time.  A launch of K sweeps on bands
 // of H rows costs 6 us (the gap to the next launch, load and store) and per
@@ -122,7 +157,8 @@ static TilePlan plan_for(mc_ctx *ctx, const Geom &g)
 // nominal 4, 1 6.4 (8.1).
 static TilePlan call_plan(mc_ctx *ctx, const Geom &g, int n)
 {
-    if (g.dims == 3 || ctx->tile_plans.count(plan_key(g))) return plan_for(ctx, g);
+    if (ctx->tile_plans.count(plan_key(g))) return plan_for(ctx, g);
+    if (g.dims == 3) return call_plan_3d(g, n);
     constexpr int kCUs = 256;
     const int Wd = g.Lx / 64;
     TilePlan p = default_tile_plan(g);
