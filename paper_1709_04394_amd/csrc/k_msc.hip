@@ -13,15 +13,28 @@
 //    of replica b for the 4 groups of 16 sites the wave covers, whose
 //    half-words are the random bit-planes of those sites (the stream the int8
 //    kernels use, so lane b of the word lattice equals the int8 run of that
-//    replica bit for bit).  A 64 x 64 bit transpose across the lanes
-//    (xor-shuffles at distances 32 .. 1) turns "replica b, 64 sites" into
-//    "site s, 64 replicas"; then each lane compares its site's 64 replicas
-//    against the class thresholds bit-serially.  Ties (top byte equal) draw
-//    their low 24 bits in place.
-//  * Per-sweep E and M per replica are summed in the odd half-sweep: the
-//    bond and down-spin count planes of the 64 sites are transposed back so
-//    that lane b adds up replica b; one atomic per replica and workgroup.
+//    replica bit for bit).  A 64 x 64 bit transpose of all eight planes at once
+//    (lane_bits.hpp) turns "replica b, 64 sites" into "site s, 64 replicas";
+//    then each lane compares its site's 64 replicas against their classes'
+//    thresholds bit-serially.
+//  * Words with ties (a replica whose top byte equals its class's threshold's,
+//    one word in seven at criticality) wait in a queue of their wave, across
+//    tasks, and are settled 64 at a time, one word per lane; their spins are
+//    stored then.
+//  * Per-sweep E and M per replica are counted in the odd half-sweep: each lane
+//    adds the unsatisfied bonds and down spins of its sites to bit-sliced
+//    counters of the 64 replicas, which are summed over the lanes once in 32
+//    tasks; one atomic per replica and workgroup.
+//
+// What bounds it: VALU issue.  4096^2, 64 replicas, Metropolis: 133 us per
+// even half-sweep and 173 with E, M, against 238 and 311 with a transpose per
+// plane through ds_swizzle (36 instructions per word), a transpose back for
+// every count of every task, rows by 64-bit division, and ties drawn in place.
+#include <algorithm>
+
 #include "internal.hpp"
+#include "lane_bits.hpp"
+#include "metro2d.hpp"
 
 namespace mcs {
 
@@ -40,220 +53,225 @@ struct MscArgs {
     int64_t *EM;  // this sweep's [count * 64][2], or nullptr
 };
 
-// Lane exchange at xor distance D: ds_swizzle in its xor mode (and mask 0x1F,
-// xor mask D; within groups of 32 lanes) for D <= 16, a permute across the
-// wave for D = 32.
-template <int D>
-__device__ __forceinline__ uint32_t xor_lane(uint32_t x)
+// Bit-sliced count (c0, c1, c2) of the set bits among Z words.
+template <int Z>
+__device__ __forceinline__ void count_words(const uint32_t (&x)[6], uint32_t &c0, uint32_t &c1, uint32_t &c2)
 {
-    if constexpr (D == 32)
-        return (uint32_t)__shfl_xor((int)x, 32, 64);
-    else
-        return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (D << 10) | 0x1F);
+    const uint32_t s1 = xor3(x[0], x[1], x[2]);
+    const uint32_t k1 = MCS_BOP3(x[0], x[1], x[2], (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
+    if constexpr (Z == 6) {
+        const uint32_t s2 = xor3(x[3], x[4], x[5]);
+        const uint32_t k2 = MCS_BOP3(x[3], x[4], x[5], (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
+        const uint32_t kk = s1 & s2;
+        c0 = s1 ^ s2;
+        c1 = xor3(k1, k2, kk);
+        c2 = MCS_BOP3(k1, k2, kk, (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
+    } else {
+        const uint32_t kk = s1 & x[3];
+        c0 = s1 ^ x[3];
+        c1 = k1 ^ kk;
+        c2 = k1 & kk;
+    }
 }
 
-// One stage of the transpose: lanes i and i ^ D swap d-bit blocks.  The lane
-// with bit D clear keeps the low block of each 2D-bit group and takes its
-// partner's low block into the high position; the other lane keeps the high
-// block and takes its partner's high block into the low position.  The select
-// is a per-lane mask, not a branch (the two lanes of a pair take different
-// sides).
-template <int D>
-__device__ __forceinline__ uint64_t transpose_stage(uint64_t v, int lane)
-{
-    constexpr uint64_t M = D == 32 ? 0x00000000FFFFFFFFull
-                         : D == 16 ? 0x0000FFFF0000FFFFull
-                         : D == 8  ? 0x00FF00FF00FF00FFull
-                         : D == 4  ? 0x0F0F0F0F0F0F0F0Full
-                         : D == 2  ? 0x3333333333333333ull
-                                   : 0x5555555555555555ull;
-    const uint32_t lo = xor_lane<D>((uint32_t)v), hi = xor_lane<D>((uint32_t)(v >> 32));
-    const uint64_t p = ((uint64_t)hi << 32) | lo;
-    const uint64_t sel = (lane & D) ? ~0ull : 0ull;
-    const uint64_t keep = M ^ sel;                      // M on the low side, ~M on the high side
-    const uint64_t up = p << D, down = p >> D;
-    const uint64_t t = up ^ ((up ^ down) & sel);        // partner's block moved into place
-    return (v & keep) | (t & ~keep);
-}
-
-// 64 x 64 bit transpose across the wave: on entry lane b holds row b, on exit
-// lane s holds column s (bit b of the result = bit s of lane b's row).
-__device__ __forceinline__ uint64_t transpose64(uint64_t v, int lane)
-{
-    v = transpose_stage<32>(v, lane);
-    v = transpose_stage<16>(v, lane);
-    v = transpose_stage<8>(v, lane);
-    v = transpose_stage<4>(v, lane);
-    v = transpose_stage<2>(v, lane);
-    return transpose_stage<1>(v, lane);
-}
+constexpr int kMscFlush = 32;  // tasks between sums of the bit-sliced counters
 
 template <int DIMS, bool MEASURE, bool HB, bool HASJ>
 __global__ __launch_bounds__(256) void k_msc(MscArgs a)
 {
     __shared__ uint32_t tlow[8];
     __shared__ long long red[2][64];
+    // tied words: {word, same-colour index, tied replicas}, {word with those
+    // unsettled, class bit 0}, {class bits 1, 2}
+    __shared__ uint4 q_id[4][kTieQueue], q_s[4][kTieQueue], q_c[(HB || DIMS == 3) ? 4 : 1][kTieQueue];
     constexpr int Z = 2 * DIMS;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = blockIdx.y;
     if (tid < 8) tlow[tid] = a.low[tid];
     if (MEASURE && tid < 128) red[tid >> 6][tid & 63] = 0;
     __syncthreads();
+    const LaneBits lb = lane_bits(tid & 63);
     uint64_t *w = a.w + (int64_t)l * a.N;
-    const int hx = a.Lx >> 1;
-    const int64_t tasks = (a.N >> 1) >> 6;
-    const uint32_t rep = a.replica0 + 64u * (uint32_t)l + (uint32_t)lane;
-    long long e_acc = 0, m_acc = 0;
-    for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < tasks; t += (int64_t)gridDim.x * 4) {
-        const int64_t j0 = t << 6;
-        const int64_t row = j0 / hx;
-        const int m0 = (int)(j0 - row * hx);
-        const int y = (int)(row % a.Ly), z = (int)(row / a.Ly);
-        const int par = (a.c + y + z) & 1;
-        const int x = 2 * (m0 + lane) + par;
-        const int64_t rbase = row * a.Lx;
-        const int64_t i = rbase + x;
-        const int xp = x + 1 == a.Lx ? 0 : x + 1, xm = x == 0 ? a.Lx - 1 : x - 1;
-        const int64_t ryp = (int64_t)(y + 1 == a.Ly ? 0 : y + 1) * a.Lx + (int64_t)z * a.Ly * a.Lx;
-        const int64_t rym = (int64_t)(y == 0 ? a.Ly - 1 : y - 1) * a.Lx + (int64_t)z * a.Ly * a.Lx;
-        const uint64_t S = w[i];
-        uint64_t n[6];
-        int64_t bi[6];
-        n[0] = w[rbase + xp], bi[0] = i;
-        n[1] = w[rbase + xm], bi[1] = rbase + xm;
-        n[2] = w[ryp + x], bi[2] = a.N + i;
-        n[3] = w[rym + x], bi[3] = a.N + rym + x;
-        if (DIMS == 3) {
-            const int64_t plane = (int64_t)a.Ly * a.Lx;
-            const int64_t rzp = (z + 1 == a.Lz ? 0 : z + 1) * plane + (int64_t)y * a.Lx;
-            const int64_t rzm = (z == 0 ? a.Lz - 1 : z - 1) * plane + (int64_t)y * a.Lx;
-            n[4] = w[rzp + x], bi[4] = 2 * a.N + i;
-            n[5] = w[rzm + x], bi[5] = 2 * a.N + rzm + x;
+    const uint32_t per_row = (uint32_t)a.Lx >> 7;  // tasks per row
+    const uint32_t tasks = (uint32_t)(a.N >> 7);
+    const uint32_t rep0 = a.replica0 + 64u * (uint32_t)l;
+    // the classes' threshold bits as full masks: even classes in vector
+    // registers (an instruction reads one scalar)
+    uint32_t tv[8][3], ts[8][4];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            tv[k][i] = ((a.top[2 * i] >> k) & 1u) ? ~0u : 0u;
+            if (i < (HB ? DIMS : 1)) asm volatile("" : "+v"(tv[k][i]));
         }
-        // wk: bit set <=> J s_j = -1 for replica b
-        uint64_t wk[6];
 #pragma unroll
-        for (int k = 0; k < Z; ++k) wk[k] = n[k] ^ ((HASJ && a.J[bi[k]] < 0) ? ~0ull : 0ull);
-        uint64_t xk[6];
-#pragma unroll
-        for (int k = 0; k < Z; ++k) xk[k] = HB ? wk[k] : (wk[k] ^ S);
-        uint64_t c0, c1, c2;
-        {
-            const uint64_t s1 = xk[0] ^ xk[1] ^ xk[2];
-            const uint64_t k1 = (xk[0] & xk[1]) | (xk[0] & xk[2]) | (xk[1] & xk[2]);
-            if (DIMS == 3) {
-                const uint64_t s2 = xk[3] ^ xk[4] ^ xk[5];
-                const uint64_t k2 = (xk[3] & xk[4]) | (xk[3] & xk[5]) | (xk[4] & xk[5]);
-                c0 = s1 ^ s2;
-                const uint64_t kk = s1 & s2;
-                c1 = k1 ^ k2 ^ kk;
-                c2 = (k1 & k2) | (k1 & kk) | (k2 & kk);
-            } else {
-                c0 = s1 ^ xk[3];
-                const uint64_t kk = s1 & xk[3];
-                c1 = k1 ^ kk;
-                c2 = k1 & kk;
+        for (int i = 0; i < 4; ++i) ts[k][i] = ((a.top[i < 3 ? 2 * i + 1 : 6] >> k) & 1u) ? ~0u : 0u;
+    }
+    uint32_t qn = 0;
+    auto settle = [&]() {
+        const uint32_t q = tid & 63;
+        if (q < qn) {
+            const uint4 id = q_id[wave][q], sw = q_s[wave][q];
+            uint4 cw = make_uint4(0u, 0u, 0u, 0u);
+            if (HB || DIMS == 3) cw = q_c[wave][q];
+            uint64_t pend = ((uint64_t)id.w << 32) | id.z, S = ((uint64_t)sw.y << 32) | sw.x;
+            const uint64_t c0 = ((uint64_t)sw.w << 32) | sw.z, c1 = ((uint64_t)cw.y << 32) | cw.x,
+                           c2 = ((uint64_t)cw.w << 32) | cw.z;
+            while (pend) {
+                const int b = __builtin_ctzll(pend);
+                pend &= pend - 1ull;
+                const uint32_t cls = (uint32_t)((c0 >> b) & 1ull) | ((uint32_t)((c1 >> b) & 1ull) << 1) |
+                                     ((uint32_t)((c2 >> b) & 1ull) << 2);
+                const uint4 lo =
+                    philox(make_uint4(id.y, rep0 + (uint32_t)b, a.sweep_lo, a.w3lo), a.seed_lo, a.seed_hi);
+                // Metropolis: flip; heat-bath: the provisional -1 becomes +1
+                if ((lo.x & 0xFFFFFFu) < tlow[cls]) {
+                    if (MEASURE) {
+                        // unsatisfied bonds gained: Metropolis z - 2a, heat-bath 2d - z
+                        const int du = HB ? 2 * (int)cls - Z : Z - 2 * (int)cls;
+                        atomicAdd((unsigned long long *)&red[0][b], (unsigned long long)(long long)(2 * du));
+                        atomicAdd((unsigned long long *)&red[1][b],
+                                  (unsigned long long)(((S >> b) & 1ull) ? 2ll : -2ll));
+                    }
+                    S ^= 1ull << b;
+                }
             }
+            w[id.x] = S;
         }
-        // Metropolis: a >= z/2 gives dE <= 0
-        const uint64_t ge = HB ? 0ull : (DIMS == 3 ? (c2 | (c1 & c0)) : (c2 | c1));
+        qn = 0;
+    };
+    BitCounter<8> cu;  // unsatisfied bonds of the odd sites, up to 6 a task
+    BitCounter<7> cd;  // down spins of both sites of a pair
+    long long u_acc = 0, d_acc = 0;
+    int since = 0;
+    if (MEASURE) {
+        cu.clear();
+        cd.clear();
+    }
+    uint32_t done = 0;
+    for (uint32_t t = blockIdx.x * 4u + (uint32_t)wave; t < tasks; t += gridDim.x * 4u) {
+        const uint32_t j0 = t << 6;
+        const uint32_t row = t / per_row, m0 = (t - row * per_row) << 6;
+        const uint32_t z = row / (uint32_t)a.Ly, y = row - z * (uint32_t)a.Ly;
+        const int par = (int)((uint32_t)a.c + y + z) & 1;
+        const uint32_t x = 2u * (m0 + (uint32_t)lb.label) + (uint32_t)par;
+        const int64_t plane = (int64_t)a.Ly * a.Lx, rbase = (int64_t)row * a.Lx;
+        const uint32_t xp = x + 1 == (uint32_t)a.Lx ? 0 : x + 1, xm = x == 0 ? (uint32_t)a.Lx - 1 : x - 1;
+        const int64_t ryp = y + 1 == (uint32_t)a.Ly ? rbase - (plane - a.Lx) : rbase + a.Lx;
+        const int64_t rym = y == 0 ? rbase + (plane - a.Lx) : rbase - a.Lx;
+        const int64_t rzp = z + 1 == (uint32_t)a.Lz ? rbase - (a.N - plane) : rbase + plane;
+        const int64_t rzm = z == 0 ? rbase + (a.N - plane) : rbase - plane;
+        const uint64_t S = (w + rbase)[x];
+        uint64_t n[6] = {(w + rbase)[xp], (w + rbase)[xm], (w + ryp)[x], (w + rym)[x], 0, 0};
+        if (DIMS == 3) {
+            n[4] = (w + rzp)[x];
+            n[5] = (w + rzm)[x];
+        }
         // random planes: lane = replica, 4 groups of 16 sites -> transpose
         uint4 B[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            B[g] = philox(make_uint4((uint32_t)((j0 >> 4) + g), rep, a.sweep_lo, a.w3), a.seed_lo, a.seed_hi);
-        // One indicator word per class (heat-bath d = 0..6; Metropolis a below
-        // z/2, larger a being accepted outright); a plane's threshold word is the
-        // OR of the indicators of the classes whose threshold has that bit, the
-        // bits being uniform (argument block), so only the indicator words stay
-        // live across the planes.
-        constexpr int NC = HB ? 7 : DIMS;  // Metropolis: a = 0 .. z/2 - 1
-        uint64_t onehot[7];
-        uint32_t tp[7];
-        {
-            const uint64_t n0 = ~c0, n1 = ~c1, n2 = ~c2;
-            onehot[0] = n2 & n1 & n0;
-            onehot[1] = n2 & n1 & c0;
-            onehot[2] = n2 & c1 & n0;
-            onehot[3] = n2 & c1 & c0;
-            onehot[4] = c2 & n1 & n0;
-            onehot[5] = c2 & n1 & c0;
-            onehot[6] = c2 & c1 & n0;
-            // the thresholds' top bytes, marked as redefined per task so the plane
-            // masks below are formed where used, not hoisted out of the task loop
-            // into scalar registers (where they would spill)
-#pragma unroll
-            for (int d = 0; d < NC; ++d) {
-                tp[d] = a.top[d];
-                asm volatile("" : "+s"(tp[d]));
-            }
-        }
-        uint64_t lt = 0ull, eq = ~0ull;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const uint64_t rowk = (uint64_t)plane_pair(B[0], B[1], k) | ((uint64_t)plane_pair(B[2], B[3], k) << 32);
-            const uint64_t X = transpose64(rowk, lane);
-            uint32_t tlo = 0u, thi = 0u;
-#pragma unroll
-            for (int d = 0; d < NC; ++d) {
-                const uint32_t m = ((tp[d] >> k) & 1u) ? ~0u : 0u;
-                tlo |= (uint32_t)onehot[d] & m;
-                thi |= (uint32_t)(onehot[d] >> 32) & m;
-            }
-            const uint64_t T = ((uint64_t)thi << 32) | tlo;
-            lt = (~X & T) | (~X & lt) | (T & lt);
-            eq = eq & ~(X ^ T);
-        }
-        uint64_t acc = HB ? ~lt : (ge | lt);
-        uint64_t pend = HB ? eq : (eq & ~ge);
-        const uint32_t j = (uint32_t)(j0 + lane);
-        while (pend) {
-            const int b = __builtin_ctzll(pend);
-            pend &= pend - 1ull;
-            const uint32_t cls = (uint32_t)((c0 >> b) & 1ull) | ((uint32_t)((c1 >> b) & 1ull) << 1) |
-                                 ((uint32_t)((c2 >> b) & 1ull) << 2);
-            const uint4 lo = philox(make_uint4(j, a.replica0 + 64u * (uint32_t)l + (uint32_t)b, a.sweep_lo, a.w3lo),
-                                    a.seed_lo, a.seed_hi);
-            // Metropolis: flip; heat-bath: the provisional -1 becomes +1
-            if ((lo.x & 0xFFFFFFu) < tlow[cls]) acc ^= (HB ? 1ull : 0ull) << b, acc |= (HB ? 0ull : 1ull) << b;
-        }
-        const uint64_t Sn = HB ? acc : (S ^ acc);
-        w[i] = Sn;
-        if (MEASURE) {
-            // odd sites: their bonds after the update; both sites of the pair
-            // (this odd site and the even site at the same row position) for M
-            uint64_t u[6];
-#pragma unroll
-            for (int k = 0; k < Z; ++k) u[k] = Sn ^ wk[k];
-            uint64_t u0, u1, u2;
-            const uint64_t s1 = u[0] ^ u[1] ^ u[2];
-            const uint64_t k1 = (u[0] & u[1]) | (u[0] & u[2]) | (u[1] & u[2]);
+            B[g] = philox(make_uint4((j0 >> 4) + (uint32_t)g, rep0 + (uint32_t)lb.label, a.sweep_lo, a.w3), a.seed_lo,
+                          a.seed_hi);
+        transpose_blocks(B, lb);
+        uint64_t jm[6] = {0, 0, 0, 0, 0, 0};
+        if (HASJ) {
+            const int8_t *J = a.J;
+            jm[0] = (J + rbase)[x] < 0 ? ~0ull : 0ull;
+            jm[1] = (J + rbase)[xm] < 0 ? ~0ull : 0ull;
+            jm[2] = (J + a.N + rbase)[x] < 0 ? ~0ull : 0ull;
+            jm[3] = (J + a.N + rym)[x] < 0 ? ~0ull : 0ull;
             if (DIMS == 3) {
-                const uint64_t s2 = u[3] ^ u[4] ^ u[5];
-                const uint64_t k2 = (u[3] & u[4]) | (u[3] & u[5]) | (u[4] & u[5]);
-                u0 = s1 ^ s2;
-                const uint64_t kk = s1 & s2;
-                u1 = k1 ^ k2 ^ kk;
-                u2 = (k1 & k2) | (k1 & kk) | (k2 & kk);
-            } else {
-                u0 = s1 ^ u[3];
-                const uint64_t kk = s1 & u[3];
-                u1 = k1 ^ kk;
-                u2 = k1 & kk;
+                jm[4] = (J + 2 * a.N + rbase)[x] < 0 ? ~0ull : 0ull;
+                jm[5] = (J + 2 * a.N + rzm)[x] < 0 ? ~0ull : 0ull;
             }
-            const uint64_t pw = par == 1 ? n[1] : n[0];  // the even site 2m + (1 - par)
-            const uint64_t d0 = Sn ^ pw, d1 = Sn & pw;
-            const uint64_t U0 = transpose64(u0, lane), U1 = transpose64(u1, lane), U2 = transpose64(u2, lane);
-            const uint64_t D0 = transpose64(d0, lane), D1 = transpose64(d1, lane);
-            const int ub = __popcll(U0) + 2 * __popcll(U1) + 4 * __popcll(U2);
-            const int db = __popcll(D0) + 2 * __popcll(D1);
-            e_acc += 2 * ub - 64 * Z;
-            m_acc += 128 - 2 * db;
+        }
+        uint32_t So[2], pend[2], C0[2], C1[2], C2[2];
+        uint64_t u[3] = {0, 0, 0}, dn[2] = {0, 0};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {  // replicas 32 h .. 32 h + 31
+            const uint32_t Sh = (uint32_t)(S >> (32 * h));
+            // wk: bit set <=> J s_j = -1; Metropolis counts unsatisfied bonds
+            // S ^ wk, heat-bath counts wk
+            uint32_t wk[6], xk[6];
+#pragma unroll
+            for (int k = 0; k < Z; ++k) {
+                wk[k] = (uint32_t)((n[k] ^ jm[k]) >> (32 * h));
+                xk[k] = HB ? wk[k] : (wk[k] ^ Sh);
+            }
+            uint32_t c0, c1, c2;
+            count_words<Z>(xk, c0, c1, c2);
+            // Metropolis: a >= z/2 gives dE <= 0
+            const uint32_t ge = HB ? 0u : DIMS == 3 ? MCS_BOP3(c2, c1, c0, MCS_A | (MCS_B & MCS_C)) : (c2 | c1);
+            uint32_t lt = 0u, eq = ~0u;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const uint32_t X = plane_pair(B[2 * h], B[2 * h + 1], k);
+                auto mux = [](uint32_t sel, uint32_t hi, uint32_t lo) {
+                    return MCS_BOP3(sel, hi, lo, (MCS_A & MCS_B) | (~MCS_A & MCS_C));
+                };
+                uint32_t T = mux(c0, ts[k][0], tv[k][0]);  // classes 0, 1
+                if (HB) {
+                    T = mux(c1, mux(c0, ts[k][1], tv[k][1]), T);
+                    T = DIMS == 3 ? mux(c2, mux(c1, ts[k][3], mux(c0, ts[k][2], tv[k][2])), T) : mux(c2, tv[k][2], T);
+                } else if (DIMS == 3) {
+                    T = mux(c1, tv[k][1], T);
+                }
+                lt = MCS_BOP3(X, T, lt, (~MCS_A & MCS_B) | (~MCS_A & MCS_C) | (MCS_B & MCS_C));
+                eq = MCS_BOP3(eq, X, T, MCS_A & ~(MCS_B ^ MCS_C));
+            }
+            So[h] = HB ? ~lt : MCS_BOP3(Sh, ge, lt, MCS_A ^ (MCS_B | MCS_C));
+            pend[h] = HB ? eq : (eq & ~ge);
+            C0[h] = c0;
+            C1[h] = c1;
+            C2[h] = c2;
+            if (MEASURE) {
+                // odd sites: their bonds after the update; both sites of the pair
+                // (this odd site and the even site at the same row position) for M
+                uint32_t uk[6], v0, v1, v2;
+#pragma unroll
+                for (int k = 0; k < Z; ++k) uk[k] = So[h] ^ wk[k];
+                count_words<Z>(uk, v0, v1, v2);
+                const uint32_t pw = (uint32_t)((par ? n[1] : n[0]) >> (32 * h));  // even site 2m + (1 - par)
+                u[0] |= (uint64_t)v0 << (32 * h);
+                u[1] |= (uint64_t)v1 << (32 * h);
+                u[2] |= (uint64_t)v2 << (32 * h);
+                dn[0] |= (uint64_t)(So[h] ^ pw) << (32 * h);
+                dn[1] |= (uint64_t)(So[h] & pw) << (32 * h);
+            }
+        }
+        const bool tied = (pend[0] | pend[1]) != 0u;
+        if (!tied) (w + rbase)[x] = ((uint64_t)So[1] << 32) | So[0];
+        const uint64_t m = __ballot(tied);
+        const uint32_t cnt = (uint32_t)__popcll(m);
+        if (qn + cnt > (uint32_t)kTieQueue) settle();
+        if (tied) {
+            const uint32_t at = qn + wave_rank(m);
+            q_id[wave][at] = make_uint4((uint32_t)(rbase + x), j0 + (uint32_t)lb.label, pend[0], pend[1]);
+            q_s[wave][at] = make_uint4(So[0], So[1], C0[0], C0[1]);
+            if (HB || DIMS == 3) q_c[wave][at] = make_uint4(C1[0], C1[1], C2[0], C2[1]);
+        }
+        qn += cnt;
+        if (MEASURE) {
+            cu.add(u);
+            cd.add(dn);
+            ++done;
+            if (++since == kMscFlush) {
+                u_acc += cu.flush(lb);
+                d_acc += cd.flush(lb);
+                since = 0;
+            }
         }
     }
+    settle();
     if (MEASURE) {
-        atomicAdd((unsigned long long *)&red[0][lane], (unsigned long long)e_acc);
-        atomicAdd((unsigned long long *)&red[1][lane], (unsigned long long)m_acc);
+        u_acc += cu.flush(lb);
+        d_acc += cd.flush(lb);
+        // E: 2 (unsatisfied) - z per odd site; M: 2 - 2 (down) per pair
+        const long long e = 2 * u_acc - 64ll * Z * done, mg = 128ll * done - 2 * d_acc;
+        atomicAdd((unsigned long long *)&red[0][lb.label], (unsigned long long)e);
+        atomicAdd((unsigned long long *)&red[1][lb.label], (unsigned long long)mg);
         __syncthreads();
         if (tid < 128) {
             const int q = tid >> 6, b = tid & 63;
@@ -272,8 +290,9 @@ template <int D, bool HB, bool HJ>
 static hipError_t launch_msc_t(const MscArgs &a, int count, hipStream_t s)
 {
     const int64_t tasks = (a.N >> 1) >> 6;
-    int64_t blocks = (tasks + 3) / 4;
-    if (blocks > 1024) blocks = 1024;
+    // as many waves as fit at once (four per SIMD with the counters' registers,
+    // else eight), each walking its share of the tasks
+    const int64_t blocks = std::min<int64_t>((tasks + 3) / 4, a.EM ? 1024 : 2048);
     dim3 grid((unsigned)blocks, (unsigned)count);
     if (a.EM) hipLaunchKernelGGL((k_msc<D, true, HB, HJ>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((k_msc<D, false, HB, HJ>), grid, dim3(256), 0, s, a);
