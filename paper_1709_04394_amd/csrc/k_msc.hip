@@ -53,27 +53,6 @@ struct MscArgs {
     int64_t *EM;  // this sweep's [count * 64][2], or nullptr
 };
 
-// Bit-sliced count (c0, c1, c2) of the set bits among Z words.
-template <int Z>
-__device__ __forceinline__ void count_words(const uint32_t (&x)[6], uint32_t &c0, uint32_t &c1, uint32_t &c2)
-{
-    const uint32_t s1 = xor3(x[0], x[1], x[2]);
-    const uint32_t k1 = MCS_BOP3(x[0], x[1], x[2], (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
-    if constexpr (Z == 6) {
-        const uint32_t s2 = xor3(x[3], x[4], x[5]);
-        const uint32_t k2 = MCS_BOP3(x[3], x[4], x[5], (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
-        const uint32_t kk = s1 & s2;
-        c0 = s1 ^ s2;
-        c1 = xor3(k1, k2, kk);
-        c2 = MCS_BOP3(k1, k2, kk, (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
-    } else {
-        const uint32_t kk = s1 & x[3];
-        c0 = s1 ^ x[3];
-        c1 = k1 ^ kk;
-        c2 = k1 & kk;
-    }
-}
-
 constexpr int kMscFlush = 32;  // tasks between sums of the bit-sliced counters
 
 template <int DIMS, bool MEASURE, bool HB, bool HASJ>

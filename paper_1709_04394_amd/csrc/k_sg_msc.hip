@@ -8,13 +8,24 @@
 // per-realisation coupling words give every realisation's class (unsatisfied
 // bonds for Metropolis, neighbours with J s_j = -1 for heat-bath) as a
 // bit-sliced count.  The site's single 32-bit draw (the byte-lazy stream of
-// the word lattice's replica id) is compared once with each class threshold,
-// and the per-class outcomes are spread over the realisations of that class
-// with one-hot class words.  A tie (top byte equal to a threshold's that a
-// present class needs) draws the low 24 bits once for all realisations.
-// Per-sweep E and M per realisation come from the odd half-sweep through the
-// 64 x 64 bit transpose across the wave, as in the 64-replica kernel.
+// the word lattice's replica id) is compared once with each class threshold;
+// the outcomes, all-ones or zero per class, are selected per realisation by
+// the bits of its class.  A lane whose top byte equals a threshold's draws the
+// low 24 bits once for all realisations.  Per-sweep E and M per realisation
+// are bit-sliced counters of the odd half-sweep, summed over the lanes every
+// few tasks (lane_bits.hpp).
+//
+// What bounds it: memory.  A half-sweep reads every coupling word once and
+// every spin word, and writes half of those.  32^3, 4096 realisations (75 MB):
+// 15.0 us per even half-sweep, 5.0 TB/s, against 25.6 with workgroups dealt
+// round the L2 caches (each then read most rows' words and couplings again)
+// and rows by 64-bit division; 21.7 with E, M, against 33.4 with five 64 x 64
+// transposes per task.  Couplings loaded past the caches (non-temporal) cost
+// 15 %: a line of them serves two rows.
+#include <algorithm>
+
 #include "internal.hpp"
+#include "lane_bits.hpp"
 
 namespace mcs {
 
@@ -31,182 +42,181 @@ struct SgMscArgs {
     // heat-bath class d = neighbours with J s_j = -1, T of h = z - 2d
     uint32_t top[8], low[8];
     int64_t *EM;          // this sweep's [count * 64][2], or nullptr
+    uint32_t tasks;       // of 64 sites, per lattice
+    uint32_t parts;       // workgroups per lattice
+    uint32_t total;       // workgroups with work
+    // n / (Lx / 2) and n / Ly as the high word of a product, for n below the
+    // divisor + 64 (the divisor < 64; else the quotient is n >= divisor)
+    uint32_t mul_hx, mul_ly;
 };
 
-template <int D>
-__device__ __forceinline__ uint32_t sg_xor_lane(uint32_t x)
+// Workgroups of a launch, over all lattices.  Without E, M a wave takes one
+// task where there are enough: all its loads are then in flight with those of
+// seven others on its SIMD (32^3, 64 words per site: 15.0 us at 4096 or 8192
+// workgroups, 17.8 at 2048, 18.7 at 1024).  With E, M four tasks share a sum of
+// the counters over the lanes and the registers hold five waves (odd
+// half-sweep: 21.7 us at 1024 or 2048, 28 at 4096).
+constexpr int kSgBlocks = 4096, kSgBlocksEM = 1024;
+// Tasks between sums of the bit-sliced counters: four keep them at 18 registers
+// (32 tasks: 30 registers, and 25 us per odd half-sweep).
+constexpr int kSgFlush = 4, kSgPlanes = 5;
+
+// n / d for n < d + 64
+__device__ __forceinline__ uint32_t small_quotient(uint32_t n, uint32_t d, uint32_t mul)
 {
-    if constexpr (D == 32)
-        return (uint32_t)__shfl_xor((int)x, 32, 64);
-    else
-        return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (D << 10) | 0x1F);
+    return d >= 64u ? (n >= d ? 1u : 0u) : __umulhi(n, mul);
 }
 
-template <int D>
-__device__ __forceinline__ uint64_t sg_transpose_stage(uint64_t v, int lane)
+// I: the type of byte offsets within a lattice
+template <int DIMS, bool MEASURE, bool HB, class I>
+__global__ __launch_bounds__(256, 5) void k_sg_msc(SgMscArgs a)
 {
-    constexpr uint64_t M = D == 32 ? 0x00000000FFFFFFFFull
-                         : D == 16 ? 0x0000FFFF0000FFFFull
-                         : D == 8  ? 0x00FF00FF00FF00FFull
-                         : D == 4  ? 0x0F0F0F0F0F0F0F0Full
-                         : D == 2  ? 0x3333333333333333ull
-                                   : 0x5555555555555555ull;
-    const uint32_t lo = sg_xor_lane<D>((uint32_t)v), hi = sg_xor_lane<D>((uint32_t)(v >> 32));
-    const uint64_t p = ((uint64_t)hi << 32) | lo;
-    const uint64_t sel = (lane & D) ? ~0ull : 0ull;
-    const uint64_t keep = M ^ sel;
-    const uint64_t up = p << D, down = p >> D;
-    const uint64_t t = up ^ ((up ^ down) & sel);
-    return (v & keep) | (t & ~keep);
-}
-
-// 64 x 64 bit transpose across the wave (lane s ends with bit b = bit s of
-// lane b's word)
-__device__ __forceinline__ uint64_t sg_transpose64(uint64_t v, int lane)
-{
-    v = sg_transpose_stage<32>(v, lane);
-    v = sg_transpose_stage<16>(v, lane);
-    v = sg_transpose_stage<8>(v, lane);
-    v = sg_transpose_stage<4>(v, lane);
-    v = sg_transpose_stage<2>(v, lane);
-    return sg_transpose_stage<1>(v, lane);
-}
-
-// bit-sliced count (c0, c1, c2) of set bits among n words (n = 4 or 6)
-template <int Z>
-__device__ __forceinline__ void count_bits(const uint64_t (&x)[6], uint64_t &c0, uint64_t &c1, uint64_t &c2)
-{
-    const uint64_t s1 = x[0] ^ x[1] ^ x[2];
-    const uint64_t k1 = (x[0] & x[1]) | (x[0] & x[2]) | (x[1] & x[2]);
-    if constexpr (Z == 6) {
-        const uint64_t s2 = x[3] ^ x[4] ^ x[5];
-        const uint64_t k2 = (x[3] & x[4]) | (x[3] & x[5]) | (x[4] & x[5]);
-        c0 = s1 ^ s2;
-        const uint64_t kk = s1 & s2;
-        c1 = k1 ^ k2 ^ kk;
-        c2 = (k1 & k2) | (k1 & kk) | (k2 & kk);
-    } else {
-        c0 = s1 ^ x[3];
-        const uint64_t kk = s1 & x[3];
-        c1 = k1 ^ kk;
-        c2 = k1 & kk;
-    }
-}
-
-template <int DIMS, bool MEASURE, bool HB>
-__global__ __launch_bounds__(256) void k_sg_msc(SgMscArgs a)
-{
-    __shared__ long long red[2][64];
+    __shared__ int red[2][4][64];
     constexpr int Z = 2 * DIMS;
-    constexpr int NC = HB ? 7 : DIMS;  // heat-bath d = 0..6; Metropolis a = 0 .. z/2 - 1
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l = blockIdx.y;
-    if (MEASURE && tid < 128) red[tid >> 6][tid & 63] = 0;
-    __syncthreads();
-    uint64_t *w = a.w + (int64_t)l * a.N;
-    const uint64_t *Jl = a.J + (int64_t)l * DIMS * a.N;
-    const int hx = a.Lx >> 1;
-    const int64_t tasks = (a.N >> 1) >> 6;
-    const uint32_t rep = a.replica0 + (uint32_t)l;  // the shared stream of the 64 realisations
-    long long e_acc = 0, m_acc = 0;
-    for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < tasks; t += (int64_t)gridDim.x * 4) {
+    constexpr int NC = HB ? Z + 1 : DIMS;  // heat-bath d = 0..z; Metropolis a = 0 .. z/2 - 1
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // workgroups in the order of their sites on each of the 8 L2 caches:
+    // neighbouring rows' words and couplings are read from the same one
+    const uint32_t g = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (g >= a.total) return;
+    const uint32_t l = g / a.parts, part = g - l * a.parts;
+    const LaneBits lb = lane_bits(tid & 63);
+    char *w = (char *)(a.w + (int64_t)l * a.N);
+    const char *J0 = (const char *)(a.J + (int64_t)l * DIMS * a.N);
+    const char *J1 = J0 + a.N * 8, *J2 = J1 + (DIMS == 3 ? a.N * 8 : 0);
+    auto at = [](const char *p, I off) { return *(const uint64_t *)(p + off); };
+    const uint32_t hx = (uint32_t)a.Lx >> 1;
+    const uint32_t rep = a.replica0 + l;  // the shared stream of the 64 realisations
+    const I row_b = (I)a.Lx * 8, plane_b = (I)a.Ly * row_b;
+    BitCounter<kSgPlanes> cu;      // unsatisfied bonds of the odd sites, up to 6 a task
+    BitCounter<kSgPlanes - 1> cd;  // down spins of both sites of a pair
+    int u_acc = 0, d_acc = 0;
+    int since = 0;
+    uint32_t done = 0;
+    if (MEASURE) {
+        cu.clear();
+        cd.clear();
+    }
+    auto flush = [&]() {
+        u_acc += cu.flush(lb, 32 - __builtin_clz((unsigned)(Z * since)));
+        d_acc += cd.flush(lb, 32 - __builtin_clz((unsigned)(2 * since)));
+        since = 0;
+    };
+    const uint32_t t1 = (uint32_t)((uint64_t)a.tasks * (part + 1) / a.parts);
+    for (uint32_t t = (uint32_t)((uint64_t)a.tasks * part / a.parts) + (uint32_t)wave; t < t1; t += 4u) {
         // lane: same-colour site j = 64 t + lane
-        const int64_t j = (t << 6) + lane;
-        const int64_t row = j / hx;
-        const int m = (int)(j - row * hx);
-        const int y = (int)(row % a.Ly), z = (int)(row / a.Ly);
-        const int par = (a.c + y + z) & 1;
-        const int x = 2 * m + par;
-        const int64_t rbase = row * a.Lx;
-        const int64_t i = rbase + x;
-        const int xp = x + 1 == a.Lx ? 0 : x + 1, xm = x == 0 ? a.Lx - 1 : x - 1;
-        const int64_t plane = (int64_t)a.Ly * a.Lx;
-        const int64_t ryp = (int64_t)(y + 1 == a.Ly ? 0 : y + 1) * a.Lx + (int64_t)z * plane;
-        const int64_t rym = (int64_t)(y == 0 ? a.Ly - 1 : y - 1) * a.Lx + (int64_t)z * plane;
-        const uint64_t S = w[i];
+        const uint64_t j0 = (uint64_t)t << 6;
+        const uint64_t row0 = j0 / hx;
+        const uint32_t z0 = (uint32_t)(row0 / (uint32_t)a.Ly), y0 = (uint32_t)(row0 - (uint64_t)z0 * (uint32_t)a.Ly);
+        const uint32_t mm = (uint32_t)(j0 - row0 * hx) + (uint32_t)(tid & 63);
+        const uint32_t dr = small_quotient(mm, hx, a.mul_hx);
+        const uint32_t yy = y0 + dr, dz = small_quotient(yy, (uint32_t)a.Ly, a.mul_ly);
+        const uint32_t m = mm - dr * hx, y = yy - dz * (uint32_t)a.Ly, z = z0 + dz;
+        const uint32_t par = ((uint32_t)a.c + y + z) & 1u;
+        const I xb = (I)(2u * m + par) * 8, rb = (I)(row0 + dr) * row_b;
+        const I xpb = xb + 8 == row_b ? 0 : xb + 8, xmb = xb == 0 ? row_b - 8 : xb - 8;
+        const I ryp = y + 1 == (uint32_t)a.Ly ? rb - (plane_b - row_b) : rb + row_b;
+        const I rym = y == 0 ? rb + (plane_b - row_b) : rb - row_b;
+        const uint64_t S = at(w, rb + xb);
         uint64_t n[6] = {0, 0, 0, 0, 0, 0}, jw[6] = {0, 0, 0, 0, 0, 0};
-        n[0] = w[rbase + xp], jw[0] = Jl[i];
-        n[1] = w[rbase + xm], jw[1] = Jl[rbase + xm];
-        n[2] = w[ryp + x], jw[2] = Jl[a.N + i];
-        n[3] = w[rym + x], jw[3] = Jl[a.N + rym + x];
+        n[0] = at(w, rb + xpb), jw[0] = at(J0, rb + xb);
+        n[1] = at(w, rb + xmb), jw[1] = at(J0, rb + xmb);
+        n[2] = at(w, ryp + xb), jw[2] = at(J1, rb + xb);
+        n[3] = at(w, rym + xb), jw[3] = at(J1, rym + xb);
         if (DIMS == 3) {
-            const int64_t rzp = (z + 1 == a.Lz ? 0 : z + 1) * plane + (int64_t)y * a.Lx;
-            const int64_t rzm = (z == 0 ? a.Lz - 1 : z - 1) * plane + (int64_t)y * a.Lx;
-            n[4] = w[rzp + x], jw[4] = Jl[2 * a.N + i];
-            n[5] = w[rzm + x], jw[5] = Jl[2 * a.N + rzm + x];
-        }
-        // wk: bit set <=> J s_j = -1 for that realisation; Metropolis counts
-        // unsatisfied bonds wk ^ S, heat-bath counts wk
-        uint64_t wk[6], xk[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            wk[k] = n[k] ^ jw[k];
-            xk[k] = HB ? wk[k] : (wk[k] ^ S);
-        }
-        uint64_t c0, c1, c2;
-        count_bits<Z>(xk, c0, c1, c2);
-        const uint64_t ge = HB ? 0ull : (DIMS == 3 ? (c2 | (c1 & c0)) : (c2 | c1));
-        uint64_t onehot[7];
-        {
-            const uint64_t n0 = ~c0, n1 = ~c1, n2 = ~c2;
-            onehot[0] = n2 & n1 & n0;
-            onehot[1] = n2 & n1 & c0;
-            onehot[2] = n2 & c1 & n0;
-            onehot[3] = n2 & c1 & c0;
-            onehot[4] = c2 & n1 & n0;
-            onehot[5] = c2 & n1 & c0;
-            onehot[6] = c2 & c1 & n0;
+            const I vol_b = (I)a.Lz * plane_b;
+            const I rzp = z + 1 == (uint32_t)a.Lz ? rb - (vol_b - plane_b) : rb + plane_b;
+            const I rzm = z == 0 ? rb + (vol_b - plane_b) : rb - plane_b;
+            n[4] = at(w, rzp + xb), jw[4] = at(J2, rb + xb);
+            n[5] = at(w, rzm + xb), jw[5] = at(J2, rzm + xb);
         }
         // the site's one draw: top byte from block j / 16 (bit k = bit j mod 16
         // of half-word k), compared once with each class threshold
-        const uint4 B = philox(make_uint4((uint32_t)(j >> 4), rep, a.sweep_lo, a.w3), a.seed_lo, a.seed_hi);
-        const uint32_t top = byte_of(B, (uint32_t)(j & 15));
-        uint64_t acc = ge, pend = 0ull;
+        const uint32_t jl = (uint32_t)j0 + (uint32_t)(tid & 63);
+        const uint4 B =
+            philox(make_uint4((uint32_t)((j0 + (uint32_t)(tid & 63)) >> 4), rep, a.sweep_lo, a.w3), a.seed_lo, a.seed_hi);
+        const uint32_t top = byte_of(B, jl & 15u);
+        uint32_t acc[NC];
+        bool tie = false;
 #pragma unroll
         for (int d = 0; d < NC; ++d) {
-            const uint32_t td = a.top[d];
-            if (top < td) acc |= onehot[d];
-            else if (top == td) pend |= onehot[d];
+            acc[d] = top < a.top[d] ? ~0u : 0u;
+            tie |= top == a.top[d];
         }
-        if (!HB) pend &= ~ge;
-        if (pend) {
-            const uint4 lo = philox(make_uint4((uint32_t)j, rep, a.sweep_lo, a.w3lo), a.seed_lo, a.seed_hi);
-            const uint32_t low = lo.x & 0xFFFFFFu;
+        if (tie) {
+            const uint4 lo = philox(make_uint4(jl, rep, a.sweep_lo, a.w3lo), a.seed_lo, a.seed_hi);
 #pragma unroll
             for (int d = 0; d < NC; ++d)
-                if (top == a.top[d] && low < a.low[d]) acc |= onehot[d] & pend;
+                if (top == a.top[d] && (lo.x & 0xFFFFFFu) < a.low[d]) acc[d] = ~0u;
         }
-        // Metropolis: flip the accepted realisations; heat-bath: s' = +1
-        // (bit clear) where r < T
-        const uint64_t Sn = HB ? ~acc : (S ^ acc);
-        w[i] = Sn;
-        if (MEASURE) {
-            // odd sites: the realisations' bond counts after the update; both
-            // sites of the pair (this odd site and its even partner of the
-            // same row position) for M
-            uint64_t u[6];
+        uint64_t Sn = 0, u[3] = {0, 0, 0}, dn[2] = {0, 0};
 #pragma unroll
-            for (int k = 0; k < 6; ++k) u[k] = Sn ^ wk[k];
-            uint64_t u0, u1, u2;
-            count_bits<Z>(u, u0, u1, u2);
-            const uint64_t pw = par == 1 ? n[1] : n[0];
-            const uint64_t d0 = Sn ^ pw, d1 = Sn & pw;
-            const uint64_t U0 = sg_transpose64(u0, lane), U1 = sg_transpose64(u1, lane),
-                           U2 = sg_transpose64(u2, lane);
-            const uint64_t D0 = sg_transpose64(d0, lane), D1 = sg_transpose64(d1, lane);
-            const int ub = __popcll(U0) + 2 * __popcll(U1) + 4 * __popcll(U2);
-            const int db = __popcll(D0) + 2 * __popcll(D1);
-            e_acc += 2 * ub - 64 * Z;
-            m_acc += 128 - 2 * db;
+        for (int h = 0; h < 2; ++h) {  // realisations 32 h .. 32 h + 31
+            const uint32_t Sh = (uint32_t)(S >> (32 * h));
+            // wk: bit set <=> J s_j = -1; Metropolis counts unsatisfied bonds
+            // S ^ wk, heat-bath counts wk
+            uint32_t wk[6], xk[6];
+#pragma unroll
+            for (int k = 0; k < Z; ++k) {
+                const uint32_t nk = (uint32_t)(n[k] >> (32 * h)), jk = (uint32_t)(jw[k] >> (32 * h));
+                wk[k] = nk ^ jk;
+                xk[k] = HB ? wk[k] : xor3(nk, jk, Sh);
+            }
+            uint32_t c0, c1, c2;
+            count_words<Z>(xk, c0, c1, c2);
+            auto mux = [](uint32_t sel, uint32_t hi, uint32_t lo) {
+                return MCS_BOP3(sel, hi, lo, (MCS_A & MCS_B) | (~MCS_A & MCS_C));
+            };
+            uint32_t t = mux(c0, acc[1], acc[0]), so;
+            if constexpr (HB) {
+                t = mux(c1, mux(c0, acc[3], acc[2]), t);
+                if constexpr (DIMS == 3) t = mux(c2, mux(c1, acc[6], mux(c0, acc[5], acc[4])), t);
+                else t = mux(c2, acc[4], t);
+                so = ~t;  // s' = +1 (bit clear) where r < T
+            } else {
+                // a >= z/2 gives dE <= 0: flipped in any case
+                uint32_t ge = c1 | c2;
+                if constexpr (DIMS == 3) {
+                    t = mux(c1, acc[2], t);
+                    ge = MCS_BOP3(c2, c1, c0, MCS_A | (MCS_B & MCS_C));
+                }
+                so = MCS_BOP3(Sh, ge, t, MCS_A ^ (MCS_B | MCS_C));
+            }
+            Sn |= (uint64_t)so << (32 * h);
+            if (MEASURE) {
+                // odd sites: the realisations' bond counts after the update; both
+                // sites of the pair (this odd site and its even partner of the
+                // same row position) for M
+                uint32_t uk[6], v0, v1, v2;
+#pragma unroll
+                for (int k = 0; k < Z; ++k) uk[k] = so ^ wk[k];
+                count_words<Z>(uk, v0, v1, v2);
+                const uint32_t pw = (uint32_t)((par ? n[1] : n[0]) >> (32 * h));
+                u[0] |= (uint64_t)v0 << (32 * h);
+                u[1] |= (uint64_t)v1 << (32 * h);
+                u[2] |= (uint64_t)v2 << (32 * h);
+                dn[0] |= (uint64_t)(so ^ pw) << (32 * h);
+                dn[1] |= (uint64_t)(so & pw) << (32 * h);
+            }
+        }
+        *(uint64_t *)(w + (rb + xb)) = Sn;
+        if (MEASURE) {
+            cu.add(u);
+            cd.add(dn);
+            ++done;
+            if (++since == kSgFlush) flush();
         }
     }
     if (MEASURE) {
-        atomicAdd((unsigned long long *)&red[0][lane], (unsigned long long)e_acc);
-        atomicAdd((unsigned long long *)&red[1][lane], (unsigned long long)m_acc);
+        if (since) flush();
+        // E: 2 (unsatisfied) - z per odd site; M: 2 - 2 (down) per pair
+        red[0][wave][lb.label] = 2 * u_acc - 64 * Z * (int)done;
+        red[1][wave][lb.label] = 128 * (int)done - 2 * d_acc;
         __syncthreads();
         if (tid < 128) {
             const int q = tid >> 6, b = tid & 63;
-            atomicAdd((unsigned long long *)&a.EM[2 * (64 * (int64_t)l + b) + q], (unsigned long long)red[q][b]);
+            const long long v = (long long)red[q][0][b] + red[q][1][b] + red[q][2][b] + red[q][3][b];
+            atomicAdd((unsigned long long *)&a.EM[2 * (64 * (int64_t)l + b) + q], (unsigned long long)v);
         }
     }
 }
@@ -244,16 +254,19 @@ hipError_t launch_couplings_msc64(const Geom &g, uint64_t *J, uint64_t seed, uin
 
 bool sg_msc_supported(const Geom &g) { return (g.dims == 2 || g.dims == 3) && ((g.N >> 1) % 64) == 0; }
 
-template <int D, bool HB>
-static hipError_t launch_sg_t(const SgMscArgs &a, int count, hipStream_t s)
+template <int D, bool HB, class I>
+static hipError_t launch_sg_t(const SgMscArgs &a, hipStream_t s)
 {
-    const int64_t tasks = (a.N >> 1) >> 6;
-    int64_t blocks = (tasks + 3) / 4;
-    if (blocks > 1024) blocks = 1024;
-    dim3 grid((unsigned)blocks, (unsigned)count);
-    if (a.EM) hipLaunchKernelGGL((k_sg_msc<D, true, HB>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_sg_msc<D, false, HB>), grid, dim3(256), 0, s, a);
+    const dim3 grid((a.total + 7u) & ~7u);
+    if (a.EM) hipLaunchKernelGGL((k_sg_msc<D, true, HB, I>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_sg_msc<D, false, HB, I>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
+}
+
+template <int D, bool HB>
+static hipError_t launch_sg_i(const SgMscArgs &a, hipStream_t s)
+{
+    return a.N < (int64_t)1 << 29 ? launch_sg_t<D, HB, uint32_t>(a, s) : launch_sg_t<D, HB, uint64_t>(a, s);
 }
 
 hipError_t launch_sg_msc_phase(const Geom &g, int rule, const SweepTables &tab, uint64_t *words, const uint64_t *J,
@@ -286,8 +299,16 @@ hipError_t launch_sg_msc_phase(const Geom &g, int rule, const SweepTables &tab, 
         a.low[cl] = th.low;
     }
     a.EM = phase == 1 ? EM : nullptr;
-    if (g.dims == 2) return rule ? launch_sg_t<2, true>(a, g.count, s) : launch_sg_t<2, false>(a, g.count, s);
-    return rule ? launch_sg_t<3, true>(a, g.count, s) : launch_sg_t<3, false>(a, g.count, s);
+    // as many workgroups as are resident at once, in equal parts of a lattice
+    a.tasks = (uint32_t)(a.N >> 7);
+    const int64_t resident = a.EM ? kSgBlocksEM : kSgBlocks;
+    a.parts = (uint32_t)std::min<int64_t>((a.tasks + 3) / 4, std::max<int64_t>(1, (resident + g.count - 1) / g.count));
+    a.total = a.parts * (uint32_t)g.count;
+    const uint32_t hx = (uint32_t)g.Lx >> 1;
+    a.mul_hx = (uint32_t)((((uint64_t)1 << 32) + hx - 1) / hx);
+    a.mul_ly = (uint32_t)((((uint64_t)1 << 32) + (uint32_t)g.Ly - 1) / (uint32_t)g.Ly);
+    if (g.dims == 2) return rule ? launch_sg_i<2, true>(a, s) : launch_sg_i<2, false>(a, s);
+    return rule ? launch_sg_i<3, true>(a, s) : launch_sg_i<3, false>(a, s);
 }
 
 }  // namespace mcs

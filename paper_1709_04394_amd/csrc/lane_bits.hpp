@@ -112,6 +112,27 @@ __device__ __forceinline__ int column_count(uint64_t v, const LaneBits &b)
     return __builtin_popcount(exchange16(p0, b)) + __builtin_popcount(exchange16(p1, b));
 }
 
+// Bit-sliced count (c0, c1, c2) of the set bits among Z words.
+template <int Z>
+__device__ __forceinline__ void count_words(const uint32_t (&x)[6], uint32_t &c0, uint32_t &c1, uint32_t &c2)
+{
+    const uint32_t s1 = xor3(x[0], x[1], x[2]);
+    const uint32_t k1 = MCS_BOP3(x[0], x[1], x[2], (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
+    if constexpr (Z == 6) {
+        const uint32_t s2 = xor3(x[3], x[4], x[5]);
+        const uint32_t k2 = MCS_BOP3(x[3], x[4], x[5], (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
+        const uint32_t kk = s1 & s2;
+        c0 = s1 ^ s2;
+        c1 = xor3(k1, k2, kk);
+        c2 = MCS_BOP3(k1, k2, kk, (MCS_A & MCS_B) | (MCS_A & MCS_C) | (MCS_B & MCS_C));
+    } else {
+        const uint32_t kk = s1 & x[3];
+        c0 = s1 ^ x[3];
+        c1 = k1 ^ kk;
+        c2 = k1 & kk;
+    }
+}
+
 // Bit-sliced counters of 64 replicas in a lane, P planes: v planes added.
 template <int P>
 struct BitCounter {
@@ -140,12 +161,14 @@ struct BitCounter {
             }
         }
     }
-    // sum over the wave's lanes, for the replica of this lane's label; cleared
-    __device__ __forceinline__ int flush(const LaneBits &b)
+    // sum over the wave's lanes of the lowest `used` planes (the rest are zero),
+    // for the replica of this lane's label; cleared
+    __device__ __forceinline__ int flush(const LaneBits &b, int used = P)
     {
         int s = 0;
 #pragma unroll
-        for (int i = 0; i < P; ++i) s += column_count(n[i], b) << i;
+        for (int i = 0; i < P; ++i)
+            if (i < used) s += column_count(n[i], b) << i;
         clear();
         return s;
     }
