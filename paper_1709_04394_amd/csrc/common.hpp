@@ -191,6 +191,7 @@ struct SweepCall {
 
 // Launchers (defined in the kernel files).  They only enqueue work.
 hipError_t launch_fill_i64(int64_t *p, int64_t n, int64_t value, hipStream_t s);
+hipError_t launch_fill_rows(int64_t *p, int64_t rows, int64_t stride, int64_t n, hipStream_t s);
 hipError_t launch_init_int8(const Geom &g, int8_t *spins, int start, uint64_t seed, uint32_t replica0,
                             hipStream_t s);
 hipError_t launch_init_msc64(const Geom &g, uint64_t *words, int start, uint64_t seed, uint32_t replica0,
@@ -202,6 +203,10 @@ hipError_t launch_measure_int8(const Geom &g, const int8_t *spins, const int8_t 
 hipError_t launch_measure_msc64(const Geom &g, const uint64_t *words, const int8_t *J, int64_t *EM,
                                 hipStream_t s);
 
+// in-place half-sweep of int8 rows of 32 sites or more, with the sweep's (E, M)
+// in the odd one (k_half.hip)
+bool half_supported(const Geom &g);
+hipError_t launch_half(const SweepCall &c, int8_t *spins, uint64_t sweep, int phase, int64_t *EM, hipStream_t s);
 // generic in-place half-sweep, any even geometry, int8
 hipError_t launch_phase_int8(const SweepCall &c, int8_t *spins, uint64_t sweep, int phase, hipStream_t s);
 // generic in-place half-sweep, msc64

@@ -21,6 +21,24 @@ hipError_t launch_fill_i64(int64_t *p, int64_t n, int64_t value, hipStream_t s)
     return hipGetLastError();
 }
 
+// Zero the first n of every stride words, rows times (the measurements of one
+// lattice of several).
+__global__ void k_fill_rows(int64_t *p, int64_t rows, int64_t stride, int64_t n)
+{
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < rows * n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t r = i / n;
+        p[r * stride + (i - r * n)] = 0;
+    }
+}
+
+hipError_t launch_fill_rows(int64_t *p, int64_t rows, int64_t stride, int64_t n, hipStream_t s)
+{
+    if (rows * n <= 0) return hipSuccess;
+    const int64_t blocks = std::min<int64_t>((rows * n + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_fill_rows, dim3((unsigned)blocks), dim3(256), 0, s, p, rows, stride, n);
+    return hipGetLastError();
+}
+
 // ----------------------------------------------------------------------------
 // Hot start: site i of replica r is +1 iff byte (i mod 16) of
 // Philox(i/16, r, 0, TAG_INIT) < 128.  One thread per 16 consecutive sites.

@@ -344,6 +344,13 @@ int run_sweeps(mc_ctx *ctx, const SweepCall &c, int layout, void *spins, uint64_
     default:
         break;
     }
+    if (layout == MC_INT8 && half_supported(c.g)) {
+        hipError_t e = EM ? launch_fill_rows(EM, nsweeps, em_stride, 2 * (int64_t)c.g.count, s) : hipSuccess;
+        for (int t = 0; t < nsweeps && e == hipSuccess; ++t)
+            for (int phase = 0; phase < 2 && e == hipSuccess; ++phase)
+                e = launch_half(c, (int8_t *)spins, sweep0 + (uint64_t)t, phase, EM ? EM + t * em_stride : nullptr, s);
+        return device_check(ctx, e, "mc_sweep half-sweep launch");
+    }
     for (int t = 0; t < nsweeps; ++t) {
         const uint64_t sweep = sweep0 + (uint64_t)t;
         hipError_t e = hipSuccess;
