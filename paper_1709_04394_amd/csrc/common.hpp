@@ -112,49 +112,9 @@ __host__ __device__ __forceinline__ Thr split_thr(uint64_t T)
     return t;
 }
 
-// Bit masks of a threshold's top byte: tk[k] = all ones iff bit k of top is
-// set (wave-uniform, lives in scalar registers); top = 256 (T = 2^32) is the
-// "always" case.
-struct TopMask {
-    uint32_t tk[8];
-    bool always;
-};
-
-__device__ __forceinline__ TopMask top_mask(uint32_t top)
-{
-    TopMask m;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) m.tk[k] = ((top >> k) & 1u) ? ~0u : 0u;
-    m.always = top >= 256u;
-    return m;
-}
-
-// lt = (X < top), eq = (X == top) for 32 sites at once, X given as bit-planes
-// X[0] (LSB) .. X[7].  lt is the borrow out of X - top, propagated from the
-// least significant plane: borrow' = maj(~X_k, top_k, borrow); one bitop3 per
-// plane for each of lt and eq.
-__device__ __forceinline__ void compare_planes(const uint32_t (&X)[8], const TopMask &t, uint32_t &lt, uint32_t &eq)
-{
-    uint32_t b = 0u, e = ~0u;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        b = MCS_BOP3(X[k], t.tk[k], b, (~MCS_A & MCS_B) | (~MCS_A & MCS_C) | (MCS_B & MCS_C));
-        e = MCS_BOP3(e, X[k], t.tk[k], MCS_A & ~(MCS_B ^ MCS_C));
-    }
-    lt = t.always ? ~0u : b;
-    eq = t.always ? 0u : e;
-}
-
 // ---------------------------------------------------------------------------
 // wave64 reductions
 __device__ __forceinline__ long long wave_sum(long long v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    return v;
-}
-
-__device__ __forceinline__ int wave_sum_i(int v)
 {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
@@ -207,6 +167,10 @@ hipError_t launch_measure_msc64(const Geom &g, const uint64_t *words, const int8
 // in the odd one (k_half.hip)
 bool half_supported(const Geom &g);
 hipError_t launch_half(const SweepCall &c, int8_t *spins, uint64_t sweep, int phase, int64_t *EM, hipStream_t s);
+// every sweep of a call with each int8 lattice whole in a workgroup (k_whole.hip)
+bool whole_supported(const Geom &g);
+hipError_t launch_whole(const SweepCall &c, int8_t *spins, uint64_t sweep0, int nsweeps, int64_t *EM,
+                        int64_t em_stride, hipStream_t s);
 // generic in-place half-sweep, any even geometry, int8
 hipError_t launch_phase_int8(const SweepCall &c, int8_t *spins, uint64_t sweep, int phase, hipStream_t s);
 // generic in-place half-sweep, msc64

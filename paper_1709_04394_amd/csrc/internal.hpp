@@ -134,17 +134,6 @@ hipError_t launch_tile3d(const SweepCall &c, const void *src, int in_packed, voi
 size_t tile3d_slot_bytes(const Geom &g);
 hipError_t launch_pack_couplings(const Geom &g, const int8_t *J, uint32_t *Jp, hipStream_t s);
 
-// int8 lattices with 32-site rows, bit-packed whole in one workgroup's LDS
-// (k_small_bits.hip)
-bool small_bits_supported(const SweepCall &c, int layout);
-hipError_t launch_small_bits(const SweepCall &c, int8_t *spins, uint64_t sweep0, int nsweeps, int64_t *EM,
-                             int64_t em_stride, hipStream_t s);
-
-// small int8 lattices held whole in one workgroup's LDS (k_small.hip)
-bool small_supported(const SweepCall &c, int layout);
-hipError_t launch_small(const SweepCall &c, int8_t *spins, uint64_t sweep0, int nsweeps, int64_t *EM,
-                        int64_t em_stride, hipStream_t s);
-
 // 64-lane multi-spin-coded half-sweep with fused per-lane E, M (k_msc.hip)
 bool msc_fast_supported(const SweepCall &c, int layout);
 hipError_t launch_msc_phase(const SweepCall &c, uint64_t *words, uint64_t sweep, int phase, int64_t *EM,

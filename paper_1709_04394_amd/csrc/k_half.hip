@@ -28,6 +28,7 @@
 #include "internal.hpp"
 #include "lane_bits.hpp"
 #include "metro2d.hpp"
+#include "spin_bytes.hpp"
 
 namespace mcs {
 
@@ -54,41 +55,6 @@ struct HalfArgs {
     uint32_t low[8];
     int64_t *EM;          // this sweep's [count][2], or nullptr
 };
-
-// n / d, n < 2^28: the product with floor((2^32 - 1) / d) is at most one short
-__device__ __forceinline__ uint32_t quotient28(uint32_t n, uint32_t d, uint32_t mul)
-{
-    const uint32_t q = __umulhi(n, mul);
-    return n - q * d >= d ? q + 1u : q;
-}
-
-struct Row32 {
-    uint32_t d[8];
-};
-
-__device__ __forceinline__ Row32 load_row32(const int8_t *p, uint32_t off)
-{
-    Row32 r;
-    __builtin_memcpy(&r, p + off, 32);
-    return r;
-}
-
-// The 16 bytes of one parity (sel 0x06040200 even, 0x07050301 odd).
-__device__ __forceinline__ uint4 pick16(const Row32 &r, uint32_t sel)
-{
-    return make_uint4(__builtin_amdgcn_perm(r.d[1], r.d[0], sel), __builtin_amdgcn_perm(r.d[3], r.d[2], sel),
-                      __builtin_amdgcn_perm(r.d[5], r.d[4], sel), __builtin_amdgcn_perm(r.d[7], r.d[6], sel));
-}
-
-// Sign bits of 16 bytes +-1: sum of -2^i s_i over eight of them is 2 B - 255 for
-// their bits B.
-__device__ __forceinline__ uint32_t sign_bits16(const uint4 &v)
-{
-    const int w0 = (int)0xF8FCFEFFu, w1 = (int)0x80C0E0F0u;  // -1, -2, -4, -8; -16, -32, -64, -128
-    const int lo = __builtin_amdgcn_sdot4((int)v.y, w1, __builtin_amdgcn_sdot4((int)v.x, w0, 255, false), false);
-    const int hi = __builtin_amdgcn_sdot4((int)v.w, w1, __builtin_amdgcn_sdot4((int)v.z, w0, 255, false), false);
-    return (((uint32_t)hi << 8) | (uint32_t)lo) >> 1;
-}
 
 template <int DIMS, bool HB, bool HASJ, bool MEASURE>
 __global__ __launch_bounds__(kHalfThreads) void k_half(HalfArgs a)
@@ -229,7 +195,7 @@ __global__ __launch_bounds__(kHalfThreads) void k_half(HalfArgs a)
             Row32 out;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                q[i] ^= ((((F >> (4 * i)) & 15u) * 0x00204081u) & 0x01010101u) * 0xFEu;
+                q[i] ^= spread4((F >> (4 * i)) & 15u) * 0xFEu;
                 out.d[2 * i] = __builtin_amdgcn_perm(o[i], q[i], s0);
                 out.d[2 * i + 1] = __builtin_amdgcn_perm(o[i], q[i], s1);
             }

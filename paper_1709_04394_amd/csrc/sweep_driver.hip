@@ -261,17 +261,32 @@ static int run_fused(mc_ctx *ctx, const SweepCall &c, const TilePlan &p, int8_t 
     return device_check(ctx, e, "mc_sweep fused launch");
 }
 
+// Small int8 lattices: rows of 32 sites whose bits (and couplings) fit 128 KB,
+// and those whose bytes, couplings and random blocks fit 150 KB.
+static bool small_bits_call(const SweepCall &c, int layout)
+{
+    const int64_t rows = c.g.N / 32;
+    return layout == MC_INT8 && !c.per_lattice && c.g.Lx == 32 &&
+           4 * rows * (2 + (c.J ? 2 * c.g.dims : 0)) <= 128 * 1024;
+}
+
+static bool small_call(const SweepCall &c, int layout)
+{
+    auto pad16 = [](int64_t n) { return (n + 15) & ~(int64_t)15; };
+    return layout == MC_INT8 && !c.per_lattice && c.g.N <= (1 << 20) &&
+           pad16(c.g.N) + (c.J ? pad16(c.g.dims * c.g.N) : 0) + pad16(c.g.N / 2) <= 150 * 1024;
+}
+
 // Which kernel family runs a call, in order of preference: the fused tiles
-// (given a large enough workspace and a usable plan), the bit-packed whole
-// lattice, the int8 whole lattice, the multi-spin-coded kernel, the generic
-// half-sweeps.
+// (given a large enough workspace and a usable plan), the whole-lattice kernel,
+// the multi-spin-coded kernel, the half-sweeps.
 static int sweep_path(mc_ctx *ctx, const SweepCall &c, int layout, bool have_ws, size_t ws_bytes)
 {
     if ((tile2d_supported(c, layout) || tile3d_supported(c, layout)) && have_ws &&
         ws_bytes >= fused_workspace_bytes(c.g, layout) && plan_ok(c.g, plan_for(ctx, c.g)))
         return c.g.dims == 2 ? MC_PATH_FUSED_2D : MC_PATH_FUSED_3D;
-    if (small_bits_supported(c, layout)) return MC_PATH_SMALL_BITS;
-    if (small_supported(c, layout)) return MC_PATH_SMALL;
+    if (small_bits_call(c, layout)) return MC_PATH_SMALL_BITS;
+    if (small_call(c, layout)) return MC_PATH_SMALL;
     if (msc_fast_supported(c, layout)) return MC_PATH_MSC64;
     return MC_PATH_GENERIC;
 }
@@ -301,6 +316,17 @@ static int betas_path(mc_ctx *ctx, const SweepCall &c, bool have_ws, size_t ws_b
     return sweep_path(ctx, c1, MC_INT8, false, 0);
 }
 
+// Of the fused tiles' lattices without a set or tuned plan, those of 2^15 sites
+// or fewer run whole in one workgroup: a launch per call instead of one per few
+// sweeps.  Tiles (whole), us per call of 10 sweeps with E, M, host time
+// included: 64^2 46 (32), 4096 of them 140 (56), 128^2 47 (34), 2048 of them 171
+// (93), 256 x 128 51 (40), 256^2 50 (56); 64 x 16 x 16 heat-bath 64 (38), 64 x
+// 32 x 32 64 (64).
+static bool whole_instead_of_tiles(mc_ctx *ctx, const SweepCall &c)
+{
+    return !c.per_lattice && c.g.N <= (1 << 15) && !ctx->tile_plans.count(plan_key(c.g));
+}
+
 int run_sweeps_betas(mc_ctx *ctx, const SweepCall &c, int8_t *spins, uint64_t sweep0, int nsweeps, int64_t *EM,
                      int64_t em_stride, void *ws, size_t ws_bytes, hipStream_t s)
 {
@@ -326,13 +352,15 @@ int run_sweeps(mc_ctx *ctx, const SweepCall &c, int layout, void *spins, uint64_
     switch (path) {
     case MC_PATH_FUSED_2D:
     case MC_PATH_FUSED_3D:
-        return run_fused(ctx, c, call_plan(ctx, c.g, nsweeps), (int8_t *)spins, (char *)ws, sweep0, nsweeps, EM, em_stride, s);
+        if (!whole_instead_of_tiles(ctx, c))
+            return run_fused(ctx, c, call_plan(ctx, c.g, nsweeps), (int8_t *)spins, (char *)ws, sweep0, nsweeps, EM,
+                             em_stride, s);
+        [[fallthrough]];
     case MC_PATH_SMALL_BITS:
-        return device_check(ctx, launch_small_bits(c, (int8_t *)spins, sweep0, nsweeps, EM, em_stride, s),
-                            "mc_sweep small bit-packed lattice launch");
     case MC_PATH_SMALL:
-        return device_check(ctx, launch_small(c, (int8_t *)spins, sweep0, nsweeps, EM, em_stride, s),
-                            "mc_sweep small-lattice launch");
+        if (!whole_supported(c.g)) break;
+        return device_check(ctx, launch_whole(c, (int8_t *)spins, sweep0, nsweeps, EM, em_stride, s),
+                            "mc_sweep whole-lattice launch");
     case MC_PATH_MSC64: {
         hipError_t e = EM ? launch_fill_i64(EM, (int64_t)nsweeps * em_stride, 0, s) : hipSuccess;
         for (int t = 0; t < nsweeps && e == hipSuccess; ++t)
