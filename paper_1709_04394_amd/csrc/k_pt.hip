@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void k_pt_sweep(PtSweepArgs a)
     la.ng_max = a.G;
     la.ng = min(a.G, a.count - s0);
     la.rep0 = (uint32_t)s0;  // lattice l = set s, replica r is replica id s n_temps + r = l
-    la.sweep0 = a.sweep0;
+    la.sweep0 = ((a.xtab[0] >> kPtZeroBits) + a.round) * (uint64_t)a.theta;
     la.theta = a.theta;
     la.seed_lo = a.seed_lo;
     la.seed_hi = a.seed_hi;
@@ -63,21 +63,25 @@ __global__ __launch_bounds__(1024) void k_pt_exchange(PtExchangeArgs a)
     int32_t *tof = a.temp_of + (int64_t)s * nT;
     int32_t *rat = a.replica_at + (int64_t)s * nT;
     const int32_t *Es = a.E + (int64_t)s * nT;
+    const uint64_t round = (a.xtab[0] >> kPtZeroBits) + a.round;
     if (i < nT) {
         rep[i] = rat[i];
         if (a.E_at) a.E_at[(int64_t)s * nT + i] = Es[rep[i]];
     }
     __syncthreads();
-    if (i + 1 < nT && (uint32_t)(i & 1) == (uint32_t)(a.round & 1u)) {
+    if (i + 1 < nT && (uint32_t)(i & 1) == (uint32_t)(round & 1u)) {
         const int32_t ra = rep[i], rb = rep[i + 1];
         const int32_t d = Es[ra] - Es[rb];
         // beta_i < beta_{i+1}: the exponent (beta_i - beta_{i+1}) d is >= 0 iff
         // d <= 0; energies of the even torus differ by multiples of 4
         bool acc = d <= 0;
         if (!acc) {
-            const uint64_t T = a.xtab[(int64_t)i * (a.mmax + 1) + (d >> 2)];
-            const uint4 r = philox(make_uint4((uint32_t)i >> 2, (uint32_t)s, (uint32_t)a.round,
-                                              ctr_w3(kTagExchange, 0, a.round)),
+            // beyond the row the threshold is 1, then 0
+            const uint64_t *x = a.xtab + (int64_t)i * a.row;
+            const int m = d >> 2;
+            const uint64_t T = m < a.row ? x[m] : m < (int)(x[0] & ((1u << kPtZeroBits) - 1u)) ? 1u : 0u;
+            const uint4 r = philox(make_uint4((uint32_t)i >> 2, (uint32_t)s, (uint32_t)round,
+                                              ctr_w3(kTagExchange, 0, round)),
                                    a.seed_lo, a.seed_hi);
             const uint32_t w[4] = {r.x, r.y, r.z, r.w};
             acc = (uint64_t)w[i & 3] < T;

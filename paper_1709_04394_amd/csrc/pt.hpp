@@ -6,6 +6,7 @@
 namespace mcs {
 
 constexpr int kPtMaxTemps = 1024;  // temperatures per set: one exchange workgroup
+constexpr int kPtZeroBits = 24;    // low bits of a pair's entry 0: first m of threshold 0; above: first round
 
 struct PtSweepArgs {
     int8_t *spins;              // [count][L^2], lattice l = set s, replica r at l = s n_temps + r
@@ -14,7 +15,8 @@ struct PtSweepArgs {
     const int32_t *temp_of;     // [count] temperature index held by lattice l
     const Thr *thr;             // [n_temps][2] Metropolis thresholds dE = 4, 8
     int32_t *E;                 // [count] energy after the sweeps
-    uint64_t sweep0;            // round theta
+    const uint64_t *xtab;       // entry 0 holds the call's first round
+    uint32_t round;             // within the call: the sweeps start at (first + round) theta
     int theta;
     uint32_t seed_lo, seed_hi;
 };
@@ -23,11 +25,11 @@ struct PtExchangeArgs {
     int n_temps;
     int32_t *temp_of, *replica_at;  // [n_sets][n_temps]
     const int32_t *E;               // [n_sets][n_temps] by replica
-    const uint64_t *xtab;           // [n_temps - 1][mmax + 1]: ceil(exp((beta_i - beta_{i+1}) 4m) 2^32)
-    int mmax;                       // largest (E_a - E_b) / 4
+    const uint64_t *xtab;           // [n_temps - 1][row]: ceil(exp((beta_i - beta_{i+1}) 4m) 2^32)
+    int row;
     int64_t *accepted;              // [n_sets][n_temps - 1]
     int64_t *E_at;                  // [n_sets][n_temps] of this round, or nullptr
-    uint64_t round;
+    uint32_t round;                 // within the call
     uint32_t seed_lo, seed_hi;
 };
 

@@ -8,6 +8,7 @@
 // mc_sweep_betas per-sweep E), so no extra pass over the lattices is needed.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "internal.hpp"
@@ -99,26 +100,53 @@ namespace {
 
 size_t pt_align(size_t b) { return (b + 255) & ~(size_t)255; }
 
+// One copy to the device before the rounds (thr .. accepted) and two back after
+// them (temp_of .. accepted, E_at).  E_at and E follow at `rows`.
 struct PtLayout {
-    size_t thr = 0, xtab = 0, temp_of = 0, replica_at = 0, E = 0, accepted = 0, E_at = 0, total = 0;
+    size_t thr = 0, xtab = 0, temp_of = 0, replica_at = 0, accepted = 0, E_at = 0, E = 0, total = 0;
 };
 
 int64_t pt_mmax(int L) { return (int64_t)L * L; }  // (E_a - E_b) / 4 <= 4N / 4
 
-PtLayout pt_layout(const mc_pt_args *a)
+// With exchange tables of `row` entries per pair (at most pt_mmax + 1, the
+// size that the workspace is asked for).
+PtLayout pt_layout(const mc_pt_args *a, int64_t row)
 {
     PtLayout l;
     const size_t nT = (size_t)a->n_temps, count = nT * (size_t)a->n_sets;
     size_t off = 0;
     l.thr = off, off += pt_align(nT * 2 * sizeof(Thr));
-    l.xtab = off, off += pt_align((nT - 1) * (size_t)(pt_mmax(a->L) + 1) * 8);
+    l.xtab = off, off += pt_align((nT - 1) * (size_t)row * 8);
     l.temp_of = off, off += pt_align(count * 4);
     l.replica_at = off, off += pt_align(count * 4);
-    l.E = off, off += pt_align(count * 4);
     l.accepted = off, off += pt_align((size_t)a->n_sets * (nT - 1) * 8);
     l.E_at = off, off += pt_align((size_t)a->rounds * count * 8);
+    l.E = off, off += pt_align(count * 4);
     l.total = off;
     return l;
+}
+
+// The exchange threshold ceil(exp(x) 2^32), x = (beta_i - beta_{i+1}) 4m < 0, is
+// 1 from x = -22.5 (exp(x) 2^32 < 0.73) until exp(x) is 0: the entries up to
+// `cut`, and the first m whose threshold is 0.
+struct PtPair {
+    int64_t cut, zero;
+};
+
+PtPair pt_pair(double b0, double b1, int64_t mmax)
+{
+    const double d = b0 - b1;
+    auto first_below = [&](double x) {  // first m with d 4m < x, at most mmax + 1
+        const double m = std::floor(x / (4.0 * d));
+        int64_t k = m < 0.0 ? 0 : m > (double)mmax ? mmax + 1 : (int64_t)m;
+        while (k <= mmax && !(d * (double)(4 * k) < x)) ++k;
+        return k;
+    };
+    PtPair p;
+    p.cut = std::min(first_below(-22.5), mmax);
+    p.zero = first_below(-744.0);
+    while (p.zero <= mmax && std::exp(d * (double)(4 * p.zero)) != 0.0) ++p.zero;
+    return p;
 }
 
 int check_pt(mc_ctx *ctx, const mc_pt_args *a)
@@ -151,7 +179,7 @@ extern "C" {
 size_t mc_pt_workspace_bytes(const mc_pt_args *args)
 {
     if (check_pt(nullptr, args) != MC_OK) return 0;
-    return pt_layout(args).total;
+    return pt_layout(args, pt_mmax(args->L) + 1).total;
 }
 
 int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of, int32_t *replica_at,
@@ -172,37 +200,44 @@ int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of,
             seen[(size_t)r] = 1;
         }
     }
-    const PtLayout lay = pt_layout(a);
-    if (!ws || ws_bytes < lay.total) return fail(ctx, MC_E_WORKSPACE, "workspace needs %zu bytes", lay.total);
+    const int64_t mmax = pt_mmax(a->L);
+    const size_t need = pt_layout(a, mmax + 1).total;
+    if (!ws || ws_bytes < need) return fail(ctx, MC_E_WORKSPACE, "workspace needs %zu bytes", need);
     if ((rc = set_device(ctx))) return rc;
     hipStream_t s = (hipStream_t)stream;
     char *w = (char *)ws;
 
     // host FP64 tables: Metropolis thresholds per temperature, exchange
     // thresholds per pair and energy difference 4m (m = 1 .. N), both
-    // ceil(p 2^32) with libm exp, exactly as mc_pt_exchange computes them
-    std::vector<Thr> thr((size_t)nT * 2);
+    // ceil(p 2^32) with libm exp, exactly as mc_pt_exchange computes them.
+    // Entry 0 of a pair's row (no exchange asks for it) is the call's first
+    // round and the m from which the threshold is 0.
+    std::vector<PtPair> pair((size_t)nT - 1);
+    int64_t row = 1;
+    for (int i = 0; i + 1 < nT; ++i) {
+        pair[(size_t)i] = pt_pair(a->beta[i], a->beta[i + 1], mmax);
+        row = std::max(row, pair[(size_t)i].cut + 1);
+    }
+    const PtLayout lay = pt_layout(a, row);
+    std::vector<char> up(lay.E_at);
+    Thr *thr = (Thr *)(up.data() + lay.thr);
     for (int i = 0; i < nT; ++i) {
         const SweepTables t = build_tables(a->beta[i]);
-        thr[2 * (size_t)i] = t.met[1];
-        thr[2 * (size_t)i + 1] = t.met[2];
+        thr[2 * i] = t.met[1];
+        thr[2 * i + 1] = t.met[2];
     }
-    const int64_t mmax = pt_mmax(a->L);
-    std::vector<uint64_t> xt((size_t)(nT - 1) * (size_t)(mmax + 1), 0);
-    for (int i = 0; i + 1 < nT; ++i)
-        for (int64_t m = 1; m <= mmax; ++m) {
-            const double x = (a->beta[i] - a->beta[i + 1]) * (double)(4 * m);
-            xt[(size_t)i * (mmax + 1) + (size_t)m] = (uint64_t)std::ceil(std::ldexp(std::exp(x), 32));
-        }
-    hipError_t e = hipMemcpyAsync(w + lay.thr, thr.data(), thr.size() * sizeof(Thr), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(w + lay.xtab, xt.data(), xt.size() * 8, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(w + lay.temp_of, temp_of, (size_t)count * 4, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(w + lay.replica_at, replica_at, (size_t)count * 4, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(w + lay.accepted, accepted, (size_t)nS * (nT - 1) * 8, hipMemcpyHostToDevice, s);
+    for (int i = 0; i + 1 < nT; ++i) {
+        uint64_t *x = (uint64_t *)(up.data() + lay.xtab) + (size_t)i * (size_t)row;
+        const PtPair p = pair[(size_t)i];
+        x[0] = a->round0 << kPtZeroBits | (uint64_t)p.zero;
+        for (int64_t m = 1; m <= p.cut; ++m)
+            x[m] = (uint64_t)std::ceil(std::ldexp(std::exp((a->beta[i] - a->beta[i + 1]) * (double)(4 * m)), 32));
+        for (int64_t m = p.cut + 1; m < row; ++m) x[m] = m < p.zero ? 1u : 0u;
+    }
+    std::memcpy(up.data() + lay.temp_of, temp_of, (size_t)count * 4);
+    std::memcpy(up.data() + lay.replica_at, replica_at, (size_t)count * 4);
+    std::memcpy(up.data() + lay.accepted, accepted, (size_t)nS * (nT - 1) * 8);
+    hipError_t e = hipMemcpyAsync(w, up.data(), up.size(), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return device_check(ctx, e, "mc_pt_run setup");
 
     PtSweepArgs sw{};
@@ -221,19 +256,20 @@ int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of,
     ex.temp_of = (int32_t *)(w + lay.temp_of);
     ex.replica_at = (int32_t *)(w + lay.replica_at);
     ex.E = sw.E;
-    ex.xtab = (const uint64_t *)(w + lay.xtab);
-    ex.mmax = (int)mmax;
+    ex.xtab = sw.xtab = (const uint64_t *)(w + lay.xtab);
+    ex.row = (int)row;
     ex.accepted = (int64_t *)(w + lay.accepted);
     ex.seed_lo = sw.seed_lo;
     ex.seed_hi = sw.seed_hi;
 
-    // every round as one graph, kept in the context for a call with the same
-    // inputs (arguments, schedule, buffers, launch shape)
+    // every round as one graph, kept in the context for calls that differ only
+    // in the first round and the buffers' contents (the kernels add the first
+    // round to their own number): a run in several calls captures once
     std::vector<unsigned char> key;
     auto put = [&key](const void *p, size_t n) {
         key.insert(key.end(), (const unsigned char *)p, (const unsigned char *)p + n);
     };
-    const int64_t fields[8] = {ctx->device, a->L, nT, nS, a->theta, (int64_t)a->seed, (int64_t)a->round0, a->rounds};
+    const int64_t fields[8] = {ctx->device, a->L, nT, nS, a->theta, (int64_t)a->seed, row, a->rounds};
     put(fields, sizeof fields);
     put(a->beta, sizeof(double) * (size_t)nT);
     put(&spins, sizeof spins);
@@ -250,9 +286,7 @@ int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of,
         hipGraphExec_t exec = nullptr;
         e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
         for (int r = 0; r < a->rounds && e == hipSuccess; ++r) {
-            const uint64_t round = a->round0 + (uint64_t)r;
-            sw.sweep0 = round * (uint64_t)a->theta;
-            ex.round = round;
+            sw.round = ex.round = (uint32_t)r;
             ex.E_at = E_at ? (int64_t *)(w + lay.E_at) + (size_t)r * count : nullptr;
             e = launch_pt_round(sw, ex, nS, cap);
         }
@@ -269,11 +303,7 @@ int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of,
     }
     if (a->rounds > 0) e = hipGraphLaunch(ctx->pt_graph.exec, s);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(temp_of, w + lay.temp_of, (size_t)count * 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(replica_at, w + lay.replica_at, (size_t)count * 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(accepted, w + lay.accepted, (size_t)nS * (nT - 1) * 8, hipMemcpyDeviceToHost, s);
+        e = hipMemcpyAsync(up.data() + lay.temp_of, w + lay.temp_of, lay.E_at - lay.temp_of, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess && E_at && a->rounds > 0)
         e = hipMemcpyAsync(E_at, w + lay.E_at, (size_t)a->rounds * count * 8, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -281,6 +311,9 @@ int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of,
         ctx->pt_graph.reset();
         return device_check(ctx, e, "mc_pt_run");
     }
+    std::memcpy(temp_of, up.data() + lay.temp_of, (size_t)count * 4);
+    std::memcpy(replica_at, up.data() + lay.replica_at, (size_t)count * 4);
+    std::memcpy(accepted, up.data() + lay.accepted, (size_t)nS * (nT - 1) * 8);
     return MC_OK;
 }
 
