@@ -364,7 +364,9 @@ __global__ __launch_bounds__(256) void k_pa_sweep(PaStep st)
         atomicAdd((unsigned long long *)&P.hist[(int64_t)st.hist_idx * (N + 1) + (e + 2 * N) / 4], 1ull);
     }
 
-    // ---- unpack and store the new population
+    // ---- unpack and store the new population (a measuring pass may leave it
+    // where it is)
+    if (P.nxt == P.cur) return;
     for (int t = tid; t < tasks_ld; t += nt) {
         const int g = lds_div(t, a.P, a.inv_p);
         unpack_lattice_words(lds, a, g, P.nxt + (int64_t)(s0 + g) * N, t - g * a.P);

@@ -127,17 +127,8 @@ int mc_pa_anneal(mc_ctx *ctx, const mc_pa_args *a, void *const *pop_spins, doubl
     int nmax = 0;
     for (int p = 0; p < a->npop; ++p) nmax = std::max(nmax, a->L[p] * a->L[p]);
 
-    // host FP64 weight tables: w_i(k) = exp(-(beta_i - beta_{i-1}) 4k)
-    std::vector<double> wt((size_t)a->nsteps * (nmax + 1));
-    for (int s_ = 0; s_ < a->nsteps; ++s_) {
-        const int i = a->step_first + s_;
-        const double dbeta = a->beta[i] - a->beta[i - 1];
-        for (int k = 0; k <= nmax; ++k) wt[(size_t)s_ * (nmax + 1) + k] = std::exp(-dbeta * (double)(4 * k));
-    }
-    hipError_t e = hipSuccess;
-    if (!wt.empty()) e = hipMemcpyAsync(w + lay.wtab, wt.data(), wt.size() * 8, hipMemcpyHostToDevice, s);
-
     // population layout and launch shape
+    hipError_t e = hipSuccess;
     PaStep st{};
     st.npop = a->npop;
     st.seed_lo = (uint32_t)a->seed;
@@ -165,6 +156,16 @@ int mc_pa_anneal(mc_ctx *ctx, const mc_pa_args *a, void *const *pop_spins, doubl
             Geom g{2, a->L[p], a->L[p], 1, (int64_t)a->L[p] * a->L[p], a->R};
             e = launch_init_int8(g, (int8_t *)pop_spins[p], 1, a->seed, (uint32_t)(p * a->R), s);
         }
+    if (e != hipSuccess) return device_check(ctx, e, "mc_pa_anneal setup");
+    // host FP64 weight tables while the populations are written: w_i(k) =
+    // exp(-(beta_i - beta_{i-1}) 4k)
+    std::vector<double> wt((size_t)a->nsteps * (nmax + 1));
+    for (int s_ = 0; s_ < a->nsteps; ++s_) {
+        const int i = a->step_first + s_;
+        const double dbeta = a->beta[i] - a->beta[i - 1];
+        for (int k = 0; k <= nmax; ++k) wt[(size_t)s_ * (nmax + 1) + k] = std::exp(-dbeta * (double)(4 * k));
+    }
+    if (!wt.empty()) e = hipMemcpyAsync(w + lay.wtab, wt.data(), wt.size() * 8, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return device_check(ctx, e, "mc_pa_anneal setup");
 
     // the measuring pass and every step as one graph.  The caller's stream may
@@ -194,22 +195,27 @@ int mc_pa_anneal(mc_ctx *ctx, const mc_pa_args *a, void *const *pop_spins, doubl
     s = s_cap;
     if (!reuse) e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     int half = 0;  // which half of each population buffer holds the current population
+    // The measuring pass moves the population to the other half if the steps are
+    // odd in number and leaves it where it is if they are even, so that the
+    // last step writes the first half.
+    const int moved = a->nsteps & 1;
     auto bind = [&](PaStep &x) {
+        const int to = x.identity ? half ^ moved : half ^ 1;
         for (int p = 0; p < a->npop; ++p) {
             PaPop &P = x.pop[p];
             int8_t *base = (int8_t *)pop_spins[p];
             const size_t bytes = (size_t)P.R * P.N;
             P.cur = base + (half ? bytes : 0);
-            P.nxt = base + (half ? 0 : bytes);
+            P.nxt = base + (to ? bytes : 0);
             P.E = (const int32_t *)(w + (half ? lay.Enew[p] : lay.E[p]));
-            P.Enew = (int32_t *)(w + (half ? lay.E[p] : lay.Enew[p]));
+            P.Enew = (int32_t *)(w + (to ? lay.Enew[p] : lay.E[p]));
         }
+        half = to;
     };
-    if (e == hipSuccess && reuse) half = (1 + a->nsteps) & 1;  // as after the recording below
     if (e == hipSuccess && !reuse) {
         PaStep m = st;
-        bind(m);
         m.identity = 1;
+        bind(m);
         m.theta = 0;
         m.step = (uint32_t)a->step_first;  // unused without sweeps
         m.hist_idx = 0;
@@ -219,13 +225,12 @@ int mc_pa_anneal(mc_ctx *ctx, const mc_pa_args *a, void *const *pop_spins, doubl
         m.t4 = t.met[1];
         m.t8 = t.met[2];
         e = launch_pa_step(m, a->R, blocks, s);
-        half ^= 1;
     }
     for (int s_ = 0; s_ < a->nsteps && e == hipSuccess && !reuse; ++s_) {
         const int i = a->step_first + s_;
         PaStep x = st;
-        bind(x);
         x.identity = 0;
+        bind(x);
         x.step = (uint32_t)i;
         x.hist_idx = s_ + 1;
         x.ctot_idx = s_;
@@ -234,7 +239,6 @@ int mc_pa_anneal(mc_ctx *ctx, const mc_pa_args *a, void *const *pop_spins, doubl
         x.t4 = t.met[1];
         x.t8 = t.met[2];
         e = launch_pa_step(x, a->R, blocks, s);
-        half ^= 1;
     }
     if (!reuse) {
         const hipError_t ec = hipStreamEndCapture(s, &graph);
@@ -251,12 +255,6 @@ int mc_pa_anneal(mc_ctx *ctx, const mc_pa_args *a, void *const *pop_spins, doubl
     }
     s = s_rec;
     if (e == hipSuccess) e = hipGraphLaunch(exec, s);
-    // the final population goes back to the first half of each buffer
-    if (e == hipSuccess && half)
-        for (int p = 0; p < a->npop && e == hipSuccess; ++p) {
-            const size_t bytes = (size_t)a->R * a->L[p] * a->L[p];
-            e = hipMemcpyAsync(pop_spins[p], (int8_t *)pop_spins[p] + bytes, bytes, hipMemcpyDeviceToDevice, s);
-        }
     // results to the host
     size_t hoff = 0;
     for (int p = 0; p < a->npop && e == hipSuccess; ++p) {
