@@ -112,6 +112,14 @@ __host__ __device__ __forceinline__ Thr split_thr(uint64_t T)
     return t;
 }
 
+// Position of workgroup b of n in the order of the data: workgroups are dealt
+// round the 8 XCDs, so each XCD (and its L2 cache) gets a consecutive eighth.
+__device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t n)
+{
+    const uint32_t per = n >> 3;
+    return b < 8u * per ? (b & 7u) * per + (b >> 3) : b;
+}
+
 // ---------------------------------------------------------------------------
 // wave64 reductions
 __device__ __forceinline__ long long wave_sum(long long v)

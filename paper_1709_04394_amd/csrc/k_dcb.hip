@@ -16,10 +16,12 @@
 // compare, ties settled from a queue of the wave) is the 2D band kernel's
 // (metro2d.hpp).
 //
-// What bounds it: VALU issue from ten hits on (4096^2 x 3, tiles of 128: 3780
-// attempted updates per ns at ten hits, 4650 at a hundred; 3050 and 3700 with a
-// comparison per class and two barriers per half-step), with one hit the
-// launch, the tile's load and the sums (1360 against 1180).
+// What bounds it: VALU issue from ten hits on, with one hit the launch, the
+// tile's load and the sums.  Attempted updates per ns, 4096^2 x 3, tiles of 128,
+// at one, ten and a hundred hits: 1970, 4270 and 5010; 1330, 3880 and 4980 with
+// tiles side by side on different XCDs (each then loads whole lines for 8 bytes
+// of a row), 1340, 3790 and 4660 with every wave settling its own ties, 1180,
+// 3050 and 3700 with a comparison per class besides.
 //
 // Energy and magnetisation of a sweep: every bond lies inside one tile or
 // joins a tile of colour 0 to one of colour 1.  Colour-0 tiles are final
@@ -43,6 +45,7 @@ struct DcbArgs {
     int L, T;                   // extent, tile side (multiples of 64)
     int coarse;                 // colour of the tiles of this launch
     int hits;
+    int pool;                   // one wave at a time settles the ties of all
     uint32_t replica0;
     uint64_t sweep;             // global sweep number; hit h draws as plain sweep sweep * hits + h
     uint32_t seed_lo, seed_hi;
@@ -52,10 +55,11 @@ struct DcbArgs {
 };
 
 // Workgroup -> tile: tiles of one coarse colour, (L/T)^2 / 2 of them, row by
-// row of tiles.
+// row of tiles (on one XCD: tiles side by side share the lines of their rows).
 __device__ __forceinline__ void dcb_tile(const DcbArgs &a, int b, int &tx, int &ty)
 {
     const int nt = a.L / a.T, half = nt / 2;
+    b = (int)xcd_order((uint32_t)b, gridDim.x);
     ty = b / half;
     tx = 2 * (b - ty * half) + ((ty + a.coarse) & 1);
 }
@@ -63,8 +67,9 @@ __device__ __forceinline__ void dcb_tile(const DcbArgs &a, int b, int &tx, int &
 __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
 {
     extern __shared__ uint32_t lds[];
-    __shared__ long long red[2][kDcbMaxWaves];
+    __shared__ int red[2][kDcbMaxWaves];
     __shared__ long long red_prev[2][16];
+    __shared__ uint32_t tied[kDcbMaxWaves];
     const int l = blockIdx.y;
     int tx, ty;
     dcb_tile(a, blockIdx.x, tx, ty);
@@ -80,64 +85,53 @@ __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
     // LDS word (r, par, c): tile row r - 1 (r = 0 and T + 1 are halo rows),
     // word column c - 1 of the tile (c = 0 and Wt + 1 are halo columns)
     auto widx = [&](int r, int par, int c) { return (r * 2 + par) * Ww + c; };
-    auto gy = [&](int r) {
-        int y = y0 + r - 1;
-        if (y < 0) y += a.L;
-        if (y >= a.L) y -= a.L;
-        return y;
-    };
-    auto gw = [&](int c) {
-        int w = wc0 + c - 1;
-        if (w < 0) w += Wl;
-        if (w >= Wl) w -= Wl;
-        return w;
-    };
     const MetroMasks mm = metro_masks(a.t4.top, a.t8.top, true);
-    uint4 *const tq = (uint4 *)(lds + ((rows * 2 * Ww + 3) & ~3)) + wave * kTieQueue;  // behind the tile
+    uint4 *const queue = (uint4 *)(lds + ((rows * 2 * Ww + 3) & ~3));  // behind the tile
+    const int nsh = 31 - __builtin_clz(nwaves);  // the waves are a power of two in number
     const int slots_per_lattice = (a.L / a.T) * (a.L / a.T);
     long long pre_e, pre_m;
     em_prefetch(a.prev, blockIdx.x, slots_per_lattice, l, gridDim.y, tid, pre_e, pre_m);
 
-    // ---- load the tile and its halo (corner words are not needed), a batch
-    // of words per thread in flight at once
-    const int ld = rows * 2 * Ww;
-    const uint32_t inv_ww = 0xFFFFFFFFu / (uint32_t)Ww + 1u;  // i / Ww as a high word, exact for i < 2^16
-    constexpr int kLoadBatch = 8;
-    for (int i0 = tid; i0 < ld; i0 += kLoadBatch * nt) {
-        uint32_t v[kLoadBatch];
-#pragma unroll
-        for (int j = 0; j < kLoadBatch; ++j) {
-            const int i = i0 + j * nt;
-            v[j] = 0u;
-            if (i < ld) {
-                const int rp = (int)__umulhi((uint32_t)i, inv_ww), c = i - rp * Ww, r = rp >> 1, par = rp & 1;
-                const bool corner = (r == 0 || r == rows - 1) && (c == 0 || c == Ww - 1);
-                if (!corner) v[j] = lat[((size_t)gy(r) * 2 + par) * Wl + gw(c)];
+    // ---- load the tile and its halo: a row's words of one parity, of the column
+    // to the left (odd) or right (even) that word, and the rows above and below
+    const int left = wc0 == 0 ? Wl - 1 : wc0 - 1, right = wc0 + Wt == Wl ? 0 : wc0 + Wt;
+    for (int i = tid; i < 2 * a.T; i += nt) {
+        const uint32_t *src = lat + (size_t)(2 * y0 + i) * Wl;
+        uint32_t *dst = lds + (i + 2) * Ww;
+        const uint32_t edge = src[(i & 1) ? left : right];
+        if (Wt == 1) {
+            dst[1] = src[wc0];
+        } else {
+            for (int c = 0; c < Wt; c += 2) {
+                uint2 v;
+                __builtin_memcpy(&v, src + wc0 + c, 8);
+                dst[1 + c] = v.x;
+                dst[2 + c] = v.y;
             }
         }
-#pragma unroll
-        for (int j = 0; j < kLoadBatch; ++j)
-            if (i0 + j * nt < ld) lds[i0 + j * nt] = v[j];
+        dst[(i & 1) ? 0 : Wt + 1] = edge;
+    }
+    for (int i = tid; i < 4 * Wt; i += nt) {
+        const int rp = i >> wsh, c = i & (Wt - 1);
+        const int y = rp < 2 ? (y0 == 0 ? a.L - 1 : y0 - 1) : (y0 + a.T == a.L ? 0 : y0 + a.T);
+        lds[(rp < 2 ? rp : 2 * a.T + rp) * Ww + 1 + c] = lat[((size_t)y * 2 + (rp & 1)) * Wl + wc0 + c];
     }
     __syncthreads();
     em_reduce(a.prev, blockIdx.x, slots_per_lattice, l, gridDim.y, tid, nt, pre_e, pre_m, red_prev);
 
     const int tasks = a.T * Wt;  // words of one colour: one per (row, column), a multiple of the threads
+    uint4 *const tq = queue + wave * kTieQueue;
+    int turn = (int)blockIdx.x;  // the wave that settles, in turn (a wave's SIMD is that of its number)
     for (int h = 0; h < a.hits; ++h) {
         const uint64_t dsweep = a.sweep * (uint64_t)a.hits + (uint64_t)h;
         for (int col = 0; col < 2; ++col) {
             const uint32_t w3 = ctr_w3(kTagSweep, (uint32_t)col, dsweep);
             const uint32_t w3lo = ctr_w3(kTagSweepLo, (uint32_t)col, dsweep);
             uint32_t qn = 0;
-            auto settle = [&]() {
-                const uint32_t i = tid & 63;
-                if (i < qn) {
-                    const uint4 it = tq[i];
-                    const uint32_t f = metro_settle(it.z, it.w, it.y, rep, (uint32_t)dsweep, w3lo, a.seed_lo, a.seed_hi,
-                                                    a.t4.low, a.t8.low);
-                    if (f) lds[it.x] ^= f;
-                }
-                qn = 0;
+            auto settle = [&](const uint4 &it) {
+                const uint32_t f = metro_settle(it.z, it.w, it.y, rep, (uint32_t)dsweep, w3lo, a.seed_lo, a.seed_hi,
+                                                a.t4.low, a.t8.low);
+                if (f) lds[it.x] ^= f;
             };
             for (int t = tid; t < tasks; t += nt) {
                 // words column by column: T is a power of two
@@ -161,35 +155,56 @@ __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
                 lds[is] = mw.S;
                 const uint64_t m = __ballot(mw.pend != 0u);
                 const uint32_t cnt = (uint32_t)__popcll(m);
-                if (qn + cnt > (uint32_t)kTieQueue) settle();
+                if (qn + cnt > (uint32_t)kTieQueue) {
+                    if ((uint32_t)(tid & 63) < qn) settle(tq[tid & 63]);
+                    qn = 0;
+                }
                 if (mw.pend) tq[qn + wave_rank(m)] = make_uint4((uint32_t)is, blk, mw.pend, mw.c8);
                 qn += cnt;
             }
-            settle();
+            if (a.pool) {
+                if ((tid & 63) == 0) tied[wave] = qn;
+                __syncthreads();
+                // the queues of all waves, an equal share of a wave's lanes each
+                if (wave == (turn++ & (nwaves - 1))) {
+                    const int sh = 6 - nsh, of = (tid & 63) >> sh;
+                    for (uint32_t i = tid & ((1 << sh) - 1), n = tied[of]; __any(i < n); i += 1u << sh)
+                        if (i < n) settle(queue[of * kTieQueue + i]);
+                }
+            } else if ((uint32_t)(tid & 63) < qn) {
+                settle(tq[tid & 63]);
+            }
             __syncthreads();
         }
     }
 
     // ---- store the tile in place
-    for (int i = tid; i < a.T * 2 * Wt; i += nt) {
-        const int rp = i >> wsh, c = 1 + (i & (Wt - 1)), r = 1 + (rp >> 1), par = rp & 1;
-        lat[((size_t)(y0 + r - 1) * 2 + par) * Wl + wc0 + c - 1] = lds[widx(r, par, c)];
+    for (int i = tid; i < 2 * a.T; i += nt) {
+        uint32_t *dst = lat + (size_t)(2 * y0 + i) * Wl + wc0;
+        const uint32_t *src = lds + (i + 2) * Ww + 1;
+        if (Wt == 1) {
+            dst[0] = src[0];
+        } else {
+            for (int c = 0; c < Wt; c += 2) {
+                const uint2 v = make_uint2(src[c], src[c + 1]);
+                __builtin_memcpy(dst + c, &v, 8);
+            }
+        }
     }
 
     // ---- energy and magnetisation of this tile's share
     if (!a.part) return;
-    long long e_acc = 0, m_acc = 0;
+    int e_acc = 0, m_acc = 0;
     const bool edges = a.coarse == 1;
     for (int t = tid; t < tasks; t += nt) {
         const int c = 1 + (t >> tsh), r = 1 + (t & (a.T - 1));
         const int y = y0 + r - 1;
         // the odd-colour word of row r (x parity q) and its four neighbours
         const int q = (1 + y) & 1;
-        const uint32_t S = lds[widx(r, q, c)];
-        const uint32_t U = lds[widx(r - 1, q, c)], D = lds[widx(r + 1, q, c)];
-        const uint32_t O = lds[widx(r, 1 - q, c)];
-        const uint32_t Sh = q == 0 ? __builtin_amdgcn_alignbit(O, lds[widx(r, 1, c - 1)], 31)
-                                   : __builtin_amdgcn_alignbit(lds[widx(r, 0, c + 1)], O, 1);
+        const int e = r * 2 * Ww + c, o = e + Ww, is = q ? o : e, io = q ? e : o;
+        const uint32_t S = lds[is], U = lds[is - 2 * Ww], D = lds[is + 2 * Ww], O = lds[io];
+        const uint32_t Nb = lds[io + (q ? 1 : -1)];
+        const uint32_t Sh = __builtin_amdgcn_alignbit(q ? Nb : O, q ? O : Nb, q ? 1u : 31u);
         // bonds inside the tile seen from their odd end: up and down unless
         // the neighbour row is a halo row, the same-column partner always,
         // the shifted partner but for the one bit across the tile's edge
@@ -208,7 +223,7 @@ __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
         // halo rows (both parity arrays), first and last column against the
         // halo columns
         for (int t = tid; t < 2 * 2 * Wt; t += nt) {
-            const int side = t / (2 * Wt), rem = t - side * 2 * Wt, par = rem / Wt, c = 1 + rem - par * Wt;
+            const int side = t >> (wsh + 1), par = (t >> wsh) & 1, c = 1 + (t & (Wt - 1));
             const int r = side == 0 ? 1 : a.T, rh = side == 0 ? 0 : a.T + 1;
             e_acc += 2 * __builtin_popcount(lds[widx(r, par, c)] ^ lds[widx(rh, par, c)]) - 32;
         }
@@ -221,9 +236,9 @@ __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
             e_acc += 2 * (int)((l0 ^ l1) + (r1 ^ r0)) - 2;
         }
     }
-    e_acc = wave_sum(e_acc);
-    m_acc = wave_sum(m_acc);
-    if ((tid & 63) == 0) {
+    e_acc = wave_sum_last(e_acc);
+    m_acc = wave_sum_last(m_acc);
+    if ((tid & 63) == 63) {
         red[0][wave] = e_acc;
         red[1][wave] = m_acc;
     }
@@ -273,6 +288,12 @@ hipError_t launch_dcb_phase(uint32_t *packed, int L, int T, int count, int coars
     int threads = std::min(256, T * T / 64);
     while (threads < std::min(64 * kDcbMaxWaves, T * T / 64) && (int64_t)tiles * count * (threads / 64) < 3072)
         threads *= 2;
+    // One wave settles the ties of all four where their six or so each would
+    // take four passes, and where other workgroups fill the second barrier's
+    // wait: tiles of 128, 4096^2 x 3 (1536 workgroups) 3980 against 3790, 1024
+    // workgroups 3190 against 3150, 512 2240 against 2350; tiles of 256, whose
+    // waves gather four words' ties per lane, 4350 against 4840 (768).
+    a.pool = threads > 64 && threads == T * T / 64 && (int64_t)tiles * count >= 1024;
     hipLaunchKernelGGL(k_dcb, dim3((unsigned)tiles, (unsigned)count), dim3(threads), dcb_lds_bytes(T, threads), s, a);
     return hipGetLastError();
 }

@@ -75,9 +75,8 @@ __global__ __launch_bounds__(256, 5) void k_sg_msc(SgMscArgs a)
     constexpr int Z = 2 * DIMS;
     constexpr int NC = HB ? Z + 1 : DIMS;  // heat-bath d = 0..z; Metropolis a = 0 .. z/2 - 1
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // workgroups in the order of their sites on each of the 8 L2 caches:
-    // neighbouring rows' words and couplings are read from the same one
-    const uint32_t g = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    // neighbouring rows' words and couplings are read on the same XCD
+    const uint32_t g = xcd_order(blockIdx.x, gridDim.x);
     if (g >= a.total) return;
     const uint32_t l = g / a.parts, part = g - l * a.parts;
     const LaneBits lb = lane_bits(tid & 63);
