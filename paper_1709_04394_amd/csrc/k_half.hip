@@ -22,7 +22,7 @@
 // pass through the kernel (heat-bath 1000 x 750: 5.0 us per even half-sweep and
 // 5.4 with E, M, 11.8 us per sweep with the launches' gaps, against 63 with a
 // thread that walks 16 sites one by one and a measurement of its own); above,
-// memory and VALU issue (4096^2: 11 and 13 us, 27 us per sweep against 432).
+// memory and VALU issue (4096^2: 11 and 13 us, 26 us per sweep against 432).
 #include <algorithm>
 
 #include "internal.hpp"
@@ -46,6 +46,7 @@ struct HalfArgs {
     uint32_t chunks, mul_chunks;  // per row; floor((2^32 - 1) / chunks)
     uint32_t mul_ly;              // floor((2^32 - 1) / Ly)
     uint32_t total;               // chunks of a lattice
+    uint32_t blocks;              // workgroups of a lattice
     uint32_t c;                   // colour
     uint32_t seed_lo, seed_hi, replica0, sweep_lo, w3, w3lo;
     // class thresholds (top byte, low 24 bits; T = 2^32 as 255 * 2^24 + 2^24):
@@ -80,7 +81,11 @@ __global__ __launch_bounds__(kHalfThreads) void k_half(HalfArgs a)
             if (i < (HB ? DIMS : 1)) asm volatile("" : "+v"(tv[k][i]));
         }
     int e_acc = 0, m_acc = 0;
-    for (uint32_t t = blockIdx.x * blockDim.x + tid; t < a.total; t += gridDim.x * blockDim.x) {
+    // Large lattices by XCD (4096^2 25.6 against 26.7 us per sweep, 200^3 with
+    // couplings 33 against 37); where a thread has one chunk it costs 4 % (1000 x
+    // 750).
+    const uint32_t b = a.blocks == kHalfBlocks ? xcd_order(blockIdx.x, kHalfBlocks) : blockIdx.x;
+    for (uint32_t t = b * kHalfThreads + tid; t < a.total; t += a.blocks * kHalfThreads) {
         const uint32_t row = quotient28(t, a.chunks, a.mul_chunks);
         const uint32_t m0 = 16u * (t - row * a.chunks);
         uint32_t y = row, z = 0;
@@ -235,7 +240,7 @@ bool half_supported(const Geom &g) { return g.Lx >= 32; }
 template <int D, bool HB, bool HJ>
 static hipError_t launch_half_t(const HalfArgs &a, int count, hipStream_t s)
 {
-    const dim3 grid(std::min<uint32_t>((a.total + kHalfThreads - 1) / kHalfThreads, kHalfBlocks), (unsigned)count);
+    const dim3 grid(a.blocks, (unsigned)count);
     if (a.EM) hipLaunchKernelGGL((k_half<D, HB, HJ, true>), grid, dim3(kHalfThreads), 0, s, a);
     else hipLaunchKernelGGL((k_half<D, HB, HJ, false>), grid, dim3(kHalfThreads), 0, s, a);
     return hipGetLastError();
@@ -258,6 +263,7 @@ hipError_t launch_half(const SweepCall &c, int8_t *spins, uint64_t sweep, int ph
     a.mul_chunks = 0xFFFFFFFFu / a.chunks;
     a.mul_ly = 0xFFFFFFFFu / a.Ly;
     a.total = a.chunks * (uint32_t)(g.N / g.Lx);
+    a.blocks = std::min<uint32_t>((a.total + kHalfThreads - 1) / kHalfThreads, kHalfBlocks);
     a.c = (uint32_t)phase;
     a.seed_lo = c.seed_lo;
     a.seed_hi = c.seed_hi;

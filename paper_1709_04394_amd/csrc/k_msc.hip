@@ -129,7 +129,7 @@ __global__ __launch_bounds__(256) void k_msc(MscArgs a)
         cd.clear();
     }
     uint32_t done = 0;
-    for (uint32_t t = blockIdx.x * 4u + (uint32_t)wave; t < tasks; t += gridDim.x * 4u) {
+    for (uint32_t t = xcd_order(blockIdx.x, gridDim.x) * 4u + (uint32_t)wave; t < tasks; t += gridDim.x * 4u) {
         const uint32_t j0 = t << 6;
         const uint32_t row = t / per_row, m0 = (t - row * per_row) << 6;
         const uint32_t z = row / (uint32_t)a.Ly, y = row - z * (uint32_t)a.Ly;
