@@ -6,8 +6,8 @@
 //
 // Layout: the sites of a colour in the order of their index j = m + (Lx / 2)
 // (y + Ly z), 32 to a word, set bit = spin -1, rows following one another
-// without gaps.  A thread updates whole words: two Philox blocks give the
-// bit-planes of a word's 32 sites whatever the row length.  The neighbours of
+// without gaps.  A thread updates whole words, or halves of them: two Philox
+// blocks (one) give the bit-planes of their sites whatever the row length.  The neighbours of
 // the sites j are bits of the other colour's words at fixed distances: j (the
 // partner in the pair of columns), j - 1 or j + 1 by the row's parity, j +- Lx/2
 // (y), j +- Lx Ly / 2 (z).  Those are windows of 32 bits that start at any bit
@@ -26,13 +26,15 @@
 // top byte, the low 24 bits from Philox(j, .., SWEEP_LO | c).  E and M are
 // popcounts of the odd half-sweep (every bond has one odd site).
 //
-// What bounds it: up to about 10^4 sites the latency of a half-sweep's chain
-// (0.7 us: windows, bit-serial comparison, ties, barrier), above it the VALU of
-// the one CU.  us per sweep of long calls with E, M, against byte per site in
-// LDS (rows of 32 sites: 16-bit words per row): 64^2 1.5 (3.8), 128^2 1.7 (11.5),
-// 200^2 heat-bath 3.1 (25), 300^2 5.0 (58), 30^3 +-J 3.0 (23), 32^3 +-J 2.7 (5.7),
-// 32 x 64^2 +-J 8.0 (18).  A half that is a multiple of 32 repeats word 0 after
-// the last and needs no test for the end (64^2 1.43 against 1.59).
+// What bounds it: up to about 10^4 sites the issue of single waves (a half-sweep
+// is 0.5 to 0.7 us: windows, bit-serial comparison, ties, barrier), above it the
+// VALU of the one CU.  us per sweep of long calls with E, M, against a byte per
+// site in LDS (rows of 32 sites: a 16-bit word per row and parity): 64^2 1.14
+// (3.8), 128^2 1.6 (11.5), 200^2 heat-bath 3.1 (25), 300^2 5.0 (58), 30^3 +-J 2.9
+// (23), 32^3 +-J 2.6 (5.7), 32 x 64^2 +-J 8.0 (18).  A half that is a multiple of
+// 32 repeats word 0 after the last and needs no test for the end (64^2 1.43
+// against 1.59).  One wave that settles the ties of all between two barriers
+// made 128^2 2.5 and 32^3 3.0: its latency is longer than the passes it saves.
 #include <algorithm>
 
 #include "internal.hpp"
@@ -59,6 +61,18 @@ struct WholeArgs {
     int64_t em_stride;
 };
 
+// A thread's sites: 32, or 16 for lattices of few words.
+template <int BITS>
+struct WholeItem;
+template <>
+struct WholeItem<32> {
+    using type = uint32_t;
+};
+template <>
+struct WholeItem<16> {
+    using type = uint16_t;
+};
+
 constexpr int kWholePad = 2;  // words read past the last one (their bits are not used)
 
 // 33 or more bits of an array of `half` bits from bit pos (0 <= pos < half),
@@ -75,9 +89,9 @@ __device__ __forceinline__ uint64_t bit_window(const uint32_t *v, uint32_t pos, 
     return r;
 }
 
-// What a word's sites share in every half-sweep.
+// What an item's sites share in every half-sweep.
 struct WordGeo {
-    uint32_t w;
+    uint32_t w;                 // item number
     uint32_t odd;               // sites in rows with y + z odd
     uint32_t first, last;       // first and last sites of their rows
     uint32_t top, bottom;       // 3D: sites with y = Ly - 1, y = 0
@@ -91,20 +105,21 @@ __device__ __forceinline__ uint32_t wrap_add(uint32_t j0, uint32_t d, uint32_t h
     return p < p - half ? p : p - half;
 }
 
-template <int DIMS>
+template <int DIMS, int BITS>
 __device__ __forceinline__ WordGeo word_geo(const WholeArgs &a, uint32_t w)
 {
+    constexpr uint32_t ALL = BITS == 32 ? ~0u : 0xFFFFu;
     WordGeo g;
-    const uint32_t j0 = 32u * w;
+    const uint32_t j0 = BITS * w;
     g.w = w;
     g.odd = g.first = g.last = g.top = g.bottom = 0u;
     const uint32_t row = quotient28(j0, a.hx, a.mul_hx);
     uint32_t m = j0 - row * a.hx, z = quotient28(row, a.Ly, a.mul_ly), y = row - z * a.Ly;
-    for (uint32_t s = 0; s < 32u;) {
-        const uint32_t e = s + (a.hx - m), end = e < 32u ? e : 32u;
-        const uint32_t seg = (end < 32u ? (1u << end) - 1u : ~0u) & ~((1u << s) - 1u);
+    for (uint32_t s = 0; s < BITS;) {
+        const uint32_t e = s + (a.hx - m), end = e < BITS ? e : BITS;
+        const uint32_t seg = (end < BITS ? (1u << end) - 1u : ALL) & ~((1u << s) - 1u);
         if (m == 0) g.first |= 1u << s;
-        if (e <= 32u) g.last |= 1u << (e - 1u);
+        if (e <= BITS) g.last |= 1u << (e - 1u);
         if ((y + z) & 1u) g.odd |= seg;
         if (y == 0) g.bottom |= seg;
         if (y + 1 == a.Ly) g.top |= seg;
@@ -115,7 +130,7 @@ __device__ __forceinline__ WordGeo word_geo(const WholeArgs &a, uint32_t w)
             ++z;
         }
     }
-    g.valid = a.half - j0 < 32u ? (1u << (a.half - j0)) - 1u : ~0u;
+    g.valid = a.half - j0 < BITS ? (1u << (a.half - j0)) - 1u : ALL;
     return g;
 }
 
@@ -127,16 +142,17 @@ __device__ __forceinline__ uint32_t bit_mux(uint32_t sel, uint32_t hi, uint32_t 
 // Bits of the sites' neighbours in the other colour's array v: n[0] at j, n[1]
 // the other x neighbour (par: right, else left), n[2], n[3] at y + 1, y - 1,
 // n[4], n[5] at z + 1, z - 1.
-template <int DIMS, bool ALIGNED>
+template <int DIMS, bool ALIGNED, int BITS>
 __device__ __forceinline__ void neighbour_words(const uint32_t *v, const WordGeo &g, uint32_t par, const WholeArgs &a,
                                                 uint32_t (&n)[6])
 {
-    const uint32_t half = a.half, j0 = 32u * g.w;
-    const uint32_t o = v[g.w], before = v[(int)g.w - (g.w ? 1 : 0)], after = v[g.w + 1];
+    const uint32_t half = a.half, j0 = BITS * g.w;
+    const auto *vi = (const typename WholeItem<BITS>::type *)v;
+    const uint32_t o = vi[g.w], before = vi[(int)g.w - (g.w ? 1 : 0)], after = vi[g.w + 1];
     const uint64_t U = bit_window<ALIGNED>(v, wrap_add(j0, a.hx - 1u, half), half);
     const uint64_t D = bit_window<ALIGNED>(v, wrap_add(j0, half - a.hx, half), half);
-    const uint32_t left = bit_mux(g.first, (uint32_t)U, (o << 1) | (before >> 31));
-    const uint32_t right = bit_mux(g.last, (uint32_t)(D >> 1), __builtin_amdgcn_alignbit(after, o, 1));
+    const uint32_t left = bit_mux(g.first, (uint32_t)U, (o << 1) | (before >> (BITS - 1)));
+    const uint32_t right = bit_mux(g.last, (uint32_t)(D >> 1), BITS == 32 ? __builtin_amdgcn_alignbit(after, o, 1) : (o | after << 16) >> 1);
     n[0] = o;
     n[1] = bit_mux(par, right, left);
     n[2] = (uint32_t)(U >> 1);
@@ -151,16 +167,24 @@ __device__ __forceinline__ void neighbour_words(const uint32_t *v, const WordGeo
     }
 }
 
-// Sign bits of the pairs j of word w, from the lattice's bytes: even and odd
-// bytes.  The last word's are the end of the last 32 pairs.
+// Sign bits of the pairs j of item w, from the lattice's bytes: even and odd
+// bytes.  The last item's are the end of the last BITS pairs.
+template <int BITS>
 __device__ __forceinline__ void pack_pairs(const int8_t *p, uint32_t w, uint32_t half, uint32_t &ev, uint32_t &od)
 {
-    const uint32_t cnt = half - 32u * w;
-    if (cnt >= 32u || half >= 32u) {
-        const uint32_t sh = cnt >= 32u ? 0u : 32u - cnt, off = 64u * w - 2u * sh;
-        const Row32 a = load_row32(p, off), b = load_row32(p, off + 32u);
-        ev = (sign_bits16(pick16(a, 0x06040200u)) | sign_bits16(pick16(b, 0x06040200u)) << 16) >> sh;
-        od = (sign_bits16(pick16(a, 0x07050301u)) | sign_bits16(pick16(b, 0x07050301u)) << 16) >> sh;
+    const uint32_t cnt = half - BITS * w;
+    if (cnt >= BITS || half >= BITS) {
+        const uint32_t sh = cnt >= BITS ? 0u : BITS - cnt, off = 2u * (BITS * w - sh);
+        const Row32 a = load_row32(p, off);
+        ev = sign_bits16(pick16(a, 0x06040200u));
+        od = sign_bits16(pick16(a, 0x07050301u));
+        if (BITS == 32) {
+            const Row32 b = load_row32(p, off + 32u);
+            ev |= sign_bits16(pick16(b, 0x06040200u)) << 16;
+            od |= sign_bits16(pick16(b, 0x07050301u)) << 16;
+        }
+        ev >>= sh;
+        od >>= sh;
     } else {
         ev = od = 0u;
         for (uint32_t i = 0; i < cnt; ++i) {
@@ -170,10 +194,11 @@ __device__ __forceinline__ void pack_pairs(const int8_t *p, uint32_t w, uint32_t
     }
 }
 
+template <int BITS>
 __device__ __forceinline__ void store_pairs(int8_t *p, uint32_t ev, uint32_t od)
 {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < BITS / 16; ++h) {
         Row32 r;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -186,17 +211,24 @@ __device__ __forceinline__ void store_pairs(int8_t *p, uint32_t ev, uint32_t od)
     }
 }
 
-// K: words of a colour per thread
-template <int DIMS, bool HB, bool HASJ, int K, bool ALIGNED>
+// K: items of BITS sites of a colour per thread
+template <int DIMS, bool HB, bool HASJ, int K, bool ALIGNED, int BITS>
 __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
 {
     constexpr int Z = 2 * DIMS;
+    using item_t = typename WholeItem<BITS>::type;
     extern __shared__ uint32_t sm[];  // spins [2][stride], then couplings [2][Z][stride]
     __shared__ uint32_t tlow[8];
     __shared__ unsigned long long sums[2];  // of a sweep: down spins << 32 | unsatisfied bonds
     const uint32_t tid = threadIdx.x, nt = blockDim.x, l = blockIdx.x;
-    const uint32_t stride = a.words + kWholePad;
+    const uint32_t stride = a.words + kWholePad, items = (a.half + (BITS - 1)) / BITS;
     uint32_t *S = sm, *Jb = sm + 2 * stride;
+    auto item = [](uint32_t *v) { return (item_t *)v; };
+    // item w of array v, and its copy after the last word
+    auto put = [&](uint32_t *v, uint32_t w, uint32_t x) {
+        item(v)[w] = (item_t)x;
+        if (ALIGNED && w < 32u / BITS) item(v + a.words)[w] = (item_t)x;
+    };
     const int64_t N = 2 * (int64_t)a.half;
     if (tid < 8) tlow[tid] = a.low[tid];
     if (tid < 2) sums[tid] = 0ull;
@@ -206,28 +238,20 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const uint32_t w = tid + k * nt;
-        mine[k] = w < a.words;
+        mine[k] = w < items;
         if (!mine[k]) continue;
-        g[k] = word_geo<DIMS>(a, w);
+        g[k] = word_geo<DIMS, BITS>(a, w);
         uint32_t ev, od;
-        pack_pairs(src, w, a.half, ev, od);
-        S[w] = bit_mux(g[k].odd, od, ev);
-        S[stride + w] = bit_mux(g[k].odd, ev, od);
-        if (ALIGNED && w == 0) {
-            S[a.words] = S[0];
-            S[stride + a.words] = S[stride];
-        }
+        pack_pairs<BITS>(src, w, a.half, ev, od);
+        put(S, w, bit_mux(g[k].odd, od, ev));
+        put(S + stride, w, bit_mux(g[k].odd, ev, od));
         if (HASJ)
 #pragma unroll
             for (int d = 0; d < DIMS; ++d) {
                 // own couplings: right (for now in n[0]'s place), up, z + 1
-                pack_pairs(a.J + d * N, w, a.half, ev, od);
-                Jb[(2 * d) * stride + w] = bit_mux(g[k].odd, od, ev);
-                Jb[(Z + 2 * d) * stride + w] = bit_mux(g[k].odd, ev, od);
-                if (ALIGNED && w == 0) {
-                    Jb[(2 * d) * stride + a.words] = Jb[(2 * d) * stride];
-                    Jb[(Z + 2 * d) * stride + a.words] = Jb[(Z + 2 * d) * stride];
-                }
+                pack_pairs<BITS>(a.J + d * N, w, a.half, ev, od);
+                put(Jb + (2 * d) * stride, w, bit_mux(g[k].odd, od, ev));
+                put(Jb + (Z + 2 * d) * stride, w, bit_mux(g[k].odd, ev, od));
             }
     }
     __syncthreads();
@@ -240,24 +264,24 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
                 for (int c = 0; c < 2; ++c) {
                     // the bond to a left, lower or z - 1 neighbour is that neighbour's own
                     const uint32_t par = c ? ~g[k].odd : g[k].odd, w = g[k].w;
-                    const uint32_t *own = Jb + c * Z * stride, *oth = Jb + (1 - c) * Z * stride;
+                    uint32_t *own = Jb + c * Z * stride, *oth = Jb + (1 - c) * Z * stride;
                     uint32_t n[6], nx[6];
-                    neighbour_words<DIMS, ALIGNED>(oth, g[k], 0u, a, nx);  // x, at the left neighbour
-                    j0[c][k] = bit_mux(par, oth[w], own[w]);
-                    Jb[(c * Z + 1) * stride + w] = bit_mux(par, own[w], nx[1]);
-                    neighbour_words<DIMS, ALIGNED>(oth + 2 * stride, g[k], 0u, a, n);
-                    Jb[(c * Z + 3) * stride + w] = n[3];
+                    neighbour_words<DIMS, ALIGNED, BITS>(oth, g[k], 0u, a, nx);  // x, at the left neighbour
+                    j0[c][k] = bit_mux(par, item(oth)[w], item(own)[w]);
+                    item(own + stride)[w] = (item_t)bit_mux(par, item(own)[w], nx[1]);
+                    neighbour_words<DIMS, ALIGNED, BITS>(oth + 2 * stride, g[k], 0u, a, n);
+                    item(own + 3 * stride)[w] = (item_t)n[3];
                     if (DIMS == 3) {
-                        neighbour_words<DIMS, ALIGNED>(oth + 4 * stride, g[k], 0u, a, n);
-                        Jb[(c * Z + 5) * stride + w] = n[5];
+                        neighbour_words<DIMS, ALIGNED, BITS>(oth + 4 * stride, g[k], 0u, a, n);
+                        item(own + 5 * stride)[w] = (item_t)n[5];
                     }
                 }
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < K; ++k)
             if (mine[k]) {
-                Jb[g[k].w] = j0[0][k];
-                Jb[Z * stride + g[k].w] = j0[1][k];
+                item(Jb)[g[k].w] = (item_t)j0[0][k];
+                item(Jb + Z * stride)[g[k].w] = (item_t)j0[1][k];
             }
         __syncthreads();
     }
@@ -287,21 +311,22 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
         for (int c = 0; c < 2; ++c) {
             const uint32_t w3 = ctr_w3(kTagSweep, (uint32_t)c, sweep), w3lo = ctr_w3(kTagSweepLo, (uint32_t)c, sweep);
             uint32_t *own = S + c * stride;
-            const uint32_t *oth = S + (1 - c) * stride;
+            uint32_t *oth = S + (1 - c) * stride;
             uint32_t count = 0;  // down spins << 16 | unsatisfied bonds, of this thread's words
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 if (!mine[k]) continue;
                 const uint32_t w = g[k].w;
                 uint32_t n[6];
-                neighbour_words<DIMS, ALIGNED>(oth, g[k], c ? ~g[k].odd : g[k].odd, a, n);
-                const uint32_t s = own[w];
-                const uint4 A = philox(make_uint4(2u * w, rep, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
-                const uint4 B = philox(make_uint4(2u * w + 1u, rep, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
+                neighbour_words<DIMS, ALIGNED, BITS>(oth, g[k], c ? ~g[k].odd : g[k].odd, a, n);
+                const uint32_t s = item(own)[w], blk = BITS / 16 * w;
+                const uint4 A = philox(make_uint4(blk, rep, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
+                uint4 B = A;
+                if (BITS == 32) B = philox(make_uint4(blk + 1u, rep, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
                 uint32_t xk[6];
 #pragma unroll
                 for (int i = 0; i < Z; ++i) {
-                    if (HASJ) n[i] ^= Jb[(c * Z + i) * stride + w];
+                    if (HASJ) n[i] ^= item(Jb + (c * Z + i) * stride)[w];
                     xk[i] = HB ? n[i] : (n[i] ^ s);
                 }
                 uint32_t c0, c1, c2;
@@ -311,7 +336,13 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
                 uint32_t lt = 0u, eq = g[k].valid;
 #pragma unroll
                 for (int b = 0; b < 8; ++b) {
-                    const uint32_t X = plane_pair(A, B, b);
+                    uint32_t X;
+                    if (BITS == 32) {
+                        X = plane_pair(A, B, b);
+                    } else {
+                        X = b < 2 ? A.x : b < 4 ? A.y : b < 6 ? A.z : A.w;
+                        if (b & 1) X >>= 16;
+                    }
                     const uint32_t *ts = a.mask[b];
                     uint32_t T = bit_mux(c0, ts[1], tv[b][0]);  // classes 0, 1
                     if (HB) {
@@ -331,17 +362,16 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
                     const int b = __builtin_ctz(pend);
                     pend &= pend - 1u;
                     const uint32_t cls = ((c0 >> b) & 1u) | (((c1 >> b) & 1u) << 1) | (((c2 >> b) & 1u) << 2);
-                    const uint4 lo = philox(make_uint4(32u * w + (uint32_t)b, rep, (uint32_t)sweep, w3lo), a.seed_lo,
+                    const uint4 lo = philox(make_uint4(BITS * w + (uint32_t)b, rep, (uint32_t)sweep, w3lo), a.seed_lo,
                                             a.seed_hi);
                     if ((lo.x & 0xFFFFFFu) < tlow[cls]) so ^= 1u << b;
                 }
-                own[w] = so;
-                if (ALIGNED && w == 0) own[a.words] = so;
+                put(own, w, so);
                 if (c == 1 && a.EM) {
                     uint32_t u = 0;
 #pragma unroll
                     for (int i = 0; i < Z; ++i) u += (uint32_t)__builtin_popcount((so ^ n[i]) & g[k].valid);
-                    const uint32_t o = HASJ ? oth[w] : n[0];
+                    const uint32_t o = HASJ ? item(oth)[w] : n[0];
                     const uint32_t dn = (uint32_t)(__builtin_popcount(so & g[k].valid) + __builtin_popcount(o & g[k].valid));
                     count += u | dn << 16;
                 }
@@ -362,18 +392,18 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         if (!mine[k]) continue;
-        const uint32_t w = g[k].w, s0 = S[w], s1 = S[stride + w];
+        const uint32_t w = g[k].w, s0 = item(S)[w], s1 = item(S + stride)[w];
         const uint32_t ev = bit_mux(g[k].odd, s1, s0), od = bit_mux(g[k].odd, s0, s1);
-        if (a.half - 32u * w >= 32u) store_pairs(src + 64 * (int64_t)w, ev, od);
-        S[w] = ev;
-        S[stride + w] = od;
+        if (a.half - BITS * w >= BITS) store_pairs<BITS>(src + 2 * BITS * (int64_t)w, ev, od);
+        item(S)[w] = (item_t)ev;
+        item(S + stride)[w] = (item_t)od;
     }
     if (ALIGNED) return;
     __syncthreads();
-    if (a.half >= 32u) {  // the last 32 pairs
+    if (a.half >= BITS) {  // the last BITS pairs
         if (tid == 0)
-            store_pairs(src + 2 * (int64_t)(a.half - 32u), (uint32_t)bit_window<true>(S, a.half - 32u, a.half),
-                        (uint32_t)bit_window<true>(S + stride, a.half - 32u, a.half));
+            store_pairs<BITS>(src + 2 * (int64_t)(a.half - BITS), (uint32_t)bit_window<true>(S, a.half - BITS, a.half),
+                              (uint32_t)bit_window<true>(S + stride, a.half - BITS, a.half));
     } else if (tid < a.half) {
         src[2 * tid] = ((S[0] >> tid) & 1u) ? (int8_t)-1 : (int8_t)1;
         src[2 * tid + 1] = ((S[stride] >> tid) & 1u) ? (int8_t)-1 : (int8_t)1;
@@ -390,29 +420,43 @@ static size_t whole_lds_bytes(const Geom &g, bool hasJ)
 // sites one workgroup takes longer than two launches over the whole chip.
 bool whole_supported(const Geom &g) { return g.N <= (1 << 17); }
 
-template <int DIMS, bool HB, bool HASJ, int K, bool ALIGNED>
-static hipError_t launch_whole_a(const WholeArgs &a, int count, unsigned threads, size_t lds, hipStream_t s)
+template <int DIMS, bool HB, bool HASJ, int K, bool ALIGNED, int BITS>
+static hipError_t launch_whole_a(const WholeArgs &a, int count, size_t lds, hipStream_t s)
 {
     static LdsLimit lim;
-    const hipError_t e = lim.ensure((const void *)k_whole<DIMS, HB, HASJ, K, ALIGNED>, 128 * 1024);
+    const auto f = k_whole<DIMS, HB, HASJ, K, ALIGNED, BITS>;
+    const hipError_t e = lim.ensure((const void *)f, 128 * 1024);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_whole<DIMS, HB, HASJ, K, ALIGNED>), dim3((unsigned)count), dim3(threads), lds, s, a);
+    const uint32_t items = (a.half + BITS - 1) / BITS;
+    hipLaunchKernelGGL(f, dim3((unsigned)count), dim3(std::min(1024u, (items + 63u) & ~63u)), lds, s, a);
     return hipGetLastError();
 }
 
-template <int DIMS, bool HB, bool HASJ, int K>
-static hipError_t launch_whole_t(const WholeArgs &a, int count, unsigned threads, size_t lds, hipStream_t s)
+template <int DIMS, bool HB, bool HASJ, int K, int BITS>
+static hipError_t launch_whole_t(const WholeArgs &a, int count, size_t lds, hipStream_t s)
 {
-    return a.half % 32u ? launch_whole_a<DIMS, HB, HASJ, K, false>(a, count, threads, lds, s)
-                        : launch_whole_a<DIMS, HB, HASJ, K, true>(a, count, threads, lds, s);
+    return a.half % 32u ? launch_whole_a<DIMS, HB, HASJ, K, false, BITS>(a, count, lds, s)
+                        : launch_whole_a<DIMS, HB, HASJ, K, true, BITS>(a, count, lds, s);
+}
+
+// 16 sites per thread, a Philox block instead of two, where the waves are then
+// at most two per SIMD and each issues by itself, or where 32 sites per thread
+// leave half a wave idle.  us per sweep (32 sites per thread): 64^2 1.14 (1.43),
+// 80^2 1.24 (1.62), 128^2 1.59 (1.74), 12^3 heat-bath 1.42 (1.75), 16^3 +-J 1.50
+// (1.80), 4096 of 32^2 2.41 (3.24); beyond, 30^3 +-J 3.24 (2.92), 32^3 3.08
+// (2.61), 4096 of 64^2 4.5 (3.4), 2048 of 128^2 8.4 (6.7).
+static bool whole_halves(uint32_t words, int count)
+{
+    constexpr uint32_t kCUs = 256;
+    return words <= 32 || words * (((uint32_t)count + kCUs - 1) / kCUs) <= 256;
 }
 
 template <int DIMS, bool HB, bool HASJ>
 static hipError_t launch_whole_k(const WholeArgs &a, int count, size_t lds, hipStream_t s)
 {
-    const unsigned threads = std::min(1024u, (a.words + 63u) & ~63u);
-    return a.words <= 1024u ? launch_whole_t<DIMS, HB, HASJ, 1>(a, count, threads, lds, s)
-                            : launch_whole_t<DIMS, HB, HASJ, 2>(a, count, threads, lds, s);
+    if (whole_halves(a.words, count)) return launch_whole_t<DIMS, HB, HASJ, 1, 16>(a, count, lds, s);
+    return a.words <= 1024u ? launch_whole_t<DIMS, HB, HASJ, 1, 32>(a, count, lds, s)
+                            : launch_whole_t<DIMS, HB, HASJ, 2, 32>(a, count, lds, s);
 }
 
 // Every sweep of a call, one workgroup per lattice.

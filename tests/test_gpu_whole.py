@@ -100,6 +100,31 @@ def test_lattices_of_the_tiles_shapes(ctx, dims, shape, rule, J):
     _check(ctx, dims, shape, 2, rule, J, True, nsw=9, with_ws=True)
 
 
+@pytest.mark.parametrize("dims,shape,J", [(2, (34, 18), False), (2, (64, 64), False), (2, (66, 62), True),
+                                          (3, (12, 12, 12), True), (2, (16, 8), False)])
+def test_many_lattices(ctx, dims, shape, J):
+    """Enough lattices that a thread takes 32 sites: samples against the same
+    lattices in a call of three (16 sites), which other tests compare with the
+    oracle."""
+    seed, count, nsw = 43, 1100, 3
+    g = mcs.make_geom(dims, shape, count=count)
+    lat = mcs.lattice_tensor(g)
+    ctx.init(g, lat, mcs.HOT, seed, 0)
+    Jt = None
+    if J:
+        Jt = torch.empty(dims * g.N, dtype=torch.int8, device="cuda")
+        ctx.couplings(g, Jt, seed + 1)
+    g3 = mcs.make_geom(dims, shape, count=3)
+    few = lat.view(count, -1)[500:503].clone()
+    EM = torch.empty((nsw, count, 2), dtype=torch.int64, device="cuda")
+    EM3 = torch.empty((nsw, 3, 2), dtype=torch.int64, device="cuda")
+    ctx.sweep(g, lat, 0.5, seed, nsw, J=Jt, EM=EM)
+    ctx.sweep(g3, few, 0.5, seed, nsw, replica0=500, J=Jt, EM=EM3)
+    torch.cuda.synchronize()
+    assert torch.equal(lat.view(count, -1)[500:503], few.view(3, -1))
+    assert torch.equal(EM[:, 500:503], EM3)
+
+
 @pytest.mark.parametrize("beta", [0.0, 0.05, 3.0])
 @pytest.mark.parametrize("rule", [0, 1])
 def test_extreme_temperatures(ctx, beta, rule):
