@@ -38,13 +38,16 @@
 //
 // What bounds it: VALU issue, about 170 instructions of a wave per 64 words of
 // 32 sites (74 of them Philox) and 55 per settled batch of ties, then the
-// barriers' and the launch's latency.  Three 4096^2 lattices, bands of 16 rows,
-// 2 sweeps per launch, 512 threads, (E, M) every sweep: 15.1 us per sweep
-// against 17.8 with a comparison per class, both sideways words read, and ties
-// settled by the whole workgroup between two barriers.
+// barriers' and the launch's latency.  Three 4096^2 lattices, (E, M) every
+// sweep, us per sweep: bands of 16 rows, 2 sweeps per launch, 512 threads 14.6,
+// 15.1 with one word in flight per thread while the band loads and a serial sum
+// over the waves each sweep, 17.8 with a comparison per class, both sideways
+// words read, and ties settled by the whole workgroup between two barriers
+// besides; bands of 49 rows, 4 per launch, 1024 threads 13.4.
 #include "em_slots.hpp"
 #include "internal.hpp"
 #include "metro2d.hpp"
+#include "spin_bytes.hpp"
 
 namespace mcs {
 
@@ -66,7 +69,7 @@ template <int K, bool MEASURE>
 __global__ __launch_bounds__(1024) void k_tile2d(Tile2DArgs a)
 {
     extern __shared__ uint32_t lds[];
-    __shared__ int red[2][16];
+    __shared__ int sums[2][K > 0 ? K : 1];  // anti-aligned bonds and down spins of each sweep
     __shared__ long long red64[2][16];
     const int l = blockIdx.y;
     const int y0 = blockIdx.x * a.H;
@@ -101,7 +104,8 @@ __global__ __launch_bounds__(1024) void k_tile2d(Tile2DArgs a)
         while (y >= a.Ly) y -= a.Ly;
         return y;
     };
-    const int wave = tid >> 6, nwaves = nt >> 6;
+    const int wave = tid >> 6;
+    if (MEASURE && tid < 2 * K) sums[tid & 1][tid >> 1] = 0;
     uint4 *const tq = (uint4 *)(lds + ((rows * 2 * Wd + 3) & ~3)) + wave * kTieQueue;
     const int ntile = gridDim.x, nlat = gridDim.y;
     long long pre_e, pre_m;
@@ -111,35 +115,26 @@ __global__ __launch_bounds__(1024) void k_tile2d(Tile2DArgs a)
     if (a.in_packed) {
         // packed row y of lattice l: 2 Wd words at (l Ly + y) 2 Wd, even array first
         const uint2 *src = (const uint2 *)a.src + (int64_t)l * a.Ly * Wd;
-        for (int r = r0; r < rows; r += Q) {
-            const uint2 *row = src + (int64_t)lat_row(r) * Wd;
-            for (int w = w0; w < Wd; w += P) ((uint2 *)lds)[r * Wd + w] = row[w];
-        }
+        constexpr int kBatch = 8;  // words of a thread in flight at once
+        for (int w = w0; w < Wd; w += P)
+            for (int rb = r0; rb < rows; rb += kBatch * Q) {
+                uint2 v[kBatch];
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j)
+                    if (rb + j * Q < rows) v[j] = src[(int64_t)lat_row(rb + j * Q) * Wd + w];
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j)
+                    if (rb + j * Q < rows) ((uint2 *)lds)[(rb + j * Q) * Wd + w] = v[j];
+            }
     } else {
         // int8: sign bit of each byte, even-x sites to array 0, odd-x to array 1
         const int8_t *src = (const int8_t *)a.src + (int64_t)l * a.N;
         for (int r = r0; r < rows; r += Q) {
             const int8_t *row = src + (int64_t)lat_row(r) * a.Lx;
             for (int w = w0; w < Wd; w += P) {
-                const uint4 *p = (const uint4 *)(row + 64 * w);
-                uint32_t ev = 0, od = 0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint4 v = p[q];
-                    const uint32_t dw[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        // sign bits at 7, 15, 23, 31 -> m + (m << 15) puts the two
-                        // even-x bits at 22..23 and the two odd-x bits at 30..31
-                        const uint32_t m = dw[i] & 0x80808080u;
-                        const uint32_t Pm = m + (m << 15);
-                        const int sh = 2 * (4 * q + i);
-                        ev |= ((Pm >> 22) & 3u) << sh;
-                        od |= (Pm >> 30) << sh;
-                    }
-                }
-                lds[widx(r, 0, w)] = ev;
-                lds[widx(r, 1, w)] = od;
+                const Row32 h0 = load_row32(row, 64u * w), h1 = load_row32(row, 64u * w + 32u);
+                lds[widx(r, 0, w)] = sign_bits16(pick16(h0, 0x06040200u)) | sign_bits16(pick16(h1, 0x06040200u)) << 16;
+                lds[widx(r, 1, w)] = sign_bits16(pick16(h0, 0x07050301u)) | sign_bits16(pick16(h1, 0x07050301u)) << 16;
             }
         }
     }
@@ -228,26 +223,18 @@ __global__ __launch_bounds__(1024) void k_tile2d(Tile2DArgs a)
             }
             settle();
             if (MEASURE && c == 1) {
-                n_acc = wave_sum_last(n_acc);
-                d_acc = wave_sum_last(d_acc);
-                if ((tid & 63) == 63) {
-                    red[0][wave] = n_acc;
-                    red[1][wave] = d_acc;
-                }
+                n_acc = __builtin_amdgcn_readlane(wave_sum_last(n_acc), 63);
+                d_acc = __builtin_amdgcn_readlane(wave_sum_last(d_acc), 63);
+                if ((tid & 63) < 2) atomicAdd(&sums[tid & 1][s], (tid & 1) ? d_acc : n_acc);
             }
             __syncthreads();
         }
-        if (MEASURE && tid == 0) {
-            long long n = 0, d = 0;
-            for (int i = 0; i < nwaves; ++i) {
-                n += red[0][i];
-                d += red[1][i];
-            }
-            // every bond once: 2 (anti-aligned) - 4 per odd site; M from both parities
-            const long long words = (long long)Hh * Wd;
-            *em_slot(a.em.slots, s, l, nlat, blockIdx.x, ntile) =
-                make_longlong2(2 * n - 128 * words, 64 * words - 2 * d);
-        }
+    }
+    if (MEASURE && tid < K) {
+        // every bond once: 2 (anti-aligned) - 4 per odd site; M from both parities
+        const long long words = (long long)Hh * Wd;
+        *em_slot(a.em.slots, tid, l, nlat, blockIdx.x, ntile) =
+            make_longlong2(2ll * sums[0][tid] - 128 * words, 64 * words - 2ll * sums[1][tid]);
     }
 
     // ---- store the band's own rows
@@ -269,13 +256,13 @@ __global__ __launch_bounds__(1024) void k_tile2d(Tile2DArgs a)
             for (int q = 0; q < 4; ++q) {
                 uint32_t dw[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int sh = 2 * (4 * q + i);
-                    // bytes: x = 16q+4i (even bit sh), +1 (odd bit sh), +2 (even sh+1), +3 (odd sh+1)
-                    const uint32_t bits = ((ev >> sh) & 1u) | (((od >> sh) & 1u) << 8) |
-                                          (((ev >> (sh + 1)) & 1u) << 16) | (((od >> (sh + 1)) & 1u) << 24);
-                    // bit 0 -> byte 0x01 (+1), bit 1 -> byte 0xFF (-1)
-                    dw[i] = __builtin_amdgcn_perm(0u, 0x0000FF01u, bits);
+                for (int i = 0; i < 2; ++i) {
+                    // four even and four odd columns, bit 0 -> byte 0x01 (+1), 1 -> 0xFF (-1)
+                    const int sh = 8 * q + 4 * i;
+                    const uint32_t ee = 0x01010101u ^ (spread4((ev >> sh) & 15u) * 0xFEu);
+                    const uint32_t oo = 0x01010101u ^ (spread4((od >> sh) & 15u) * 0xFEu);
+                    dw[2 * i] = __builtin_amdgcn_perm(oo, ee, 0x05010400u);
+                    dw[2 * i + 1] = __builtin_amdgcn_perm(oo, ee, 0x07030602u);
                 }
                 p[q] = make_uint4(dw[0], dw[1], dw[2], dw[3]);
             }
