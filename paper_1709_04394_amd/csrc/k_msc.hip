@@ -53,16 +53,18 @@ struct MscArgs {
     int64_t *EM;  // this sweep's [count * 64][2], or nullptr
 };
 
+constexpr int kMscWaves = 16;  // of a workgroup that measures, at most
 constexpr int kMscFlush = 32;  // tasks between sums of the bit-sliced counters
 
 template <int DIMS, bool MEASURE, bool HB, bool HASJ>
-__global__ __launch_bounds__(256) void k_msc(MscArgs a)
+__global__ __launch_bounds__(MEASURE ? 64 * kMscWaves : 256) void k_msc(MscArgs a)
 {
+    constexpr int WAVES = MEASURE ? kMscWaves : 4;
     __shared__ uint32_t tlow[8];
     __shared__ long long red[2][64];
     // tied words: {word, same-colour index, tied replicas}, {word with those
     // unsettled, class bit 0}, {class bits 1, 2}
-    __shared__ uint4 q_id[4][kTieQueue], q_s[4][kTieQueue], q_c[(HB || DIMS == 3) ? 4 : 1][kTieQueue];
+    __shared__ uint4 q_id[WAVES][kTieQueue], q_s[WAVES][kTieQueue], q_c[(HB || DIMS == 3) ? WAVES : 1][kTieQueue];
     constexpr int Z = 2 * DIMS;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = blockIdx.y;
@@ -129,7 +131,8 @@ __global__ __launch_bounds__(256) void k_msc(MscArgs a)
         cd.clear();
     }
     uint32_t done = 0;
-    for (uint32_t t = xcd_order(blockIdx.x, gridDim.x) * 4u + (uint32_t)wave; t < tasks; t += gridDim.x * 4u) {
+    const uint32_t waves = MEASURE ? blockDim.x >> 6 : 4u;
+    for (uint32_t t = xcd_order(blockIdx.x, gridDim.x) * waves + (uint32_t)wave; t < tasks; t += gridDim.x * waves) {
         const uint32_t j0 = t << 6;
         const uint32_t row = t / per_row, m0 = (t - row * per_row) << 6;
         const uint32_t z = row / (uint32_t)a.Ly, y = row - z * (uint32_t)a.Ly;
@@ -253,8 +256,7 @@ __global__ __launch_bounds__(256) void k_msc(MscArgs a)
         atomicAdd((unsigned long long *)&red[1][lb.label], (unsigned long long)mg);
         __syncthreads();
         if (tid < 128) {
-            const int q = tid >> 6, b = tid & 63;
-            atomicAdd((unsigned long long *)&a.EM[2 * (64 * (int64_t)l + b) + q], (unsigned long long)red[q][b]);
+            atomicAdd((unsigned long long *)&a.EM[128 * (int64_t)l + tid], (unsigned long long)red[tid & 1][tid >> 1]);
         }
     }
 }
@@ -269,12 +271,22 @@ template <int D, bool HB, bool HJ>
 static hipError_t launch_msc_t(const MscArgs &a, int count, hipStream_t s)
 {
     const int64_t tasks = (a.N >> 1) >> 6;
-    // as many waves as fit at once (four per SIMD with the counters' registers,
-    // else eight), each walking its share of the tasks
-    const int64_t blocks = std::min<int64_t>((tasks + 3) / 4, a.EM ? 1024 : 2048);
-    dim3 grid((unsigned)blocks, (unsigned)count);
-    if (a.EM) hipLaunchKernelGGL((k_msc<D, true, HB, HJ>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_msc<D, false, HB, HJ>), grid, dim3(256), 0, s, a);
+    // Without E, M as many waves as fit at once (eight per SIMD), each walking
+    // its share of the tasks.  With them one workgroup per CU of up to sixteen
+    // waves, as few as give every task one: each workgroup adds 128 numbers to
+    // the same eight lines, which takes 1024 workgroups 40 us whatever the
+    // lattice (us per sweep at four waves each: 512 x 1024 57.8, now 24.2;
+    // 1024^2 66, 35; 128 x 64^2 heat-bath 60, 26; 4096^2 296, 296).
+    if (!a.EM) {
+        const dim3 grid((unsigned)std::min<int64_t>((tasks + 3) / 4, 2048), (unsigned)count);
+        hipLaunchKernelGGL((k_msc<D, false, HB, HJ>), grid, dim3(256), 0, s, a);
+        return hipGetLastError();
+    }
+    constexpr int64_t kCUs = 256;
+    int waves = 4;
+    while (waves < kMscWaves && tasks > kCUs * waves) waves *= 2;
+    const dim3 grid((unsigned)std::min<int64_t>((tasks + waves - 1) / waves, kCUs), (unsigned)count);
+    hipLaunchKernelGGL((k_msc<D, true, HB, HJ>), grid, dim3(64 * waves), 0, s, a);
     return hipGetLastError();
 }
 

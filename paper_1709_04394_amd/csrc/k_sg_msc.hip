@@ -213,9 +213,9 @@ __global__ __launch_bounds__(256, 5) void k_sg_msc(SgMscArgs a)
         red[1][wave][lb.label] = 128 * (int)done - 2 * d_acc;
         __syncthreads();
         if (tid < 128) {
-            const int q = tid >> 6, b = tid & 63;
+            const int q = tid & 1, b = tid >> 1;
             const long long v = (long long)red[q][0][b] + red[q][1][b] + red[q][2][b] + red[q][3][b];
-            atomicAdd((unsigned long long *)&a.EM[2 * (64 * (int64_t)l + b) + q], (unsigned long long)v);
+            atomicAdd((unsigned long long *)&a.EM[128 * (int64_t)l + tid], (unsigned long long)v);
         }
     }
 }
