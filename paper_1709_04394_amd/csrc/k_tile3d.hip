@@ -28,11 +28,14 @@
 // What bounds it: VALU issue (heat-bath about 230 instructions of a wave per 64
 // words of 32 sites, Metropolis 190) with the redone halo (1.4 times at H = 16,
 // K = 2), then the half-sweeps' latency where a CU has one tile.  256^3 x 4
-// heat-bath, 16, 2, 256 threads: 30.0 us per sweep against 38.8 with the
-// thresholds read from LDS for every plane, rows found by division and wrapped
-// in loops, and ties settled between two barriers; 256^3 13.3 against 17.2.
+// heat-bath, H = 16, K = 1, 256 threads: 28.4 us per sweep, 30.4 with a
+// tile's rows loaded one after the other, each by its own division, and a
+// serial sum over the waves each sweep; at K = 2 with the thresholds read from
+// LDS for every plane and ties settled between two barriers besides 38.8.
+// 256^3 alone, 768 threads: 12.3, 13.1 and 17.2.
 #include "internal.hpp"
 #include "metro2d.hpp"
+#include "spin_bytes.hpp"
 
 namespace mcs {
 
@@ -81,7 +84,7 @@ template <int K, bool MEASURE, bool HB, bool HASJ>
 __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
 {
     extern __shared__ uint32_t lds[];
-    __shared__ int red[2][16];
+    __shared__ int sums[2][K > 0 ? K : 1];  // anti-aligned bonds and down spins of each sweep
     __shared__ long long red64[2][16];
     __shared__ uint32_t tlow[8];
     const int l = blockIdx.y;
@@ -115,27 +118,19 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
         ts[k][2] = ((a.top[li][5] >> k) & 1u) ? ~0u : 0u;
         ts[k][3] = ((a.top[li][6] >> k) & 1u) ? ~0u : 0u;
     }
-    // thread -> (word column, first row, row stride)
-    int P, Q, w0, r0;
-    if (Wd <= nt) {
-        P = Wd;
-        Q = nt / Wd;
-        w0 = tid % Wd;
-        r0 = tid / Wd;
-        if (r0 >= Q) r0 = 1 << 28;
-    } else {
-        P = nt;
-        Q = 1;
-        w0 = tid;
-        r0 = 0;
-    }
+    // thread -> (word column, first row, row stride); a row's words are at most
+    // the threads
+    const int Q = nt / Wd, w0 = tid % Wd, r0 = tid / Wd;
+    const bool own = r0 < Q;  // surplus threads idle
     auto widx = [&](int row, int par, int w) { return (row * 2 + par) * Wd + w; };
     auto wrap = [](int v, int n) {
+        if (n >= R) return v < 0 ? v + n : v >= n ? v - n : v;
         while (v < 0) v += n;
         while (v >= n) v -= n;
         return v;
     };
-    const int wave = tid >> 6, nwaves = nt >> 6;
+    const int wave = tid >> 6;
+    if (MEASURE && tid < 2 * K) sums[tid & 1][tid >> 1] = 0;
     uint4 *const tq = (uint4 *)(lds + (((size_t)rows * (2 * Wd * (HASJ ? 4 : 1) + 1) + 3) & ~(size_t)3)) +
                       wave * (kTieQueue * 3 / 2);
     uint2 *const tq2 = (uint2 *)(tq + kTieQueue);
@@ -145,55 +140,68 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
     em_prefetch(a.em, blockIdx.x, ntile, l, nlat, tid, pre_e, pre_m);
 
     // ---- load rows (z0-R .. z1+R-1) x (y0-R .. y1+R-1), row id = rz Ry + ry
-    const float invRy = 1.0f / (float)Ry;
-    for (int rr = r0; rr < rows; rr += Q) {
+    {
+        const float invRy = 1.0f / (float)Ry;
+        const int sz = Q / Ry, sy = Q - sz * Ry;  // a step of Q rows
         int rz, ry;
-        divmod_small(rr, Ry, invRy, rz, ry);
-        const int y = wrap(y0 - R + ry, a.Ly), z = wrap(z0 - R + rz, a.Lz);
-        const int64_t grow = (int64_t)z * a.Ly + y;
-        if (a.in_packed) {
-            const uint2 *src = (const uint2 *)a.src + ((int64_t)l * plane_rows + grow) * Wd;
-            for (int w = w0; w < Wd; w += P) ((uint2 *)lds)[rr * Wd + w] = src[w];
-        } else {
-            const int8_t *row = (const int8_t *)a.src + (int64_t)l * a.N + grow * a.Lx;
-            for (int w = w0; w < Wd; w += P) {
-                const uint4 *p = (const uint4 *)(row + 64 * w);
-                uint32_t ev = 0, od = 0;
+        divmod_small(own ? r0 : 0, Ry, invRy, rz, ry);
+        constexpr int kBatch = 4;  // rows of a thread in flight at once
+        for (int base = 0; base < rows; base += kBatch * Q) {
+            const int rb = own ? base + r0 : rows;
+            uint32_t at[kBatch];  // word in the lattice
 #pragma unroll
-                for (int qq = 0; qq < 4; ++qq) {
-                    const uint4 v = p[qq];
-                    const uint32_t dw[4] = {v.x, v.y, v.z, v.w};
+            for (int j = 0; j < kBatch; ++j) {
+                if (base + j * Q >= rows) break;
+                const int y = wrap(y0 - R + ry, a.Ly), z = wrap(z0 - R + rz, a.Lz);
+                const uint32_t grow = (uint32_t)z * (uint32_t)a.Ly + (uint32_t)y;
+                at[j] = grow * (uint32_t)Wd + (uint32_t)w0;
+                if (w0 == 0 && rb + j * Q < rows)
+                    rinfo[rb + j * Q] = (uint32_t)(a.Lx >> 5) * grow | ((uint32_t)(y + z) & 1u);
+                rz += sz;
+                ry += sy;
+                if (ry >= Ry) {
+                    ry -= Ry;
+                    ++rz;
+                }
+            }
+            auto copy = [&](const uint2 *src, uint2 *dst) {
+                uint2 v[kBatch];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint32_t m = dw[i] & 0x80808080u;
-                        const uint32_t Pm = m + (m << 15);
-                        const int sh = 2 * (4 * qq + i);
-                        ev |= ((Pm >> 22) & 3u) << sh;
-                        od |= (Pm >> 30) << sh;
+                for (int j = 0; j < kBatch; ++j) {
+                    if (base + j * Q >= rows) break;
+                    if (rb + j * Q < rows) v[j] = src[at[j]];
+                }
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    if (base + j * Q >= rows) break;
+                    if (rb + j * Q < rows) dst[(rb + j * Q) * Wd + w0] = v[j];
+                }
+            };
+            if (a.in_packed) {
+                copy((const uint2 *)a.src + (int64_t)l * plane_rows * Wd, (uint2 *)lds);
+            } else {
+                const int8_t *src = (const int8_t *)a.src + (int64_t)l * a.N;
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    if (base + j * Q >= rows) break;
+                    if (rb + j * Q < rows) {
+                        const int8_t *p = src + 64 * (int64_t)at[j];
+                        const Row32 h0 = load_row32(p, 0u), h1 = load_row32(p, 32u);
+                        lds[widx(rb + j * Q, 0, w0)] =
+                            sign_bits16(pick16(h0, 0x06040200u)) | sign_bits16(pick16(h1, 0x06040200u)) << 16;
+                        lds[widx(rb + j * Q, 1, w0)] =
+                            sign_bits16(pick16(h0, 0x07050301u)) | sign_bits16(pick16(h1, 0x07050301u)) << 16;
                     }
                 }
-                lds[widx(rr, 0, w)] = ev;
-                lds[widx(rr, 1, w)] = od;
             }
+            if (HASJ)
+                for (int d = 0; d < 3; ++d)
+                    copy((const uint2 *)a.Jp + (int64_t)d * plane_rows * Wd, (uint2 *)Jl + (size_t)d * rows * Wd);
         }
-        if (HASJ) {
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const uint2 *src = (const uint2 *)a.Jp + ((int64_t)d * plane_rows + grow) * Wd;
-                for (int w = w0; w < Wd; w += P) ((uint2 *)Jl)[((size_t)d * rows + rr) * Wd + w] = src[w];
-            }
-        }
-    }
-    for (int rr = tid; rr < rows; rr += nt) {
-        int rz, ry;
-        divmod_small(rr, Ry, invRy, rz, ry);
-        const int y = wrap(y0 - R + ry, a.Ly), z = wrap(z0 - R + rz, a.Lz);
-        rinfo[rr] = (uint32_t)(a.Lx >> 5) * (uint32_t)((int64_t)z * a.Ly + y) | ((uint32_t)(y + z) & 1u);
     }
     __syncthreads();
     em_reduce(a.em, blockIdx.x, ntile, l, nlat, tid, nt, pre_e, pre_m, red64);
 
-    const bool own = r0 < (1 << 28);
     for (int s = 0; s < K; ++s) {
         const uint64_t sweep = a.sweep0 + (uint64_t)s;
         int n_acc = 0, d_acc = 0;  // anti-aligned bonds and down spins of this thread's own words
@@ -362,57 +370,54 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
             }
             settle();
             if (MEASURE && c == 1) {
-                n_acc = wave_sum_last(n_acc);
-                d_acc = wave_sum_last(d_acc);
-                if ((tid & 63) == 63) {
-                    red[0][wave] = n_acc;
-                    red[1][wave] = d_acc;
-                }
+                n_acc = __builtin_amdgcn_readlane(wave_sum_last(n_acc), 63);
+                d_acc = __builtin_amdgcn_readlane(wave_sum_last(d_acc), 63);
+                if ((tid & 63) < 2) atomicAdd(&sums[tid & 1][s], (tid & 1) ? d_acc : n_acc);
             }
             __syncthreads();
         }
-        if (MEASURE && tid == 0) {
-            long long n = 0, d = 0;
-            for (int i = 0; i < nwaves; ++i) {
-                n += red[0][i];
-                d += red[1][i];
-            }
-            // every bond once: 2 (anti-aligned) - 6 per odd site; M from both parities
-            const long long words = (long long)hy * hz * Wd;
-            *em_slot(a.em.slots, s, l, nlat, blockIdx.x, ntile) =
-                make_longlong2(2 * n - 192 * words, 64 * words - 2 * d);
-        }
+    }
+    if (MEASURE && tid < K) {
+        // every bond once: 2 (anti-aligned) - 6 per odd site; M from both parities
+        const long long words = (long long)hy * hz * Wd;
+        *em_slot(a.em.slots, tid, l, nlat, blockIdx.x, ntile) =
+            make_longlong2(2ll * sums[0][tid] - 192 * words, 64 * words - 2ll * sums[1][tid]);
     }
 
     // ---- store the tile's own rows
-    const int own_rows = hy * hz;
-    const float invhy = 1.0f / (float)hy;
+    if (!own) return;
+    const int own_rows = hy * hz, sz = Q / hy, sy = Q - sz * hy;
+    int iz, iy;
+    divmod_small(r0, hy, 1.0f / (float)hy, iz, iy);
     for (int rr = r0; rr < own_rows; rr += Q) {
-        int iz, iy;
-        divmod_small(rr, hy, invhy, iz, iy);
         const int row = (R + iz) * Ry + (R + iy);
         const int64_t grow = (int64_t)(z0 + iz) * a.Ly + (y0 + iy);
         if (a.out_packed) {
             uint2 *dst = (uint2 *)a.dst + ((int64_t)l * plane_rows + grow) * Wd;
-            for (int w = w0; w < Wd; w += P) dst[w] = ((const uint2 *)lds)[row * Wd + w];
+            dst[w0] = ((const uint2 *)lds)[row * Wd + w0];
         } else {
-            int8_t *rowp = (int8_t *)a.dst + (int64_t)l * a.N + grow * a.Lx;
-            for (int w = w0; w < Wd; w += P) {
-                const uint32_t ev = lds[widx(row, 0, w)], od = lds[widx(row, 1, w)];
-                uint4 *pp = (uint4 *)(rowp + 64 * w);
+            const uint32_t ev = lds[widx(row, 0, w0)], od = lds[widx(row, 1, w0)];
+            uint4 *pp = (uint4 *)((int8_t *)a.dst + (int64_t)l * a.N + grow * a.Lx + 64 * w0);
 #pragma unroll
-                for (int qq = 0; qq < 4; ++qq) {
-                    uint32_t dw[4];
+            for (int qq = 0; qq < 4; ++qq) {
+                uint32_t dw[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int sh = 2 * (4 * qq + i);
-                        const uint32_t bits = ((ev >> sh) & 1u) | (((od >> sh) & 1u) << 8) |
-                                              (((ev >> (sh + 1)) & 1u) << 16) | (((od >> (sh + 1)) & 1u) << 24);
-                        dw[i] = __builtin_amdgcn_perm(0u, 0x0000FF01u, bits);
-                    }
-                    pp[qq] = make_uint4(dw[0], dw[1], dw[2], dw[3]);
+                for (int i = 0; i < 2; ++i) {
+                    // four even and four odd columns, bit 0 -> byte 0x01 (+1), 1 -> 0xFF (-1)
+                    const int sh = 8 * qq + 4 * i;
+                    const uint32_t ee = 0x01010101u ^ (spread4((ev >> sh) & 15u) * 0xFEu);
+                    const uint32_t oo = 0x01010101u ^ (spread4((od >> sh) & 15u) * 0xFEu);
+                    dw[2 * i] = __builtin_amdgcn_perm(oo, ee, 0x05010400u);
+                    dw[2 * i + 1] = __builtin_amdgcn_perm(oo, ee, 0x07030602u);
                 }
+                pp[qq] = make_uint4(dw[0], dw[1], dw[2], dw[3]);
             }
+        }
+        iz += sz;
+        iy += sy;
+        if (iy >= hy) {
+            iy -= hy;
+            ++iz;
         }
     }
 }

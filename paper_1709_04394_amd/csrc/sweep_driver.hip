@@ -114,8 +114,8 @@ static TilePlan plan_for(mc_ctx *ctx, const Geom &g)
 // plan: as in 2D (below), with 0.15 us for every 64 words (the class
 // multiplexers) and a tile's halo on both sides in y and z.  Measured (and
 // modelled), us per sweep, heat-bath: 256^3 x 4, H = 16, K = 2 32 (33); 256^3
-// 12.7 (12); 128^3, the chosen 8, 3 6.4 (6.1), the nominal 16, 2 (64 tiles) 9.2
-// (8.8); 64^3, 4, 4 5.2 (4.6), 16, 2 7.6 (7.1).
+// 12.3 (12); 128^3, the chosen 8, 3 6.2 (6.1), the nominal 16, 2 (64 tiles) 9.2
+// (8.8); 64^3, 4, 4 4.9 (4.6), 16, 2 7.6 (7.1).
 static TilePlan call_plan_3d(const Geom &g, int n)
 {
     constexpr int kCUs = 256;
