@@ -13,28 +13,27 @@
 //    of replica b for the 4 groups of 16 sites the wave covers, whose
 //    half-words are the random bit-planes of those sites (the stream the int8
 //    kernels use, so lane b of the word lattice equals the int8 run of that
-//    replica bit for bit).  A 64 x 64 bit transpose of all eight planes at once
-//    (lane_bits.hpp) turns "replica b, 64 sites" into "site s, 64 replicas";
-//    then each lane compares its site's 64 replicas against their classes'
-//    thresholds bit-serially.
-//  * Words with ties (a replica whose top byte equals its class's threshold's,
-//    one word in seven at criticality) wait in a queue of their wave, across
-//    tasks, and are settled 64 at a time, one word per lane; their spins are
-//    stored then.
+//    replica bit for bit).  The sites' classes, two to four bits per site and
+//    replica, are transposed to lanes that are replicas (64 x 64 bits per class
+//    bit, lane_bits.hpp), compared there bit-serially with the class's threshold
+//    where the planes already are, and the outcome is transposed back: three to
+//    five transposes instead of the eight planes'.
+//  * A tie (a replica whose top byte equals its class's threshold's) is drawn by
+//    its replica's lane before that: about one in five has one.
 //  * Per-sweep E and M per replica are counted in the odd half-sweep: each lane
 //    adds the unsatisfied bonds and down spins of its sites to bit-sliced
 //    counters of the 64 replicas, which are summed over the lanes once in 32
 //    tasks; one atomic per replica and workgroup.
 //
-// What bounds it: VALU issue.  4096^2, 64 replicas, Metropolis: 133 us per
-// even half-sweep and 173 with E, M, against 238 and 311 with a transpose per
-// plane through ds_swizzle (36 instructions per word), a transpose back for
-// every count of every task, rows by 64-bit division, and ties drawn in place.
+// What bounds it: VALU issue.  4096^2, 64 replicas, Metropolis: 116 us per even
+// half-sweep and 147 with E, M; 133 and 173 with the planes transposed and ties
+// settled from a queue, 238 and 311 with a transpose per plane through
+// ds_swizzle (36 instructions per word), a transpose back for every count of
+// every task and rows by 64-bit division.
 #include <algorithm>
 
 #include "internal.hpp"
 #include "lane_bits.hpp"
-#include "metro2d.hpp"
 
 namespace mcs {
 
@@ -59,12 +58,8 @@ constexpr int kMscFlush = 32;  // tasks between sums of the bit-sliced counters
 template <int DIMS, bool MEASURE, bool HB, bool HASJ>
 __global__ __launch_bounds__(MEASURE ? 64 * kMscWaves : 256) void k_msc(MscArgs a)
 {
-    constexpr int WAVES = MEASURE ? kMscWaves : 4;
     __shared__ uint32_t tlow[8];
     __shared__ long long red[2][64];
-    // tied words: {word, same-colour index, tied replicas}, {word with those
-    // unsettled, class bit 0}, {class bits 1, 2}
-    __shared__ uint4 q_id[WAVES][kTieQueue], q_s[WAVES][kTieQueue], q_c[(HB || DIMS == 3) ? WAVES : 1][kTieQueue];
     constexpr int Z = 2 * DIMS;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = blockIdx.y;
@@ -89,39 +84,6 @@ __global__ __launch_bounds__(MEASURE ? 64 * kMscWaves : 256) void k_msc(MscArgs 
 #pragma unroll
         for (int i = 0; i < 4; ++i) ts[k][i] = ((a.top[i < 3 ? 2 * i + 1 : 6] >> k) & 1u) ? ~0u : 0u;
     }
-    uint32_t qn = 0;
-    auto settle = [&]() {
-        const uint32_t q = tid & 63;
-        if (q < qn) {
-            const uint4 id = q_id[wave][q], sw = q_s[wave][q];
-            uint4 cw = make_uint4(0u, 0u, 0u, 0u);
-            if (HB || DIMS == 3) cw = q_c[wave][q];
-            uint64_t pend = ((uint64_t)id.w << 32) | id.z, S = ((uint64_t)sw.y << 32) | sw.x;
-            const uint64_t c0 = ((uint64_t)sw.w << 32) | sw.z, c1 = ((uint64_t)cw.y << 32) | cw.x,
-                           c2 = ((uint64_t)cw.w << 32) | cw.z;
-            while (pend) {
-                const int b = __builtin_ctzll(pend);
-                pend &= pend - 1ull;
-                const uint32_t cls = (uint32_t)((c0 >> b) & 1ull) | ((uint32_t)((c1 >> b) & 1ull) << 1) |
-                                     ((uint32_t)((c2 >> b) & 1ull) << 2);
-                const uint4 lo =
-                    philox(make_uint4(id.y, rep0 + (uint32_t)b, a.sweep_lo, a.w3lo), a.seed_lo, a.seed_hi);
-                // Metropolis: flip; heat-bath: the provisional -1 becomes +1
-                if ((lo.x & 0xFFFFFFu) < tlow[cls]) {
-                    if (MEASURE) {
-                        // unsatisfied bonds gained: Metropolis z - 2a, heat-bath 2d - z
-                        const int du = HB ? 2 * (int)cls - Z : Z - 2 * (int)cls;
-                        atomicAdd((unsigned long long *)&red[0][b], (unsigned long long)(long long)(2 * du));
-                        atomicAdd((unsigned long long *)&red[1][b],
-                                  (unsigned long long)(((S >> b) & 1ull) ? 2ll : -2ll));
-                    }
-                    S ^= 1ull << b;
-                }
-            }
-            w[id.x] = S;
-        }
-        qn = 0;
-    };
     BitCounter<8> cu;  // unsatisfied bonds of the odd sites, up to 6 a task
     BitCounter<7> cd;  // down spins of both sites of a pair
     long long u_acc = 0, d_acc = 0;
@@ -150,13 +112,12 @@ __global__ __launch_bounds__(MEASURE ? 64 * kMscWaves : 256) void k_msc(MscArgs 
             n[4] = (w + rzp)[x];
             n[5] = (w + rzm)[x];
         }
-        // random planes: lane = replica, 4 groups of 16 sites -> transpose
+        // random blocks: lane = replica, 4 groups of 16 sites
         uint4 B[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g)
             B[g] = philox(make_uint4((j0 >> 4) + (uint32_t)g, rep0 + (uint32_t)lb.label, a.sweep_lo, a.w3), a.seed_lo,
                           a.seed_hi);
-        transpose_blocks(B, lb);
         uint64_t jm[6] = {0, 0, 0, 0, 0, 0};
         if (HASJ) {
             const int8_t *J = a.J;
@@ -169,72 +130,86 @@ __global__ __launch_bounds__(MEASURE ? 64 * kMscWaves : 256) void k_msc(MscArgs 
                 jm[5] = (J + 2 * a.N + rzm)[x] < 0 ? ~0ull : 0ull;
             }
         }
-        uint32_t So[2], pend[2], C0[2], C1[2], C2[2];
-        uint64_t u[3] = {0, 0, 0}, dn[2] = {0, 0};
+        // lane = site: classes of its 64 replicas, halves of 32
+        uint32_t C0[2], C1[2], C2[2], GE[2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {  // replicas 32 h .. 32 h + 31
+        for (int h = 0; h < 2; ++h) {
             const uint32_t Sh = (uint32_t)(S >> (32 * h));
-            // wk: bit set <=> J s_j = -1; Metropolis counts unsatisfied bonds
-            // S ^ wk, heat-bath counts wk
-            uint32_t wk[6], xk[6];
+            // n ^ jm: bit set <=> J s_j = -1; Metropolis counts unsatisfied bonds,
+            // heat-bath those
+            uint32_t xk[6];
 #pragma unroll
             for (int k = 0; k < Z; ++k) {
-                wk[k] = (uint32_t)((n[k] ^ jm[k]) >> (32 * h));
-                xk[k] = HB ? wk[k] : (wk[k] ^ Sh);
+                const uint32_t wk = (uint32_t)((n[k] ^ jm[k]) >> (32 * h));
+                xk[k] = HB ? wk : (wk ^ Sh);
             }
-            uint32_t c0, c1, c2;
-            count_words<Z>(xk, c0, c1, c2);
+            count_words<Z>(xk, C0[h], C1[h], C2[h]);
             // Metropolis: a >= z/2 gives dE <= 0
-            const uint32_t ge = HB ? 0u : DIMS == 3 ? MCS_BOP3(c2, c1, c0, MCS_A | (MCS_B & MCS_C)) : (c2 | c1);
+            GE[h] = HB ? 0u : DIMS == 3 ? MCS_BOP3(C2[h], C1[h], C0[h], MCS_A | (MCS_B & MCS_C)) : (C2[h] | C1[h]);
+        }
+        // lane = replica: its 64 sites
+        uint32_t c0[2], c1[2] = {0u, 0u}, c2[2] = {0u, 0u}, ge[2] = {0u, 0u}, acc[2], pq[2];
+        to_replicas(C0[0], C0[1], c0[0], c0[1], lb);
+        if (HB || DIMS == 3) to_replicas(C1[0], C1[1], c1[0], c1[1], lb);
+        if (HB) to_replicas(C2[0], C2[1], c2[0], c2[1], lb);
+        else to_replicas(GE[0], GE[1], ge[0], ge[1], lb);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
             uint32_t lt = 0u, eq = ~0u;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const uint32_t X = plane_pair(B[2 * h], B[2 * h + 1], k);
+                const uint32_t X = plane_pair(B[q], B[q + 2], k);
                 auto mux = [](uint32_t sel, uint32_t hi, uint32_t lo) {
                     return MCS_BOP3(sel, hi, lo, (MCS_A & MCS_B) | (~MCS_A & MCS_C));
                 };
-                uint32_t T = mux(c0, ts[k][0], tv[k][0]);  // classes 0, 1
+                uint32_t T = mux(c0[q], ts[k][0], tv[k][0]);  // classes 0, 1
                 if (HB) {
-                    T = mux(c1, mux(c0, ts[k][1], tv[k][1]), T);
-                    T = DIMS == 3 ? mux(c2, mux(c1, ts[k][3], mux(c0, ts[k][2], tv[k][2])), T) : mux(c2, tv[k][2], T);
+                    T = mux(c1[q], mux(c0[q], ts[k][1], tv[k][1]), T);
+                    T = DIMS == 3 ? mux(c2[q], mux(c1[q], ts[k][3], mux(c0[q], ts[k][2], tv[k][2])), T)
+                                  : mux(c2[q], tv[k][2], T);
                 } else if (DIMS == 3) {
-                    T = mux(c1, tv[k][1], T);
+                    T = mux(c1[q], tv[k][1], T);
                 }
                 lt = MCS_BOP3(X, T, lt, (~MCS_A & MCS_B) | (~MCS_A & MCS_C) | (MCS_B & MCS_C));
                 eq = MCS_BOP3(eq, X, T, MCS_A & ~(MCS_B ^ MCS_C));
             }
-            So[h] = HB ? ~lt : MCS_BOP3(Sh, ge, lt, MCS_A ^ (MCS_B | MCS_C));
-            pend[h] = HB ? eq : (eq & ~ge);
-            C0[h] = c0;
-            C1[h] = c1;
-            C2[h] = c2;
-            if (MEASURE) {
-                // odd sites: their bonds after the update; both sites of the pair
-                // (this odd site and the even site at the same row position) for M
+            acc[q] = lt | ge[q];
+            pq[q] = eq & ~ge[q];
+        }
+        for (uint64_t pend = ((uint64_t)pq[1] << 32) | pq[0]; pend; pend &= pend - 1ull) {
+            const uint32_t i = (uint32_t)__builtin_ctzll(pend), b = i & 31u;
+            const bool up = i >= 32u;
+            const uint32_t cls = (((up ? c0[1] : c0[0]) >> b) & 1u) | ((((up ? c1[1] : c1[0]) >> b) & 1u) << 1) |
+                                 ((((up ? c2[1] : c2[0]) >> b) & 1u) << 2);
+            const uint4 lo = philox(make_uint4(j0 + site_of_bit(i), rep0 + (uint32_t)lb.label, a.sweep_lo, a.w3lo),
+                                    a.seed_lo, a.seed_hi);
+            const uint32_t f = (lo.x & 0xFFFFFFu) < tlow[cls] ? 1u << b : 0u;
+            acc[0] |= up ? 0u : f;
+            acc[1] |= up ? f : 0u;
+        }
+        // back to lane = site; Metropolis: flip, heat-bath: up where accepted
+        uint32_t A[2];
+        to_sites(acc[0], acc[1], A[0], A[1], lb);
+        const uint64_t So = HB ? ~(((uint64_t)A[1] << 32) | A[0]) : S ^ (((uint64_t)A[1] << 32) | A[0]);
+        (w + rbase)[x] = So;
+        uint64_t u[3] = {0, 0, 0}, dn[2] = {0, 0};
+        if (MEASURE) {
+            // odd sites: their bonds after the update; both sites of the pair
+            // (this odd site and the even site at the same row position) for M
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
                 uint32_t uk[6], v0, v1, v2;
 #pragma unroll
-                for (int k = 0; k < Z; ++k) uk[k] = So[h] ^ wk[k];
+                for (int k = 0; k < Z; ++k) uk[k] = (uint32_t)((So ^ n[k] ^ jm[k]) >> (32 * h));
                 count_words<Z>(uk, v0, v1, v2);
-                const uint32_t pw = (uint32_t)((par ? n[1] : n[0]) >> (32 * h));  // even site 2m + (1 - par)
                 u[0] |= (uint64_t)v0 << (32 * h);
                 u[1] |= (uint64_t)v1 << (32 * h);
                 u[2] |= (uint64_t)v2 << (32 * h);
-                dn[0] |= (uint64_t)(So[h] ^ pw) << (32 * h);
-                dn[1] |= (uint64_t)(So[h] & pw) << (32 * h);
             }
+            const uint64_t pw = par ? n[1] : n[0];  // even site 2m + (1 - par)
+            dn[0] = So ^ pw;
+            dn[1] = So & pw;
         }
-        const bool tied = (pend[0] | pend[1]) != 0u;
-        if (!tied) (w + rbase)[x] = ((uint64_t)So[1] << 32) | So[0];
-        const uint64_t m = __ballot(tied);
-        const uint32_t cnt = (uint32_t)__popcll(m);
-        if (qn + cnt > (uint32_t)kTieQueue) settle();
-        if (tied) {
-            const uint32_t at = qn + wave_rank(m);
-            q_id[wave][at] = make_uint4((uint32_t)(rbase + x), j0 + (uint32_t)lb.label, pend[0], pend[1]);
-            q_s[wave][at] = make_uint4(So[0], So[1], C0[0], C0[1]);
-            if (HB || DIMS == 3) q_c[wave][at] = make_uint4(C1[0], C1[1], C2[0], C2[1]);
-        }
-        qn += cnt;
         if (MEASURE) {
             cu.add(u);
             cd.add(dn);
@@ -246,7 +221,6 @@ __global__ __launch_bounds__(MEASURE ? 64 * kMscWaves : 256) void k_msc(MscArgs 
             }
         }
     }
-    settle();
     if (MEASURE) {
         u_acc += cu.flush(lb);
         d_acc += cd.flush(lb);
@@ -275,7 +249,7 @@ static hipError_t launch_msc_t(const MscArgs &a, int count, hipStream_t s)
     // its share of the tasks.  With them one workgroup per CU of up to sixteen
     // waves, as few as give every task one: each workgroup adds 128 numbers to
     // the same eight lines, which takes 1024 workgroups 40 us whatever the
-    // lattice (us per sweep at four waves each: 512 x 1024 57.8, now 24.2;
+    // lattice (us per sweep at four waves each: 512 x 1024 57.8, then 24.2;
     // 1024^2 66, 35; 128 x 64^2 heat-bath 60, 26; 4096^2 296, 296).
     if (!a.EM) {
         const dim3 grid((unsigned)std::min<int64_t>((tasks + 3) / 4, 2048), (unsigned)count);

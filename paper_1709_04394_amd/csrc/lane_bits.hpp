@@ -74,42 +74,42 @@ __device__ __forceinline__ void swap16(uint32_t &a, uint32_t &b)
     b = r[1];
 }
 
-// The random blocks of 64 sites in four groups of 16 (a lane's replica is its
-// label) to the bit-planes of 64 replicas (a lane's site is its label): on
-// return plane k is plane_pair(B[0], B[1], k) for replicas 0..31 and
-// plane_pair(B[2], B[3], k) for 32..63.
-__device__ __forceinline__ void transpose_blocks(uint4 (&B)[4], const LaneBits &b)
+// 64 x 64 bits between sites on the lanes (a lane's site is its label, bit b of
+// {lo, hi} replica b) and replicas on the lanes (a lane's replica is its label):
+// then bits 0..15 and 16..31 of q0 are the sites 0..15 and 32..47, those of q1
+// 16..31 and 48..63, so that plane_pair(B[0], B[2], k) and plane_pair(B[1],
+// B[3], k) are the planes of q0 and q1 for the replica's random blocks B of the
+// four groups of 16 sites.
+__device__ __forceinline__ void to_replicas(uint32_t lo, uint32_t hi, uint32_t &q0, uint32_t &q1, const LaneBits &b)
 {
-    uint32_t r[4][4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        r[g][0] = B[g].x;
-        r[g][1] = B[g].y;
-        r[g][2] = B[g].z;
-        r[g][3] = B[g].w;
-    }
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        swap32(r[0][w], r[2][w]);
-        swap32(r[1][w], r[3][w]);
-        swap16(r[0][w], r[1][w]);
-        swap16(r[2][w], r[3][w]);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) r[g][w] = exchange16(r[g][w], b);
-    }
-#pragma unroll
-    for (int g = 0; g < 4; ++g) B[g] = make_uint4(r[g][0], r[g][1], r[g][2], r[g][3]);
+    swap32(lo, hi);
+    q0 = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+    q1 = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+    swap16(q0, q1);
+    q0 = exchange16(q0, b);
+    q1 = exchange16(q1, b);
 }
+
+__device__ __forceinline__ void to_sites(uint32_t q0, uint32_t q1, uint32_t &lo, uint32_t &hi, const LaneBits &b)
+{
+    q0 = exchange16(q0, b);
+    q1 = exchange16(q1, b);
+    swap16(q0, q1);
+    lo = __builtin_amdgcn_perm(q1, q0, 0x05040100u);
+    hi = __builtin_amdgcn_perm(q1, q0, 0x07060302u);
+    swap32(lo, hi);
+}
+
+// Site of bit i of q0 (i < 32) or i - 32 of q1.
+__device__ __forceinline__ uint32_t site_of_bit(uint32_t i) { return (i & 15u) | ((i & 16u) << 1) | ((i & 32u) >> 1); }
 
 // Set bits of each replica's column over the wave's lanes: lane's result is
 // that of replica label.
 __device__ __forceinline__ int column_count(uint64_t v, const LaneBits &b)
 {
-    uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-    swap32(lo, hi);
-    uint32_t p0 = __builtin_amdgcn_perm(hi, lo, 0x05040100u), p1 = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
-    swap16(p0, p1);
-    return __builtin_popcount(exchange16(p0, b)) + __builtin_popcount(exchange16(p1, b));
+    uint32_t q0, q1;
+    to_replicas((uint32_t)v, (uint32_t)(v >> 32), q0, q1, b);
+    return __builtin_popcount(q0) + __builtin_popcount(q1);
 }
 
 // Bit-sliced count (c0, c1, c2) of the set bits among Z words.
