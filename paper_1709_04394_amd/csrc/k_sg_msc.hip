@@ -19,7 +19,8 @@
 // every spin word, and writes half of those.  32^3, 4096 realisations (75 MB):
 // 15.0 us per even half-sweep, 5.0 TB/s, against 25.6 with workgroups dealt
 // round the L2 caches (each then read most rows' words and couplings again)
-// and rows by 64-bit division; 21.7 with E, M, against 33.4 with five 64 x 64
+// and rows by 64-bit division; 21.3 with E, M (21.7 with the workgroup's share
+// of the tasks and a task's first row divided out in 64 bits), against 33.4 with five 64 x 64
 // transposes per task.  Couplings loaded past the caches (non-temporal) cost
 // 15 %: a line of them serves two rows.
 #include <algorithm>
@@ -42,8 +43,8 @@ struct SgMscArgs {
     // heat-bath class d = neighbours with J s_j = -1, T of h = z - 2d
     uint32_t top[8], low[8];
     int64_t *EM;          // this sweep's [count * 64][2], or nullptr
-    uint32_t tasks;       // of 64 sites, per lattice
     uint32_t parts;       // workgroups per lattice
+    uint32_t per, extra;  // tasks of 64 sites of a lattice: parts per + extra
     uint32_t total;       // workgroups with work
     // n / (Lx / 2) and n / Ly as the high word of a product, for n below the
     // divisor + 64 (the divisor < 64; else the quotient is n >= divisor)
@@ -101,13 +102,13 @@ __global__ __launch_bounds__(256, 5) void k_sg_msc(SgMscArgs a)
         d_acc += cd.flush(lb, 32 - __builtin_clz((unsigned)(2 * since)));
         since = 0;
     };
-    const uint32_t t1 = (uint32_t)((uint64_t)a.tasks * (part + 1) / a.parts);
-    for (uint32_t t = (uint32_t)((uint64_t)a.tasks * part / a.parts) + (uint32_t)wave; t < t1; t += 4u) {
-        // lane: same-colour site j = 64 t + lane
-        const uint64_t j0 = (uint64_t)t << 6;
-        const uint64_t row0 = j0 / hx;
-        const uint32_t z0 = (uint32_t)(row0 / (uint32_t)a.Ly), y0 = (uint32_t)(row0 - (uint64_t)z0 * (uint32_t)a.Ly);
-        const uint32_t mm = (uint32_t)(j0 - row0 * hx) + (uint32_t)(tid & 63);
+    // tasks of this workgroup: the first a.extra have one more
+    const uint32_t t0 = part * a.per + min(part, a.extra), t1 = t0 + a.per + (part < a.extra ? 1u : 0u);
+    for (uint32_t t = t0 + (uint32_t)wave; t < t1; t += 4u) {
+        // lane: same-colour site j = 64 t + lane (at most 2^31 of them)
+        const uint32_t j0 = t << 6, row0 = j0 / hx;
+        const uint32_t z0 = row0 / (uint32_t)a.Ly, y0 = row0 - z0 * (uint32_t)a.Ly;
+        const uint32_t mm = j0 - row0 * hx + (uint32_t)(tid & 63);
         const uint32_t dr = small_quotient(mm, hx, a.mul_hx);
         const uint32_t yy = y0 + dr, dz = small_quotient(yy, (uint32_t)a.Ly, a.mul_ly);
         const uint32_t m = mm - dr * hx, y = yy - dz * (uint32_t)a.Ly, z = z0 + dz;
@@ -131,9 +132,8 @@ __global__ __launch_bounds__(256, 5) void k_sg_msc(SgMscArgs a)
         }
         // the site's one draw: top byte from block j / 16 (bit k = bit j mod 16
         // of half-word k), compared once with each class threshold
-        const uint32_t jl = (uint32_t)j0 + (uint32_t)(tid & 63);
-        const uint4 B =
-            philox(make_uint4((uint32_t)((j0 + (uint32_t)(tid & 63)) >> 4), rep, a.sweep_lo, a.w3), a.seed_lo, a.seed_hi);
+        const uint32_t jl = j0 + (uint32_t)(tid & 63);
+        const uint4 B = philox(make_uint4(jl >> 4, rep, a.sweep_lo, a.w3), a.seed_lo, a.seed_hi);
         const uint32_t top = byte_of(B, jl & 15u);
         uint32_t acc[NC];
         bool tie = false;
@@ -299,10 +299,12 @@ hipError_t launch_sg_msc_phase(const Geom &g, int rule, const SweepTables &tab, 
     }
     a.EM = phase == 1 ? EM : nullptr;
     // as many workgroups as are resident at once, in equal parts of a lattice
-    a.tasks = (uint32_t)(a.N >> 7);
+    const uint32_t tasks = (uint32_t)(a.N >> 7);
     const int64_t resident = a.EM ? kSgBlocksEM : kSgBlocks;
-    a.parts = (uint32_t)std::min<int64_t>((a.tasks + 3) / 4, std::max<int64_t>(1, (resident + g.count - 1) / g.count));
+    a.parts = (uint32_t)std::min<int64_t>((tasks + 3) / 4, std::max<int64_t>(1, (resident + g.count - 1) / g.count));
     a.total = a.parts * (uint32_t)g.count;
+    a.per = tasks / a.parts;
+    a.extra = tasks % a.parts;
     const uint32_t hx = (uint32_t)g.Lx >> 1;
     a.mul_hx = (uint32_t)((((uint64_t)1 << 32) + hx - 1) / hx);
     a.mul_ly = (uint32_t)((((uint64_t)1 << 32) + (uint32_t)g.Ly - 1) / (uint32_t)g.Ly);
