@@ -19,12 +19,14 @@
 // every even site once.
 //
 // What bounds it: below about 10^6 sites the latency of a launch and of one
-// pass through the kernel (heat-bath 1000 x 750: 5.0 us per even half-sweep and
-// 5.4 with E, M, 11.8 us per sweep with the launches' gaps, against 63 with a
-// thread that walks 16 sites one by one and a measurement of its own); above,
-// memory and VALU issue (4096^2: 11 and 13 us, 26 us per sweep against 432).
+// pass through the kernel (heat-bath 1000 x 750: 9 to 10 us per sweep with the
+// launches' gaps, against 63 with a thread that walks 16 sites one by one and a
+// measurement of its own); above, memory and VALU issue (4096^2: 24.1 us per
+// sweep, 24.9 with a multiplexer over all heat-bath classes, 432 site by site;
+// 200^3 +-J 29.6 and 32.4).
 #include <algorithm>
 
+#include "heatbath.hpp"
 #include "internal.hpp"
 #include "lane_bits.hpp"
 #include "metro2d.hpp"
@@ -57,9 +59,10 @@ struct HalfArgs {
     int64_t *EM;          // this sweep's [count][2], or nullptr
 };
 
-template <int DIMS, bool HB, bool HASJ, bool MEASURE>
+template <int DIMS, int RULE, bool HASJ, bool MEASURE>
 __global__ __launch_bounds__(kHalfThreads) void k_half(HalfArgs a)
 {
+    constexpr bool HB = RULE != kMetropolis;
     __shared__ uint32_t tlow[8];
     __shared__ int red[2][kHalfThreads / 64];
     constexpr int Z = 2 * DIMS;
@@ -78,7 +81,7 @@ __global__ __launch_bounds__(kHalfThreads) void k_half(HalfArgs a)
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             tv[k][i] = a.mask[k][2 * i];
-            if (i < (HB ? DIMS : 1)) asm volatile("" : "+v"(tv[k][i]));
+            if (RULE != kHeatBathMirrored && i < (HB ? DIMS : 1)) asm volatile("" : "+v"(tv[k][i]));
         }
     int e_acc = 0, m_acc = 0;
     // Large lattices by XCD (4096^2 25.6 against 26.7 us per sweep, 200^3 with
@@ -165,6 +168,8 @@ __global__ __launch_bounds__(kHalfThreads) void k_half(HalfArgs a)
         // Metropolis: a >= z/2 gives dE <= 0
         const uint32_t ge = HB ? 0u : DIMS == 3 ? MCS_BOP3(c2, c1, c0, MCS_A | (MCS_B & MCS_C)) : (c2 | c1);
         uint32_t lt = 0u, eq = valid;
+        MirroredClasses mc;
+        if constexpr (RULE == kHeatBathMirrored) mc = mirror_classes<DIMS>(c0, c1, c2);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const uint32_t X = plane_pair(A, B, k) >> off;
@@ -173,7 +178,9 @@ __global__ __launch_bounds__(kHalfThreads) void k_half(HalfArgs a)
             };
             const uint32_t *ts = a.mask[k];
             uint32_t T = mux(c0, ts[1], tv[k][0]);  // classes 0, 1
-            if (HB) {
+            if constexpr (RULE == kHeatBathMirrored) {
+                T = k == 7 ? ~mc.s : mirrored_plane<DIMS>(mc, ts[0], ts[1], ts[2]);
+            } else if (HB) {
                 T = mux(c1, mux(c0, ts[3], tv[k][1]), T);
                 T = DIMS == 3 ? mux(c2, mux(c1, ts[6], mux(c0, ts[5], tv[k][2])), T) : mux(c2, tv[k][2], T);
             } else if (DIMS == 3) {
@@ -237,13 +244,24 @@ __global__ __launch_bounds__(kHalfThreads) void k_half(HalfArgs a)
 
 bool half_supported(const Geom &g) { return g.Lx >= 32; }
 
-template <int D, bool HB, bool HJ>
+template <int D, int RULE, bool HJ>
 static hipError_t launch_half_t(const HalfArgs &a, int count, hipStream_t s)
 {
     const dim3 grid(a.blocks, (unsigned)count);
-    if (a.EM) hipLaunchKernelGGL((k_half<D, HB, HJ, true>), grid, dim3(kHalfThreads), 0, s, a);
-    else hipLaunchKernelGGL((k_half<D, HB, HJ, false>), grid, dim3(kHalfThreads), 0, s, a);
+    if (a.EM) hipLaunchKernelGGL((k_half<D, RULE, HJ, true>), grid, dim3(kHalfThreads), 0, s, a);
+    else hipLaunchKernelGGL((k_half<D, RULE, HJ, false>), grid, dim3(kHalfThreads), 0, s, a);
     return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_half_r(const HalfArgs &a, int rule, int count, hipStream_t s)
+{
+    const bool hj = a.J != nullptr;
+    switch (rule) {
+    case kMetropolis: return hj ? launch_half_t<D, kMetropolis, true>(a, count, s) : launch_half_t<D, kMetropolis, false>(a, count, s);
+    case kHeatBath: return hj ? launch_half_t<D, kHeatBath, true>(a, count, s) : launch_half_t<D, kHeatBath, false>(a, count, s);
+    default: return hj ? launch_half_t<D, kHeatBathMirrored, true>(a, count, s) : launch_half_t<D, kHeatBathMirrored, false>(a, count, s);
+    }
 }
 
 // One half-sweep (colour c) of every lattice; EM: this sweep's (E, M),
@@ -272,6 +290,7 @@ hipError_t launch_half(const SweepCall &c, int8_t *spins, uint64_t sweep, int ph
     a.w3 = ctr_w3(kTagSweep, (uint32_t)phase, sweep);
     a.w3lo = ctr_w3(kTagSweepLo, (uint32_t)phase, sweep);
     const int z = 2 * g.dims;
+    uint32_t top[8];
     for (int cl = 0; cl < 8; ++cl) {
         Thr th{0u, 0u};
         if (c.rule == 0) {
@@ -281,16 +300,13 @@ hipError_t launch_half(const SweepCall &c, int8_t *spins, uint64_t sweep, int ph
         }
         th = metro_thr(th);
         for (int k = 0; k < 8; ++k) a.mask[k][cl] = ((th.top >> k) & 1u) ? ~0u : 0u;
+        top[cl] = th.top;
         a.low[cl] = th.low;
     }
     a.EM = phase == 1 ? EM : nullptr;
-    const bool hb = c.rule == 1, hj = c.J != nullptr;
-    if (g.dims == 2) {
-        if (hb) return hj ? launch_half_t<2, true, true>(a, g.count, s) : launch_half_t<2, true, false>(a, g.count, s);
-        return hj ? launch_half_t<2, false, true>(a, g.count, s) : launch_half_t<2, false, false>(a, g.count, s);
-    }
-    if (hb) return hj ? launch_half_t<3, true, true>(a, g.count, s) : launch_half_t<3, true, false>(a, g.count, s);
-    return hj ? launch_half_t<3, false, true>(a, g.count, s) : launch_half_t<3, false, false>(a, g.count, s);
+    const int rule = c.rule == 0 ? kMetropolis : mirrored_classes(top, z) ? kHeatBathMirrored : kHeatBath;
+    if (g.dims == 2) return launch_half_r<2>(a, rule, g.count, s);
+    return launch_half_r<3>(a, rule, g.count, s);
 }
 
 }  // namespace mcs

@@ -32,6 +32,7 @@
 // every task and rows by 64-bit division.
 #include <algorithm>
 
+#include "heatbath.hpp"
 #include "internal.hpp"
 #include "lane_bits.hpp"
 
@@ -55,9 +56,10 @@ struct MscArgs {
 constexpr int kMscWaves = 16;  // of a workgroup that measures, at most
 constexpr int kMscFlush = 32;  // tasks between sums of the bit-sliced counters
 
-template <int DIMS, bool MEASURE, bool HB, bool HASJ>
+template <int DIMS, bool MEASURE, int RULE, bool HASJ>
 __global__ __launch_bounds__(MEASURE ? 64 * kMscWaves : 256) void k_msc(MscArgs a)
 {
+    constexpr bool HB = RULE != kMetropolis;
     __shared__ uint32_t tlow[8];
     __shared__ long long red[2][64];
     constexpr int Z = 2 * DIMS;
@@ -79,7 +81,7 @@ __global__ __launch_bounds__(MEASURE ? 64 * kMscWaves : 256) void k_msc(MscArgs 
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             tv[k][i] = ((a.top[2 * i] >> k) & 1u) ? ~0u : 0u;
-            if (i < (HB ? DIMS : 1)) asm volatile("" : "+v"(tv[k][i]));
+            if (RULE != kHeatBathMirrored && i < (HB ? DIMS : 1)) asm volatile("" : "+v"(tv[k][i]));
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) ts[k][i] = ((a.top[i < 3 ? 2 * i + 1 : 6] >> k) & 1u) ? ~0u : 0u;
@@ -156,6 +158,8 @@ __global__ __launch_bounds__(MEASURE ? 64 * kMscWaves : 256) void k_msc(MscArgs 
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             uint32_t lt = 0u, eq = ~0u;
+            MirroredClasses mc;
+            if constexpr (RULE == kHeatBathMirrored) mc = mirror_classes<DIMS>(c0[q], c1[q], c2[q]);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const uint32_t X = plane_pair(B[q], B[q + 2], k);
@@ -163,7 +167,9 @@ __global__ __launch_bounds__(MEASURE ? 64 * kMscWaves : 256) void k_msc(MscArgs 
                     return MCS_BOP3(sel, hi, lo, (MCS_A & MCS_B) | (~MCS_A & MCS_C));
                 };
                 uint32_t T = mux(c0[q], ts[k][0], tv[k][0]);  // classes 0, 1
-                if (HB) {
+                if constexpr (RULE == kHeatBathMirrored) {
+                    T = k == 7 ? ~mc.s : mirrored_plane<DIMS>(mc, tv[k][0], ts[k][0], tv[k][1]);
+                } else if (HB) {
                     T = mux(c1[q], mux(c0[q], ts[k][1], tv[k][1]), T);
                     T = DIMS == 3 ? mux(c2[q], mux(c1[q], ts[k][3], mux(c0[q], ts[k][2], tv[k][2])), T)
                                   : mux(c2[q], tv[k][2], T);
@@ -241,7 +247,7 @@ bool msc_fast_supported(const SweepCall &c, int layout)
            c.g.N <= (int64_t)1 << 32;
 }
 
-template <int D, bool HB, bool HJ>
+template <int D, int RULE, bool HJ>
 static hipError_t launch_msc_t(const MscArgs &a, int count, hipStream_t s)
 {
     const int64_t tasks = (a.N >> 1) >> 6;
@@ -253,15 +259,26 @@ static hipError_t launch_msc_t(const MscArgs &a, int count, hipStream_t s)
     // 1024^2 66, 35; 128 x 64^2 heat-bath 60, 26; 4096^2 296, 296).
     if (!a.EM) {
         const dim3 grid((unsigned)std::min<int64_t>((tasks + 3) / 4, 2048), (unsigned)count);
-        hipLaunchKernelGGL((k_msc<D, false, HB, HJ>), grid, dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_msc<D, false, RULE, HJ>), grid, dim3(256), 0, s, a);
         return hipGetLastError();
     }
     constexpr int64_t kCUs = 256;
     int waves = 4;
     while (waves < kMscWaves && tasks > kCUs * waves) waves *= 2;
     const dim3 grid((unsigned)std::min<int64_t>((tasks + waves - 1) / waves, kCUs), (unsigned)count);
-    hipLaunchKernelGGL((k_msc<D, true, HB, HJ>), grid, dim3(64 * waves), 0, s, a);
+    hipLaunchKernelGGL((k_msc<D, true, RULE, HJ>), grid, dim3(64 * waves), 0, s, a);
     return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_msc_r(const MscArgs &a, int rule, int count, hipStream_t s)
+{
+    const bool hj = a.J != nullptr;
+    switch (rule) {
+    case kMetropolis: return hj ? launch_msc_t<D, kMetropolis, true>(a, count, s) : launch_msc_t<D, kMetropolis, false>(a, count, s);
+    case kHeatBath: return hj ? launch_msc_t<D, kHeatBath, true>(a, count, s) : launch_msc_t<D, kHeatBath, false>(a, count, s);
+    default: return hj ? launch_msc_t<D, kHeatBathMirrored, true>(a, count, s) : launch_msc_t<D, kHeatBathMirrored, false>(a, count, s);
+    }
 }
 
 // One half-sweep (colour c) of every word lattice; EM: this sweep's per-lane
@@ -296,13 +313,9 @@ hipError_t launch_msc_phase(const SweepCall &c, uint64_t *words, uint64_t sweep,
         a.low[cl] = th.low;
     }
     a.EM = phase == 1 ? EM : nullptr;
-    const bool hb = c.rule == 1, hj = c.J != nullptr;
-    if (c.g.dims == 2) {
-        if (hb) return hj ? launch_msc_t<2, true, true>(a, c.g.count, s) : launch_msc_t<2, true, false>(a, c.g.count, s);
-        return hj ? launch_msc_t<2, false, true>(a, c.g.count, s) : launch_msc_t<2, false, false>(a, c.g.count, s);
-    }
-    if (hb) return hj ? launch_msc_t<3, true, true>(a, c.g.count, s) : launch_msc_t<3, true, false>(a, c.g.count, s);
-    return hj ? launch_msc_t<3, false, true>(a, c.g.count, s) : launch_msc_t<3, false, false>(a, c.g.count, s);
+    const int rule = c.rule == 0 ? kMetropolis : mirrored_classes(a.top, z) ? kHeatBathMirrored : kHeatBath;
+    if (c.g.dims == 2) return launch_msc_r<2>(a, rule, c.g.count, s);
+    return launch_msc_r<3>(a, rule, c.g.count, s);
 }
 
 }  // namespace mcs

@@ -17,22 +17,25 @@
 //    a >= 3 always accepts); heat-bath counts neighbours with J s_j = -1, d
 //    (h = 6 - 2d).  Each class has its own threshold; per random bit-plane the
 //    threshold bit of every site comes from a multiplexer over the class bits
-//    (its inputs alternate between scalar and vector registers), and r32 < T is
-//    one bit-serial comparison.  Ties (top byte equal) wait in a queue of their
+//    (its inputs alternate between scalar and vector registers), in heat-bath
+//    from half the classes and their mirror images (heatbath.hpp), and r32 < T
+//    is one bit-serial comparison.  Ties (top byte equal) wait in a queue of their
 //    wave (metro2d.hpp).
 //  * Per-sweep E and M are summed from the odd half-sweep, as in 2D, and
 //    stored per tile in slots that the next launch adds up (em_slots.hpp).
 //  * Between the launches of one call the lattice stays packed in global
 //    scratch.
 //
-// What bounds it: VALU issue (heat-bath about 230 instructions of a wave per 64
-// words of 32 sites, Metropolis 190) with the redone halo (1.4 times at H = 16,
+// What bounds it: VALU issue (heat-bath about 200 instructions of a wave per 64
+// words of 32 sites, Metropolis 200) with the redone halo (1.4 times at H = 16,
 // K = 2), then the half-sweeps' latency where a CU has one tile.  256^3 x 4
-// heat-bath, H = 16, K = 1, 256 threads: 28.4 us per sweep, 30.4 with a
-// tile's rows loaded one after the other, each by its own division, and a
-// serial sum over the waves each sweep; at K = 2 with the thresholds read from
-// LDS for every plane and ties settled between two barriers besides 38.8.
-// 256^3 alone, 768 threads: 12.3, 13.1 and 17.2.
+// heat-bath, H = 16, K = 1, 256 threads: 26.1 us per sweep; 27.7 with a
+// multiplexer over all seven classes, 29.7 with a tile's rows loaded one after
+// the other besides, each by its own division, and a serial sum over the waves
+// each sweep; at K = 2 with the thresholds read from LDS for every plane and
+// ties settled between two barriers besides 38.7.
+// 256^3 alone, 768 threads: 12.0, 12.3, 13.1 and 17.2.
+#include "heatbath.hpp"
 #include "internal.hpp"
 #include "metro2d.hpp"
 #include "spin_bytes.hpp"
@@ -80,9 +83,10 @@ __device__ __forceinline__ int tile_cut(int t, int n, int L)
     return (int)((int64_t)t * L / n);
 }
 
-template <int K, bool MEASURE, bool HB, bool HASJ>
+template <int K, bool MEASURE, int RULE, bool HASJ>
 __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
 {
+    constexpr bool HB = RULE != kMetropolis;
     extern __shared__ uint32_t lds[];
     __shared__ int sums[2][K > 0 ? K : 1];  // anti-aligned bonds and down spins of each sweep
     __shared__ long long red64[2][16];
@@ -104,14 +108,15 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
     // of y + z; then each wave's tie queue
     uint32_t *rinfo = lds + (size_t)rows * 2 * Wd * (HASJ ? 4 : 1);
     // per random plane and class the threshold bit as a full mask, those of
-    // classes 0, 2, 4 in vector registers (an instruction reads one scalar)
+    // classes 0, 2, 4 in vector registers (an instruction reads one scalar);
+    // mirrored classes 0, 1, 2 in scalar ones
     uint32_t tv[8][3], ts[8][4];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
 #pragma unroll
         for (int i = 0; i < (HB ? 3 : 1); ++i) {
             tv[k][i] = ((a.top[li][2 * i] >> k) & 1u) ? ~0u : 0u;
-            asm volatile("" : "+v"(tv[k][i]));
+            if (RULE != kHeatBathMirrored) asm volatile("" : "+v"(tv[k][i]));
         }
         ts[k][0] = ((a.top[li][1] >> k) & 1u) ? ~0u : 0u;
         ts[k][1] = ((a.top[li][HB ? 3 : 2] >> k) & 1u) ? ~0u : 0u;
@@ -315,6 +320,8 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
                     // bit-serial r < T(class) from the least significant plane;
                     // the threshold bit of each site is chosen by its class
                     uint32_t lt = 0u, eq = ~0u;
+                    MirroredClasses mc;
+                    if constexpr (RULE == kHeatBathMirrored) mc = mirror_classes<3>(c0, c1, c2);
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
                         const uint32_t X = plane_pair(A, B, k);
@@ -324,7 +331,9 @@ __global__ __launch_bounds__(1024) void k_tile3d(Tile3DArgs a)
                         };
                         const uint32_t m01 = mux(c0, ts[k][0], tv[k][0]);
                         uint32_t T;
-                        if (HB) {
+                        if constexpr (RULE == kHeatBathMirrored) {
+                            T = k == 7 ? ~mc.s : mirrored_plane<3>(mc, tv[k][0], ts[k][0], tv[k][1]);
+                        } else if (HB) {
                             const uint32_t lo4 = mux(c1, mux(c0, ts[k][1], tv[k][1]), m01);
                             const uint32_t hi4 = mux(c1, ts[k][3], mux(c0, ts[k][2], tv[k][2]));
                             T = mux(c2, hi4, lo4);
@@ -467,7 +476,7 @@ static size_t tile3d_dynamic_lds(int Lx, int H, int K, bool hasJ, int threads)
 constexpr int kTile3DMaxLds = 98304 + 98304 / 32 * 4 + 16 * kTieQueue * 24;
 static_assert(kTile3DMaxLds <= 155 * 1024, "next to the static arrays in 160 KB");
 
-template <int K, bool HB, bool HASJ>
+template <int K, int RULE, bool HASJ>
 static hipError_t launch3(const Tile3DArgs &a, int H, int count, int threads, hipStream_t s)
 {
     const size_t lds = tile3d_dynamic_lds(a.Lx, H, K, HASJ, threads);
@@ -475,24 +484,24 @@ static hipError_t launch3(const Tile3DArgs &a, int H, int count, int threads, hi
     static LdsLimit lim[2];
     {
         const void *f =
-            a.em.slots ? (const void *)k_tile3d<K, true, HB, HASJ> : (const void *)k_tile3d<K, false, HB, HASJ>;
+            a.em.slots ? (const void *)k_tile3d<K, true, RULE, HASJ> : (const void *)k_tile3d<K, false, RULE, HASJ>;
         const hipError_t e = lim[a.em.slots ? 1 : 0].ensure(f, kTile3DMaxLds);
         if (e != hipSuccess) return e;
     }
-    if (a.em.slots) hipLaunchKernelGGL((k_tile3d<K, true, HB, HASJ>), grid, dim3(threads), lds, s, a);
-    else hipLaunchKernelGGL((k_tile3d<K, false, HB, HASJ>), grid, dim3(threads), lds, s, a);
+    if (a.em.slots) hipLaunchKernelGGL((k_tile3d<K, true, RULE, HASJ>), grid, dim3(threads), lds, s, a);
+    else hipLaunchKernelGGL((k_tile3d<K, false, RULE, HASJ>), grid, dim3(threads), lds, s, a);
     return hipGetLastError();
 }
 
-template <bool HB, bool HASJ>
+template <int RULE, bool HASJ>
 static hipError_t launch3k(const Tile3DArgs &a, int k, int H, int count, int threads, hipStream_t s)
 {
     switch (k) {
-    case 0: return launch3<0, HB, HASJ>(a, H, count, threads, s);
-    case 1: return launch3<1, HB, HASJ>(a, H, count, threads, s);
-    case 2: return launch3<2, HB, HASJ>(a, H, count, threads, s);
-    case 3: return launch3<3, HB, HASJ>(a, H, count, threads, s);
-    case 4: return launch3<4, HB, HASJ>(a, H, count, threads, s);
+    case 0: return launch3<0, RULE, HASJ>(a, H, count, threads, s);
+    case 1: return launch3<1, RULE, HASJ>(a, H, count, threads, s);
+    case 2: return launch3<2, RULE, HASJ>(a, H, count, threads, s);
+    case 3: return launch3<3, RULE, HASJ>(a, H, count, threads, s);
+    case 4: return launch3<4, RULE, HASJ>(a, H, count, threads, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -533,18 +542,22 @@ hipError_t launch_tile3d(const SweepCall &c, const void *src, int in_packed, voi
     a.replica0 = c.replica0;
     a.sweep0 = sweep0;
     a.per_lattice = c.per_lattice;
+    bool mirrored = c.rule == 1;
     for (int i = 0; i < kMaxTableLattices; ++i) {
         const SweepTables &t = (c.per_lattice && i < c.g.count) ? c.tabs[i] : c.tab;
         class_thresholds(t, c.rule, a.top[i], a.low[i]);
+        if (i == 0 || (c.per_lattice && i < c.g.count)) mirrored = mirrored && mirrored_classes(a.top[i], 6);
     }
     a.em = em;
     if (k == 0) a.em.slots = nullptr;
     if (!em.red_in) a.em.red_K = 0;
-    const bool hb = c.rule == 1, hj = Jp != nullptr;
-    if (hb && hj) return launch3k<true, true>(a, k, H, c.g.count, threads, s);
-    if (hb) return launch3k<true, false>(a, k, H, c.g.count, threads, s);
-    if (hj) return launch3k<false, true>(a, k, H, c.g.count, threads, s);
-    return launch3k<false, false>(a, k, H, c.g.count, threads, s);
+    const bool hj = Jp != nullptr;
+    if (mirrored) return hj ? launch3k<kHeatBathMirrored, true>(a, k, H, c.g.count, threads, s)
+                            : launch3k<kHeatBathMirrored, false>(a, k, H, c.g.count, threads, s);
+    if (c.rule == 1) return hj ? launch3k<kHeatBath, true>(a, k, H, c.g.count, threads, s)
+                               : launch3k<kHeatBath, false>(a, k, H, c.g.count, threads, s);
+    return hj ? launch3k<kMetropolis, true>(a, k, H, c.g.count, threads, s)
+              : launch3k<kMetropolis, false>(a, k, H, c.g.count, threads, s);
 }
 
 // Per-tile (E, M) slots of one launch: K <= 4 sweeps x count lattices x

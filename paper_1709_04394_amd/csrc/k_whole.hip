@@ -30,13 +30,14 @@
 // is 0.5 to 0.7 us: windows, bit-serial comparison, ties, barrier), above it the
 // VALU of the one CU.  us per sweep of long calls with E, M, against a byte per
 // site in LDS (rows of 32 sites: a 16-bit word per row and parity): 64^2 1.14
-// (3.8), 128^2 1.6 (11.5), 200^2 heat-bath 3.1 (25), 300^2 5.0 (58), 30^3 +-J 2.9
+// (3.8), 128^2 1.6 (11.5), 200^2 heat-bath 3.0 (25), 300^2 5.0 (58), 30^3 +-J 2.9
 // (23), 32^3 +-J 2.6 (5.7), 32 x 64^2 +-J 8.0 (18).  A half that is a multiple of
 // 32 repeats word 0 after the last and needs no test for the end (64^2 1.43
 // against 1.59).  One wave that settles the ties of all between two barriers
 // made 128^2 2.5 and 32^3 3.0: its latency is longer than the passes it saves.
 #include <algorithm>
 
+#include "heatbath.hpp"
 #include "internal.hpp"
 #include "lane_bits.hpp"
 #include "metro2d.hpp"
@@ -212,9 +213,10 @@ __device__ __forceinline__ void store_pairs(int8_t *p, uint32_t ev, uint32_t od)
 }
 
 // K: items of BITS sites of a colour per thread
-template <int DIMS, bool HB, bool HASJ, int K, bool ALIGNED, int BITS>
+template <int DIMS, int RULE, bool HASJ, int K, bool ALIGNED, int BITS>
 __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
 {
+    constexpr bool HB = RULE != kMetropolis;
     constexpr int Z = 2 * DIMS;
     using item_t = typename WholeItem<BITS>::type;
     extern __shared__ uint32_t sm[];  // spins [2][stride], then couplings [2][Z][stride]
@@ -294,7 +296,7 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             tv[b][i] = a.mask[b][2 * i];
-            if (i < (HB ? DIMS : 1)) asm volatile("" : "+v"(tv[b][i]));
+            if (RULE != kHeatBathMirrored && i < (HB ? DIMS : 1)) asm volatile("" : "+v"(tv[b][i]));
         }
     const int64_t sites = N;
     auto publish = [&](int t) {
@@ -334,6 +336,8 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
                 // Metropolis: a >= z/2 gives dE <= 0
                 const uint32_t ge = HB ? 0u : DIMS == 3 ? MCS_BOP3(c2, c1, c0, MCS_A | (MCS_B & MCS_C)) : (c2 | c1);
                 uint32_t lt = 0u, eq = g[k].valid;
+                MirroredClasses mc;
+                if constexpr (RULE == kHeatBathMirrored) mc = mirror_classes<DIMS>(c0, c1, c2);
 #pragma unroll
                 for (int b = 0; b < 8; ++b) {
                     uint32_t X;
@@ -345,7 +349,9 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
                     }
                     const uint32_t *ts = a.mask[b];
                     uint32_t T = bit_mux(c0, ts[1], tv[b][0]);  // classes 0, 1
-                    if (HB) {
+                    if constexpr (RULE == kHeatBathMirrored) {
+                        T = b == 7 ? ~mc.s : mirrored_plane<DIMS>(mc, ts[0], ts[1], ts[2]);
+                    } else if (HB) {
                         T = bit_mux(c1, bit_mux(c0, ts[3], tv[b][1]), T);
                         T = DIMS == 3 ? bit_mux(c2, bit_mux(c1, ts[6], bit_mux(c0, ts[5], tv[b][2])), T)
                                       : bit_mux(c2, tv[b][2], T);
@@ -420,11 +426,11 @@ static size_t whole_lds_bytes(const Geom &g, bool hasJ)
 // sites one workgroup takes longer than two launches over the whole chip.
 bool whole_supported(const Geom &g) { return g.N <= (1 << 17); }
 
-template <int DIMS, bool HB, bool HASJ, int K, bool ALIGNED, int BITS>
+template <int DIMS, int RULE, bool HASJ, int K, bool ALIGNED, int BITS>
 static hipError_t launch_whole_a(const WholeArgs &a, int count, size_t lds, hipStream_t s)
 {
     static LdsLimit lim;
-    const auto f = k_whole<DIMS, HB, HASJ, K, ALIGNED, BITS>;
+    const auto f = k_whole<DIMS, RULE, HASJ, K, ALIGNED, BITS>;
     const hipError_t e = lim.ensure((const void *)f, 128 * 1024);
     if (e != hipSuccess) return e;
     const uint32_t items = (a.half + BITS - 1) / BITS;
@@ -432,17 +438,17 @@ static hipError_t launch_whole_a(const WholeArgs &a, int count, size_t lds, hipS
     return hipGetLastError();
 }
 
-template <int DIMS, bool HB, bool HASJ, int K, int BITS>
+template <int DIMS, int RULE, bool HASJ, int K, int BITS>
 static hipError_t launch_whole_t(const WholeArgs &a, int count, size_t lds, hipStream_t s)
 {
-    return a.half % 32u ? launch_whole_a<DIMS, HB, HASJ, K, false, BITS>(a, count, lds, s)
-                        : launch_whole_a<DIMS, HB, HASJ, K, true, BITS>(a, count, lds, s);
+    return a.half % 32u ? launch_whole_a<DIMS, RULE, HASJ, K, false, BITS>(a, count, lds, s)
+                        : launch_whole_a<DIMS, RULE, HASJ, K, true, BITS>(a, count, lds, s);
 }
 
 // 16 sites per thread, a Philox block instead of two, where the waves are then
 // at most two per SIMD and each issues by itself, or where 32 sites per thread
 // leave half a wave idle.  us per sweep (32 sites per thread): 64^2 1.14 (1.43),
-// 80^2 1.24 (1.62), 128^2 1.59 (1.74), 12^3 heat-bath 1.42 (1.75), 16^3 +-J 1.50
+// 80^2 1.24 (1.62), 128^2 1.59 (1.74), 12^3 heat-bath 1.29 (1.75), 16^3 +-J 1.50
 // (1.80), 4096 of 32^2 2.41 (3.24); beyond, 30^3 +-J 3.24 (2.92), 32^3 3.08
 // (2.61), 4096 of 64^2 4.5 (3.4), 2048 of 128^2 8.4 (6.7).
 static bool whole_halves(uint32_t words, int count)
@@ -451,12 +457,23 @@ static bool whole_halves(uint32_t words, int count)
     return words <= 32 || words * (((uint32_t)count + kCUs - 1) / kCUs) <= 256;
 }
 
-template <int DIMS, bool HB, bool HASJ>
+template <int DIMS, int RULE, bool HASJ>
 static hipError_t launch_whole_k(const WholeArgs &a, int count, size_t lds, hipStream_t s)
 {
-    if (whole_halves(a.words, count)) return launch_whole_t<DIMS, HB, HASJ, 1, 16>(a, count, lds, s);
-    return a.words <= 1024u ? launch_whole_t<DIMS, HB, HASJ, 1, 32>(a, count, lds, s)
-                            : launch_whole_t<DIMS, HB, HASJ, 2, 32>(a, count, lds, s);
+    if (whole_halves(a.words, count)) return launch_whole_t<DIMS, RULE, HASJ, 1, 16>(a, count, lds, s);
+    return a.words <= 1024u ? launch_whole_t<DIMS, RULE, HASJ, 1, 32>(a, count, lds, s)
+                            : launch_whole_t<DIMS, RULE, HASJ, 2, 32>(a, count, lds, s);
+}
+
+template <int D>
+static hipError_t launch_whole_r(const WholeArgs &a, int rule, int count, size_t lds, hipStream_t s)
+{
+    const bool hj = a.J != nullptr;
+    switch (rule) {
+    case kMetropolis: return hj ? launch_whole_k<D, kMetropolis, true>(a, count, lds, s) : launch_whole_k<D, kMetropolis, false>(a, count, lds, s);
+    case kHeatBath: return hj ? launch_whole_k<D, kHeatBath, true>(a, count, lds, s) : launch_whole_k<D, kHeatBath, false>(a, count, lds, s);
+    default: return hj ? launch_whole_k<D, kHeatBathMirrored, true>(a, count, lds, s) : launch_whole_k<D, kHeatBathMirrored, false>(a, count, lds, s);
+    }
 }
 
 // Every sweep of a call, one workgroup per lattice.
@@ -483,6 +500,7 @@ hipError_t launch_whole(const SweepCall &c, int8_t *spins, uint64_t sweep0, int 
     a.EM = EM;
     a.em_stride = em_stride;
     const int z = 2 * g.dims;
+    uint32_t top[8];
     for (int cl = 0; cl < 8; ++cl) {
         Thr th{0u, 0u};
         if (c.rule == 0) {
@@ -492,16 +510,13 @@ hipError_t launch_whole(const SweepCall &c, int8_t *spins, uint64_t sweep0, int 
         }
         th = metro_thr(th);
         for (int k = 0; k < 8; ++k) a.mask[k][cl] = ((th.top >> k) & 1u) ? ~0u : 0u;
+        top[cl] = th.top;
         a.low[cl] = th.low;
     }
     const size_t lds = whole_lds_bytes(g, c.J != nullptr);
-    const bool hb = c.rule == 1, hj = c.J != nullptr;
-    if (g.dims == 2) {
-        if (hb) return hj ? launch_whole_k<2, true, true>(a, g.count, lds, s) : launch_whole_k<2, true, false>(a, g.count, lds, s);
-        return hj ? launch_whole_k<2, false, true>(a, g.count, lds, s) : launch_whole_k<2, false, false>(a, g.count, lds, s);
-    }
-    if (hb) return hj ? launch_whole_k<3, true, true>(a, g.count, lds, s) : launch_whole_k<3, true, false>(a, g.count, lds, s);
-    return hj ? launch_whole_k<3, false, true>(a, g.count, lds, s) : launch_whole_k<3, false, false>(a, g.count, lds, s);
+    const int rule = c.rule == 0 ? kMetropolis : mirrored_classes(top, z) ? kHeatBathMirrored : kHeatBath;
+    if (g.dims == 2) return launch_whole_r<2>(a, rule, g.count, lds, s);
+    return launch_whole_r<3>(a, rule, g.count, lds, s);
 }
 
 }  // namespace mcs
