@@ -18,7 +18,8 @@
 //
 // What bounds it: VALU issue from ten hits on, with one hit the launch, the
 // tile's load and the sums.  Attempted updates per ns, 4096^2 x 3, tiles of 128,
-// at one, ten and a hundred hits: 1970, 4270 and 5010; 1330, 3880 and 4980 with
+// at one, ten and a hundred hits: 2000, 4320 and 5050; 1980, 4285 and 5025 with
+// the workgroups of a CU settling ties on one SIMD at a time; 1330, 3880 and 4980 with
 // tiles side by side on different XCDs (each then loads whole lines for 8 bytes
 // of a row), 1340, 3790 and 4660 with every wave settling its own ties, 1180,
 // 3050 and 3700 with a comparison per class besides.
@@ -121,7 +122,10 @@ __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
 
     const int tasks = a.T * Wt;  // words of one colour: one per (row, column), a multiple of the threads
     uint4 *const tq = queue + wave * kTieQueue;
-    int turn = (int)blockIdx.x;  // the wave that settles, in turn (a wave's SIMD is that of its number)
+    // the wave that settles, in turn (a wave's SIMD is that of its number); the
+    // workgroups of one CU, 256 apart, start with different waves
+    const int wg = (int)(l * gridDim.x + blockIdx.x);
+    int turn = wg + (wg >> 8);
     for (int h = 0; h < a.hits; ++h) {
         const uint64_t dsweep = a.sweep * (uint64_t)a.hits + (uint64_t)h;
         for (int col = 0; col < 2; ++col) {
