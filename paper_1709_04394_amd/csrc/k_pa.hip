@@ -27,6 +27,8 @@
 // x_i + (G_q + B_b)), and rounding to nearest is monotone, so the running
 // maximum of C inside block b is fl(runmax(x) + (G_q + B_b)): the search needs
 // no materialised C.
+#include <algorithm>
+
 #include "internal.hpp"
 #include "lds_lattice.hpp"
 #include "pa.hpp"
@@ -384,7 +386,9 @@ hipError_t launch_pa_step(const PaStep &st, int rmax, int sweep_blocks, hipStrea
         hipLaunchKernelGGL(k_pa_place, dim3((rmax + kPlaceChunk - 1) / kPlaceChunk, st.npop), dim3(kPlaceThreads), 0,
                            s, st);
     }
-    const int threads = lds_lattice_threads(sweep_blocks);
+    int words = 0;
+    for (int p = 0; p < st.npop; ++p) words = std::max(words, lds_lattice_words(st.pop[p].L, st.pop[p].G));
+    const int threads = lds_lattice_threads(sweep_blocks, words);
     size_t lds = 0;
     for (int p = 0; p < st.npop; ++p) {
         const size_t b = lds_lattice_bytes(st.pop[p].L, st.pop[p].G, threads);

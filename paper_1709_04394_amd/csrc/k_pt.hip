@@ -99,7 +99,7 @@ __global__ __launch_bounds__(1024) void k_pt_exchange(PtExchangeArgs a)
 hipError_t launch_pt_round(const PtSweepArgs &sw, const PtExchangeArgs &ex, int n_sets, hipStream_t s)
 {
     const int blocks = (sw.count + sw.G - 1) / sw.G;
-    const int wg = lds_lattice_threads(blocks);
+    const int wg = lds_lattice_threads(blocks, lds_lattice_words(sw.L, sw.G));
     hipLaunchKernelGGL(k_pt_sweep, dim3(blocks), dim3(wg), lds_lattice_bytes(sw.L, sw.G, wg), s, sw);
     const int threads = ((ex.n_temps + 63) / 64) * 64;
     hipLaunchKernelGGL(k_pt_exchange, dim3(n_sets), dim3(threads), 0, s, ex);

@@ -26,6 +26,10 @@
 // L < 64, one row per word: 9.46 ms for eight annealing steps of four
 // populations of 16384 replicas, 6.46 so, and 5.84 with bytes packed by v_dot4,
 // starting lattices written as 16-byte words and the first measurement in place.
+// Where a wave has one task a half-sweep, a queue gathers nothing: there each lane
+// settles its own word's ties (32 temperatures of 128 sets of L = 64, ten rounds
+// of ten sweeps: 764 us with the queue, 715 without; 1000 annealed replicas of
+// L = 64, six steps: 402 and 370).
 #pragma once
 
 #include "common.hpp"
@@ -64,22 +68,27 @@ __device__ __forceinline__ LdsLattices lds_lattices(int L)
     return a;
 }
 
+// Words of G lattices, both colours.
+__host__ __device__ __forceinline__ int lds_lattice_words(int L, int G) { return G * 2 * (L < 8 ? 1 : L * L / 64); }
+
 // Words with ties, {LDS word | lattice << 16, first of its two blocks, tied
 // sites, those of class dE = 8}: kLdsTieQueue items per wave, used by that
 // wave's lanes only, in the dynamic LDS behind the lattices.
 __host__ __device__ __forceinline__ size_t lds_lattice_bytes(int L, int G, int threads)
 {
-    const size_t words = (size_t)G * 2 * (size_t)(L < 8 ? 1 : L * L / 64);
-    return (words * 4 + 15) / 16 * 16 + (size_t)(threads / 64) * kLdsTieQueue * 16;
+    return ((size_t)lds_lattice_words(L, G) * 4 + 15) / 16 * 16 + (size_t)(threads / 64) * kLdsTieQueue * 16;
 }
 
-// Threads per workgroup: one wave where that fills the chip (four waves per
-// SIMD), since its tied words then gather over all the workgroup's words and
-// no wave waits at a barrier; more where the workgroups are few.  Four
-// populations of 16384 replicas (22272 workgroups): 5.3 ms for six annealing
-// steps at 64 threads, 5.5 at 128, 6.1 at 256; 4000 replicas of L = 64 (1000
-// workgroups): 0.70, 0.61 and 0.59 ms.
-inline int lds_lattice_threads(int blocks) { return blocks >= 4096 ? 64 : blocks >= 2048 ? 128 : 256; }
+// Threads per workgroup, for `words` of its lattices (both colours): one wave
+// where that fills the chip, since its tied words then gather over all the
+// workgroup's words and no wave waits at a barrier; four, with a word a lane
+// where the lattices have no more, where the workgroups are few or LDS would
+// hold too few single waves per SIMD.  Annealing steps, us at 64, 128 and 256
+// threads: five steps of 2338 of L = 128 1000, 970 and 892, of 4096 1187, 1177
+// and 1130, of 6000 1460, 1433 and 1443; three of 8192 1107, 1155 and 1121, of
+// 16384 1819, 1925 and 1933; three of 4200 of L = 256 (8 KB each) 3080, 2676 and
+// 2420, of 8000 4700, 3922 and 3700.
+inline int lds_lattice_threads(int blocks, int words) { return blocks >= 6000 && words <= 1024 ? 64 : 256; }
 
 // Bits of the rows of odd y among the rows of one word (L < 64).
 __device__ __forceinline__ uint32_t odd_rows(int hx)
@@ -205,8 +214,23 @@ __device__ __forceinline__ LdsStencil lds_stencil(const uint32_t *lat, const Lds
     return s;
 }
 
-// Draws the low 24 bits of the tied sites of the wave's queued words, one word
-// per lane, and flips those accepted.
+// The accepted of a word's tied sites (pend; of class dE = 8: c8): their low 24
+// bits drawn one after the other.
+__device__ __forceinline__ uint32_t accept_lds_ties(const LdsLattices &a, uint32_t blk, uint32_t rep, uint32_t pend,
+                                                    uint32_t c8, uint32_t sweep_lo, uint32_t w3lo, uint32_t l4,
+                                                    uint32_t l8)
+{
+    uint32_t f = 0u;
+    while (pend) {
+        const int b = __builtin_ctz(pend);
+        pend &= pend - 1u;
+        const uint4 lo = philox(make_uint4(16u * blk + (uint32_t)b, rep, sweep_lo, w3lo), a.seed_lo, a.seed_hi);
+        if ((lo.x & 0xFFFFFFu) < (((c8 >> b) & 1u) ? l8 : l4)) f |= 1u << b;
+    }
+    return f;
+}
+
+// Settles the tied sites of the wave's queued words, one word per lane.
 template <bool PER_LAT>
 __device__ __forceinline__ void settle_lds_ties(uint32_t *lds, const LdsLattices &a, const uint4 *tq, uint32_t n,
                                                 uint32_t sweep_lo, uint32_t w3lo, uint32_t low4, uint32_t low8,
@@ -214,15 +238,9 @@ __device__ __forceinline__ void settle_lds_ties(uint32_t *lds, const LdsLattices
 {
     for (uint32_t i = threadIdx.x & 63; i < n; i += 64) {
         const uint4 it = tq[i];
-        const uint32_t g = it.x >> 16, blk = it.y, c8 = it.w;
-        uint32_t pend = it.z, f = 0u;
-        const uint32_t l4 = PER_LAT ? t4[g].low : low4, l8 = PER_LAT ? t8[g].low : low8;
-        while (pend) {
-            const int b = __builtin_ctz(pend);
-            pend &= pend - 1u;
-            const uint4 lo = philox(make_uint4(16u * blk + (uint32_t)b, a.rep0 + g, sweep_lo, w3lo), a.seed_lo, a.seed_hi);
-            if ((lo.x & 0xFFFFFFu) < (((c8 >> b) & 1u) ? l8 : l4)) f |= 1u << b;
-        }
+        const uint32_t g = it.x >> 16;
+        uint32_t f = accept_lds_ties(a, it.y, a.rep0 + g, it.z, it.w, sweep_lo, w3lo, PER_LAT ? t4[g].low : low4,
+                                     PER_LAT ? t8[g].low : low8);
         if (a.L == 4) f *= 0x01010101u;
         if (f) lds[it.x & 0xFFFFu] ^= f;
     }
@@ -232,7 +250,9 @@ __device__ __forceinline__ void settle_lds_ties(uint32_t *lds, const LdsLattices
 // reaches.
 __device__ __forceinline__ Thr lds_thr(Thr t) { return t.top >= 256u ? Thr{255u, 1u << 24} : t; }
 
-template <bool PER_LAT, bool SMALL>
+// ONE: a wave has at most one task, and each lane settles its own word's ties at
+// once; else tied words gather over the wave's tasks.
+template <bool PER_LAT, bool SMALL, bool ONE>
 __device__ void sweep_lds_words(uint32_t *lds, const LdsLattices &a, Thr u4, Thr u8, const Thr *t4, const Thr *t8,
                                 uint4 *tq)
 {
@@ -298,11 +318,19 @@ __device__ void sweep_lds_words(uint32_t *lds, const LdsLattices &a, Thr u4, Thr
                         lt = MCS_BOP3(X, T, lt, (~MCS_A & MCS_B) | (~MCS_A & MCS_C) | (MCS_B & MCS_C));
                         eq = MCS_BOP3(eq, X, T, MCS_A & ~(MCS_B ^ MCS_C));
                     }
-                    lat[(c ? a.P : 0) + p] = MCS_BOP3(s.S, ge2, lt, MCS_A ^ (MCS_B | MCS_C));
+                    uint32_t Sn = MCS_BOP3(s.S, ge2, lt, MCS_A ^ (MCS_B | MCS_C));
                     pend = eq & ~ge2;
                     if (SMALL && a.L == 4) pend &= 0xFFu;
+                    if (ONE) {
+                        uint32_t f = accept_lds_ties(a, blk, rep, pend, c8, (uint32_t)sweep, w3lo,
+                                                     PER_LAT ? t4[g].low : u4.low, PER_LAT ? t8[g].low : u8.low);
+                        if (SMALL && a.L == 4) f *= 0x01010101u;
+                        Sn ^= f;
+                    }
+                    lat[(c ? a.P : 0) + p] = Sn;
                     wsg = (uint32_t)(2 * g * a.P + (c ? a.P : 0) + p) | ((uint32_t)g << 16);
                 }
+                if (ONE) continue;
                 const uint64_t m = __ballot(pend != 0u);
                 if (pend) {
                     const uint32_t at = qn + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
@@ -339,8 +367,11 @@ __device__ void sweep_lds_lattices(uint32_t *lds, const LdsLattices &a, Thr u4, 
 {
     const bool small = a.L < 64;
     uint4 *tq = (uint4 *)(lds + (((size_t)a.ng_max * 2 * a.P + 3) & ~(size_t)3)) + (threadIdx.x >> 6) * kLdsTieQueue;
-    if (small) sweep_lds_words<PER_LAT, true>(lds, a, u4, u8, t4, t8, tq);
-    else sweep_lds_words<PER_LAT, false>(lds, a, u4, u8, t4, t8, tq);
+    const bool one = a.ng * a.P <= (int)blockDim.x;
+    if (small && one) sweep_lds_words<PER_LAT, true, true>(lds, a, u4, u8, t4, t8, tq);
+    else if (small) sweep_lds_words<PER_LAT, true, false>(lds, a, u4, u8, t4, t8, tq);
+    else if (one) sweep_lds_words<PER_LAT, false, true>(lds, a, u4, u8, t4, t8, tq);
+    else sweep_lds_words<PER_LAT, false, false>(lds, a, u4, u8, t4, t8, tq);
     // ---- energy over the odd sites' words (every bond has one odd end)
     const int tasks = a.ng * a.P;
     for (int t = threadIdx.x; t < tasks; t += blockDim.x) {
