@@ -13,16 +13,18 @@
 // A sweep is two launches (coarse colour 0, then 1).  The per-word update
 // (four neighbour words, Metropolis classes from 3-input bit operations, the
 // random top bytes as eight bit-planes from two Philox blocks, a bit-serial
-// compare, ties settled from a queue of the wave) is the 2D band kernel's
-// (metro2d.hpp).
+// compare, ties settled by the word's own lane or from a queue of the wave) is
+// the 2D band kernel's (metro2d.hpp).
 //
 // What bounds it: VALU issue from ten hits on, with one hit the launch, the
 // tile's load and the sums.  Attempted updates per ns, 4096^2 x 3, tiles of 128,
-// at one, ten and a hundred hits: 2000, 4320 and 5050; 1980, 4285 and 5025 with
-// the workgroups of a CU settling ties on one SIMD at a time; 1330, 3880 and 4980 with
-// tiles side by side on different XCDs (each then loads whole lines for 8 bytes
-// of a row), 1340, 3790 and 4660 with every wave settling its own ties, 1180,
-// 3050 and 3700 with a comparison per class besides.
+// at one, ten and a hundred hits: 2050, 4370 and 5060; 2000, 4320 and 5040 with
+// one wave at a time settling the ties of all between two barriers; 1330, 3880
+// and 4980 with tiles side by side on different XCDs besides (each then loads
+// whole lines for 8 bytes of a row); 1180, 3050 and 3700 with a comparison per
+// class besides.  One lattice of 2048^2, ten hits: 400 us for ten sweeps, 490
+// with each wave's ties through its queue in LDS although a lane has one word;
+// tiles of 64 (4096^2 x 3) 1122 and 1224.
 //
 // Energy and magnetisation of a sweep: every bond lies inside one tile or
 // joins a tile of colour 0 to one of colour 1.  Colour-0 tiles are final
@@ -46,7 +48,6 @@ struct DcbArgs {
     int L, T;                   // extent, tile side (multiples of 64)
     int coarse;                 // colour of the tiles of this launch
     int hits;
-    int pool;                   // one wave at a time settles the ties of all
     uint32_t replica0;
     uint64_t sweep;             // global sweep number; hit h draws as plain sweep sweep * hits + h
     uint32_t seed_lo, seed_hi;
@@ -65,12 +66,14 @@ __device__ __forceinline__ void dcb_tile(const DcbArgs &a, int b, int &tx, int &
     tx = 2 * (b - ty * half) + ((ty + a.coarse) & 1);
 }
 
+// ONE: a lane has one word and settles its ties at once; else a wave's tied words
+// gather over its lanes' words.
+template <bool ONE>
 __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
 {
     extern __shared__ uint32_t lds[];
     __shared__ int red[2][kDcbMaxWaves];
     __shared__ long long red_prev[2][16];
-    __shared__ uint32_t tied[kDcbMaxWaves];
     const int l = blockIdx.y;
     int tx, ty;
     dcb_tile(a, blockIdx.x, tx, ty);
@@ -88,7 +91,6 @@ __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
     auto widx = [&](int r, int par, int c) { return (r * 2 + par) * Ww + c; };
     const MetroMasks mm = metro_masks(a.t4.top, a.t8.top, true);
     uint4 *const queue = (uint4 *)(lds + ((rows * 2 * Ww + 3) & ~3));  // behind the tile
-    const int nsh = 31 - __builtin_clz(nwaves);  // the waves are a power of two in number
     const int slots_per_lattice = (a.L / a.T) * (a.L / a.T);
     long long pre_e, pre_m;
     em_prefetch(a.prev, blockIdx.x, slots_per_lattice, l, gridDim.y, tid, pre_e, pre_m);
@@ -122,10 +124,6 @@ __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
 
     const int tasks = a.T * Wt;  // words of one colour: one per (row, column), a multiple of the threads
     uint4 *const tq = queue + wave * kTieQueue;
-    // the wave that settles, in turn (a wave's SIMD is that of its number); the
-    // workgroups of one CU, 256 apart, start with different waves
-    const int wg = (int)(l * gridDim.x + blockIdx.x);
-    int turn = wg + (wg >> 8);
     for (int h = 0; h < a.hits; ++h) {
         const uint64_t dsweep = a.sweep * (uint64_t)a.hits + (uint64_t)h;
         for (int col = 0; col < 2; ++col) {
@@ -156,6 +154,11 @@ __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
                 const uint4 A = philox(make_uint4(blk, rep, (uint32_t)dsweep, w3), a.seed_lo, a.seed_hi);
                 const uint4 B = philox(make_uint4(blk + 1u, rep, (uint32_t)dsweep, w3), a.seed_lo, a.seed_hi);
                 const MetroWord mw = metro_update(S, U, D, O, Sh, A, B, mm);
+                if constexpr (ONE) {
+                    lds[is] = mw.S ^ metro_settle(mw.pend, mw.c8, blk, rep, (uint32_t)dsweep, w3lo, a.seed_lo,
+                                                  a.seed_hi, a.t4.low, a.t8.low);
+                    continue;
+                }
                 lds[is] = mw.S;
                 const uint64_t m = __ballot(mw.pend != 0u);
                 const uint32_t cnt = (uint32_t)__popcll(m);
@@ -166,18 +169,7 @@ __global__ __launch_bounds__(64 * kDcbMaxWaves) void k_dcb(DcbArgs a)
                 if (mw.pend) tq[qn + wave_rank(m)] = make_uint4((uint32_t)is, blk, mw.pend, mw.c8);
                 qn += cnt;
             }
-            if (a.pool) {
-                if ((tid & 63) == 0) tied[wave] = qn;
-                __syncthreads();
-                // the queues of all waves, an equal share of a wave's lanes each
-                if (wave == (turn++ & (nwaves - 1))) {
-                    const int sh = 6 - nsh, of = (tid & 63) >> sh;
-                    for (uint32_t i = tid & ((1 << sh) - 1), n = tied[of]; __any(i < n); i += 1u << sh)
-                        if (i < n) settle(queue[of * kTieQueue + i]);
-                }
-            } else if ((uint32_t)(tid & 63) < qn) {
-                settle(tq[tid & 63]);
-            }
+            if (!ONE && (uint32_t)(tid & 63) < qn) settle(tq[tid & 63]);
             __syncthreads();
         }
     }
@@ -292,13 +284,8 @@ hipError_t launch_dcb_phase(uint32_t *packed, int L, int T, int count, int coars
     int threads = std::min(256, T * T / 64);
     while (threads < std::min(64 * kDcbMaxWaves, T * T / 64) && (int64_t)tiles * count * (threads / 64) < 3072)
         threads *= 2;
-    // One wave settles the ties of all four where their six or so each would
-    // take four passes, and where other workgroups fill the second barrier's
-    // wait: tiles of 128, 4096^2 x 3 (1536 workgroups) 3980 against 3790, 1024
-    // workgroups 3190 against 3150, 512 2240 against 2350; tiles of 256, whose
-    // waves gather four words' ties per lane, 4350 against 4840 (768).
-    a.pool = threads > 64 && threads == T * T / 64 && (int64_t)tiles * count >= 1024;
-    hipLaunchKernelGGL(k_dcb, dim3((unsigned)tiles, (unsigned)count), dim3(threads), dcb_lds_bytes(T, threads), s, a);
+    const auto f = threads == T * T / 64 ? k_dcb<true> : k_dcb<false>;
+    hipLaunchKernelGGL(f, dim3((unsigned)tiles, (unsigned)count), dim3(threads), dcb_lds_bytes(T, threads), s, a);
     return hipGetLastError();
 }
 
