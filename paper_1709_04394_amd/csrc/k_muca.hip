@@ -180,9 +180,14 @@ __global__ __launch_bounds__(64 * kMucaMaxWaves) void k_muca_q(MucaArgs a)
     const int w = live ? wr : a.W - 1;
     int8_t *sp = a.spins + (int64_t)w * N;
     const uint32_t rec = (a.record && live) ? 1u : 0u;
-    // 16-bit counts: between two exchanges of a word, whichever wave makes them,
-    // each of the workgroup's waves adds at most kFlushRows rows of 16 walkers
-    constexpr int kFlushRows = 65535 / (16 * kMucaMaxWaves * L) > 0 ? 65535 / (16 * kMucaMaxWaves * L) : 1;
+    // 16-bit counts: every wave exchanges the counts it finds after each kFlushRows
+    // of its rows, from one sweep to the next as within one, so that between two
+    // exchanges of a word, whichever wave makes them, each of the workgroup's
+    // waves adds at most kFlushRows rows of 16 walkers, all of them perhaps to
+    // one level
+    constexpr int kFlushRows = 65535 / (16 * kMucaMaxWaves * L);
+    static_assert(M::kWide || (kFlushRows >= 1 && kFlushRows * 16 * kMucaMaxWaves * L < 65536), "16-bit counts");
+    int rows_since_flush = 0;
     // z: LDS address of the level's row, plus 8 where the row is indexed by -4 step
     const int zb = lds_addr(lds) + (M::kWide ? 8 : 0);
     int z = S * (int)((a.E[w] + 2 * N) / 4) + zb;
@@ -198,7 +203,6 @@ __global__ __launch_bounds__(64 * kMucaMaxWaves) void k_muca_q(MucaArgs a)
         quad_pack<L>(raw, C);
         quad_load<L>(sp, 1, q, raw);
         quad_pack<L>(raw, D);
-        int rows_since_flush = 0;
         for (int y = 0; y < L; ++y) {
             const bool pre = y + 2 < L;
             if (pre) quad_load<L>(sp, y + 2, q, raw);
