@@ -10,7 +10,9 @@
 // (131 KB at L = 128, within gfx950's 160 KB).  Moves that would leave the
 // energy window [-2N, 0] are rejected and the current level is counted again.
 // k_muca_q (four lanes per walker) does the sweeps; k_muca (one lane per
-// walker) is the plain form, kept for the one table the other cannot hold.
+// walker) those of small lattices without counting where there are walkers
+// enough to fill the chip one lane each, and the one table the other cannot
+// hold.
 #include <algorithm>
 
 #include "internal.hpp"
@@ -379,10 +381,9 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n)
         p[i] = 0u;
 }
 
-// One lane per walker, counts in global slices; taken only when a threshold is
-// 2^32 - 1, which k_muca_q cannot tell from 2^32.
+// One lane per walker, counts in global slices.
 template <int L>
-static hipError_t launch_muca_edge(const MucaArgs &a, hipStream_t s)
+static hipError_t launch_muca_lane(const MucaArgs &a, hipStream_t s)
 {
     constexpr int K = L * L / 2;
     const int nb = (a.W + 63) / 64;
@@ -396,10 +397,27 @@ static hipError_t launch_muca_edge(const MucaArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
+// Walkers from which, without counting, one lane each is faster than four: four
+// lanes take less time per update while SIMDs are idle, and more instructions.
+// us per sweep, four lanes (one): L = 4, 32768 walkers 3.6 (3.6), 65536 5.5 (3.7),
+// 2^20 61 (15); L = 8, 65536 13.1 (13.5), 98304 17.9 (15.0); L = 12, 65536 24.0
+// (28.7), 98304 33.7 (32.5), 262144 84 (82), but 524288 163 (172); L = 16, 98304
+// 53 (59), 131072 68 (59), 2^20 500 (469); L = 24, 98304 131 (133), 131072 170
+// (135); L = 32, 98304 208 (237), 131072 270 (244), 524288 979 (824); L = 48,
+// 131072 596 (803), L = 64 1071 (2057).  With counting the lanes' atomics cost
+// more than that at every number.
+template <int L>
+static bool lane_walkers(int W)
+{
+    if (L == 12) return W > 90112 && W <= 294912;
+    return L <= 32 && W > (L == 4 ? 32768 : L == 8 ? 65536 : 106496);
+}
+
 template <int L>
 static hipError_t launch_muca_L(const MucaArgs &a, hipStream_t s)
 {
-    if (a.edge) return launch_muca_edge<L>(a, s);
+    // a threshold of 2^32 - 1: k_muca_q cannot tell it from 2^32
+    if (a.edge || (!a.record && lane_walkers<L>(a.W))) return launch_muca_lane<L>(a, s);
     static LdsLimit lim;
     const hipError_t e = lim.ensure((const void *)k_muca_q<L>, MucaRow<L>::LDS);
     if (e != hipSuccess) return e;
