@@ -11,8 +11,7 @@
 // energy window [-2N, 0] are rejected and the current level is counted again.
 // k_muca_q (four lanes per walker) does the sweeps; k_muca (one lane per
 // walker) those of small lattices without counting where there are walkers
-// enough to fill the chip one lane each, and the one table the other cannot
-// hold.
+// enough to fill the chip one lane each.
 #include <algorithm>
 
 #include "internal.hpp"
@@ -34,7 +33,6 @@ __global__ __launch_bounds__(64) void k_muca(MucaArgs a)
     if (w >= a.W) return;
     int8_t *sp = a.spins + (int64_t)w * N;
     int k = (int)((a.E[w] + 2 * N) / 4);
-    uint32_t *hist = a.hist + (int64_t)blockIdx.x * (K + 1);
     for (int t = 0; t < a.nsweeps; ++t) {
         const uint64_t sweep = a.sweep0 + (uint64_t)t;
         const uint32_t w3 = ctr_w3(kTagMuca, 0, sweep);
@@ -63,7 +61,6 @@ __global__ __launch_bounds__(64) void k_muca(MucaArgs a)
                     cur[x / 32] ^= 1u << (x % 32);
                     k = k2;
                 }
-                if (a.record) atomicAdd(&hist[k], 1u);
             }
             store_row<L>(sp, y, cur);
             if (y == 0) {
@@ -86,9 +83,9 @@ __global__ __launch_bounds__(64) void k_muca(MucaArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// k_muca_q<L>: the same walk with four lanes per walker (quad_walk.hpp).  It
-// draws the same random numbers, takes the same decisions and records the same
-// levels as k_muca<L>.
+// k_muca_q<L>: the same walk with four lanes per walker (quad_walk.hpp), the
+// visited levels counted.  It draws the same random numbers and takes the same
+// decisions as k_muca<L>.
 //
 // What an update costs is the instructions its wave issues, so little is left
 // on the chain:
@@ -102,7 +99,9 @@ __global__ __launch_bounds__(64) void k_muca(MucaArgs a)
 //  * the row has an entry that always accepts for a = 2 and entries that never
 //    accept for moves out of the window (T as a 32-bit word, 2^32 stored as
 //    2^32 - 1 and r as min(r, 2^32 - 2); exact unless a threshold is 2^32 - 1
-//    itself, for which the launcher takes k_muca);
+//    itself.  EXACT is the form for such a table: T - 1 stored, r <= T - 1, and
+//    the window's end a compare of its own, 16 to 21 % slower: L = 64, 4096
+//    walkers 308 us per sweep against 261);
 //  * every fourth update the four lanes count the levels of the last four
 //    updates with one LDS atomic, each lane one of them.
 // Rows are six words (five entries and the count) for L <= 96.  L = 128 has
@@ -148,7 +147,7 @@ __device__ __forceinline__ void muca_flush(uint32_t *lds, int64_t *H, int lane)
     }
 }
 
-template <int L>
+template <int L, bool EXACT>
 __global__ __launch_bounds__(64 * kMucaMaxWaves) void k_muca_q(MucaArgs a)
 {
     using R = QuadRow<L>;
@@ -161,7 +160,7 @@ __global__ __launch_bounds__(64 * kMucaMaxWaves) void k_muca_q(MucaArgs a)
     for (int i = tid; i < (K + 1) * 4; i += nt) {
         const int k = i >> 2, e = i & 3, step = e < 2 ? e - 2 : e - 1;
         const uint32_t v = a.table[i];
-        const uint32_t T = k + step > K ? 0u : v == ~0u ? ~0u : v + 1u;
+        const uint32_t T = EXACT ? v : k + step > K ? 0u : v == ~0u ? ~0u : v + 1u;
         if constexpr (M::kWide) lds[k * 6 + 2 - step] = T;
         else lds[k * 4 + (step == -2 ? 2 : 2 - step)] = T;
     }
@@ -191,7 +190,7 @@ __global__ __launch_bounds__(64 * kMucaMaxWaves) void k_muca_q(MucaArgs a)
     static_assert(M::kWide || (kFlushRows >= 1 && kFlushRows * 16 * kMucaMaxWaves * L < 65536), "16-bit counts");
     int rows_since_flush = 0;
     // z: LDS address of the level's row, plus 8 where the row is indexed by -4 step
-    const int zb = lds_addr(lds) + (M::kWide ? 8 : 0);
+    const int zb = lds_addr(lds) + (M::kWide ? 8 : 0), zend = zb + S * K;
     int z = S * (int)((a.E[w] + 2 * N) / 4) + zb;
     for (int t = 0; t < a.nsweeps; ++t) {
         const uint64_t sweep = a.sweep0 + (uint64_t)t;
@@ -222,8 +221,8 @@ __global__ __launch_bounds__(64 * kMucaMaxWaves) void k_muca_q(MucaArgs a)
                         blk = philox(make_uint4(ctr0, (uint32_t)w, (uint32_t)sweep, w3), a.seed_lo, a.seed_hi);
                     PhiloxRounds ahead;
                     ahead.c = make_uint4(ctr0 + 4u, (uint32_t)w, (uint32_t)sweep, w3);
-                    const uint32_t r4[4] = {min(blk.x, 0xFFFFFFFEu), min(blk.y, 0xFFFFFFFEu), min(blk.z, 0xFFFFFFFEu),
-                                            min(blk.w, 0xFFFFFFFEu)};
+                    constexpr uint32_t kTop = EXACT ? ~0u : ~0u - 1u;
+                    const uint32_t r4[4] = {min(blk.x, kTop), min(blk.y, kTop), min(blk.z, kTop), min(blk.w, kTop)};
                     const QuadCounts qc = quad_counts(P, sh);
                     // i0, i1: table offset for a rejected / accepted previous
                     // update; s0, s1: the step in bytes
@@ -272,7 +271,8 @@ __global__ __launch_bounds__(64 * kMucaMaxWaves) void k_muca_q(MucaArgs a)
                         }
                         uint32_t r = quad_get(r4[I], Q);
                         if (!M::kWide) r = zn == z ? 0u : r;  // a = 2: any threshold accepts
-                        const bool ok = r < (acc ? T1 : T0);
+                        const uint32_t T = acc ? T1 : T0;
+                        const bool ok = EXACT ? r <= T && zn <= zend : r < T;
                         z = ok ? zn : z;
                         zn = ok ? p1 : p0;
                         Fg = shift_in(Fg, __ballot(ok));
@@ -365,38 +365,6 @@ __global__ void k_muca_start(int8_t *spins, int64_t *E, int L, int W)
     E[w] = e;
 }
 
-// H[k] += sum over workgroup slices of their counts (fixed order).
-__global__ void k_muca_merge(const uint32_t *slices, int nslices, int nlev, int64_t *H)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nlev) return;
-    int64_t s = 0;
-    for (int b = 0; b < nslices; ++b) s += slices[(int64_t)b * nlev + k];
-    H[k] += s;
-}
-
-__global__ void k_fill_u32(uint32_t *p, int64_t n)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0u;
-}
-
-// One lane per walker, counts in global slices.
-template <int L>
-static hipError_t launch_muca_lane(const MucaArgs &a, hipStream_t s)
-{
-    constexpr int K = L * L / 2;
-    const int nb = (a.W + 63) / 64;
-    if (a.record) hipLaunchKernelGGL(k_fill_u32, dim3(256), dim3(256), 0, s, a.hist, (int64_t)nb * (K + 1));
-    const size_t lds = (size_t)(K + 1) * 4 * 4;
-    static LdsLimit lim;
-    const hipError_t e = lim.ensure((const void *)k_muca<L>, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_muca<L>, dim3(nb), dim3(64), lds, s, a);
-    if (a.record) hipLaunchKernelGGL(k_muca_merge, dim3((K + 256) / 256), dim3(256), 0, s, a.hist, nb, K + 1, a.H);
-    return hipGetLastError();
-}
-
 // Walkers from which, without counting, one lane each is faster than four: four
 // lanes take less time per update while SIMDs are idle, and more instructions.
 // us per sweep, four lanes (one): L = 4, 32768 walkers 3.6 (3.6), 65536 5.5 (3.7),
@@ -407,27 +375,41 @@ static hipError_t launch_muca_lane(const MucaArgs &a, hipStream_t s)
 // 131072 596 (803), L = 64 1071 (2057).  With counting the lanes' atomics cost
 // more than that at every number.
 template <int L>
-static bool lane_walkers(int W)
+static bool lane_walkers(int W)  // L <= 32
 {
     if (L == 12) return W > 90112 && W <= 294912;
-    return L <= 32 && W > (L == 4 ? 32768 : L == 8 ? 65536 : 106496);
+    return W > (L == 4 ? 32768 : L == 8 ? 65536 : 106496);
 }
 
 template <int L>
-static hipError_t launch_muca_L(const MucaArgs &a, hipStream_t s)
+static hipError_t launch_muca_lane(const MucaArgs &a, hipStream_t s)
 {
-    // a threshold of 2^32 - 1: k_muca_q cannot tell it from 2^32
-    if (a.edge || (!a.record && lane_walkers<L>(a.W))) return launch_muca_lane<L>(a, s);
+    const size_t lds = (size_t)(L * L / 2 + 1) * 4 * 4;
+    hipLaunchKernelGGL(k_muca<L>, dim3((a.W + 63) / 64), dim3(64), lds, s, a);
+    return hipGetLastError();
+}
+
+template <int L, bool EXACT>
+static hipError_t launch_muca_q(const MucaArgs &a, hipStream_t s)
+{
     static LdsLimit lim;
-    const hipError_t e = lim.ensure((const void *)k_muca_q<L>, MucaRow<L>::LDS);
+    const hipError_t e = lim.ensure((const void *)k_muca_q<L, EXACT>, MucaRow<L>::LDS);
     if (e != hipSuccess) return e;
     // one wave per workgroup until every CU has one, then up to four waves
     // sharing a table (at L = 128 a CU holds one table)
     constexpr int kCUs = 256;
     const int waves = (a.W + 15) / 16;
     const int per = std::min(kMucaMaxWaves, std::max(1, (waves + kCUs - 1) / kCUs));
-    hipLaunchKernelGGL(k_muca_q<L>, dim3((waves + per - 1) / per), dim3(64 * per), MucaRow<L>::LDS, s, a);
+    hipLaunchKernelGGL((k_muca_q<L, EXACT>), dim3((waves + per - 1) / per), dim3(64 * per), MucaRow<L>::LDS, s, a);
     return hipGetLastError();
+}
+
+template <int L>
+static hipError_t launch_muca_L(const MucaArgs &a, hipStream_t s)
+{
+    if constexpr (L <= 32)
+        if (!a.record && lane_walkers<L>(a.W)) return launch_muca_lane<L>(a, s);
+    return a.edge ? launch_muca_q<L, true>(a, s) : launch_muca_q<L, false>(a, s);
 }
 
 bool muca_L_supported(int L)

@@ -9,7 +9,6 @@ struct MucaArgs {
     int8_t *spins;          // [W][L*L] int8 walker lattices (in/out)
     int64_t *E;             // [W] walker energies (in/out)
     const uint32_t *table;  // [(K+1)*4] thresholds minus one, direction -2, -1, +1, +2
-    uint32_t *hist;         // [ceil(W/64)][K+1] per-workgroup counts of k_muca (scratch)
     int64_t *H;             // [K+1] histogram the counts are added to
     int W;
     uint32_t seed_lo, seed_hi;

@@ -15,18 +15,17 @@ namespace {
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct MucaLayout {
-    size_t table = 0, hist = 0, H = 0, E = 0, prep = 0, prep_bytes = 0, total = 0;
+    size_t table = 0, H = 0, E = 0, prep = 0, prep_bytes = 0, total = 0;
 };
 
 constexpr int kPrepGroups = 16;  // walker groups of the preparation sweeps
 
 MucaLayout muca_layout(int L, int W)
 {
-    const size_t nlev = (size_t)L * L / 2 + 1, nb = (size_t)(W + 63) / 64;
+    const size_t nlev = (size_t)L * L / 2 + 1;
     MucaLayout m;
     size_t off = 0;
     m.table = off, off += align256(nlev * 16);
-    m.hist = off, off += align256(nb * nlev * 4);
     m.H = off, off += align256(nlev * 8);
     m.E = off, off += align256((size_t)W * 8);
     // fused-sweep scratch for the largest preparation group
@@ -86,7 +85,6 @@ int run_muca_sweeps(mc_ctx *ctx, int L, int W, int8_t *spins, int64_t *E, const 
     a.spins = spins;
     a.E = E;
     a.table = (const uint32_t *)(ws + lay.table);
-    a.hist = (uint32_t *)(ws + lay.hist);
     a.H = H;
     a.W = W;
     a.seed_lo = (uint32_t)seed;

@@ -47,3 +47,12 @@ def _slope(L, b):
 @pytest.mark.parametrize("L,W,bound", [(4, 1 << 20, 30.0), (8, 1 << 18, 32.0), (24, 1 << 18, 290.0)])
 def test_many_walkers_without_counting(ctx, L, W, bound):
     assert _muca_us(ctx, L, W, _slope(L, 0.3), 20 if L < 24 else 6, False) < bound
+
+
+# a table with a threshold of 2^32 - 1 takes 1.2 times an ordinary one's time, a
+# kernel with one lane per walker 2.8 to 4.3 times
+@pytest.mark.parametrize("L", [32, 64, 128])
+def test_threshold_next_to_one(ctx, L):
+    W, n = 4096, 4 if L < 128 else 1
+    plain = _muca_us(ctx, L, W, _slope(L, 0.4), n, True)
+    assert _muca_us(ctx, L, W, -3e-10 * np.arange(L * L // 2 + 1), n, True) < 1.8 * plain

@@ -1,6 +1,7 @@
 """Multicanonical sweeps without counting on both sides of the walker numbers
 from which one lane per walker is taken, bit for bit against the oracle, with an
-unfilled last wave and a threshold of 2^32 - 1 besides."""
+unfilled last wave and a threshold of 2^32 - 1 besides; and tables with that
+threshold counted, for every row shape."""
 import numpy as np
 import pytest
 import torch
@@ -29,5 +30,24 @@ def test_walker_numbers(ctx, L, W, step):
     torch.cuda.synchronize()
     os_, oE = oracle.muca_start(L, W, 41, 0)
     oracle.muca_sweeps(L, os_, oE, lnW, 41, (1 << 32) - 1, 2, False)
+    assert np.array_equal(E.cpu().numpy(), oE)
+    assert np.array_equal(spins.cpu().numpy().reshape(-1), os_)
+
+
+@pytest.mark.parametrize("L,W", [(4, 33), (8, 4113), (12, 33), (16, 33), (24, 33), (32, 33), (48, 33), (64, 33), (96, 17),
+                                 (128, 17)])
+def test_threshold_next_to_one_counted(ctx, L, W):
+    # flat weights but for thresholds of 2^32 - 1 downwards: the walkers press
+    # against the window's end
+    K = L * L // 2
+    lnW = -3e-10 * (K - np.arange(K + 1))
+    spins, E = ctx.muca_start(L, W, 43)
+    H = torch.zeros(K + 1, dtype=torch.int64, device="cuda")
+    ctx.muca_sweeps(L, spins, E, lnW, 43, 5, 3, True, H=H)
+    torch.cuda.synchronize()
+    os_, oE = oracle.muca_start(L, W, 43, 0)
+    oH = oracle.muca_sweeps(L, os_, oE, lnW, 43, 5, 3, True)
+    assert oH[K] > 0
+    assert np.array_equal(H.cpu().numpy(), oH)
     assert np.array_equal(E.cpu().numpy(), oE)
     assert np.array_equal(spins.cpu().numpy().reshape(-1), os_)
