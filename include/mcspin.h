@@ -244,8 +244,9 @@ int mc_measure(mc_ctx *ctx, const mc_geom *geom, const void *spins, const int8_t
  * set or tuned plan run whole in a workgroup instead), MC_PATH_SMALL_BITS
  * (small int8 lattices of 32-site rows) and MC_PATH_SMALL (other small int8
  * lattices): whole in one workgroup's LDS as bits, every sweep of a call in
- * one launch (above 2^17 sites half-sweeps), MC_PATH_MSC64 (64-lane words, Lx
- * a multiple of 128), MC_PATH_GENERIC (one launch per half-sweep).  Results never depend on the
+ * one launch (few lattices of above 2^17 sites: half-sweeps), MC_PATH_MSC64
+ * (64-lane words, Lx a multiple of 128), MC_PATH_GENERIC (one launch per
+ * half-sweep).  Results never depend on the
  * path.  Host only: no device work.  Errors as for mc_sweep's geometry and
  * rule; MC_E_LAYOUT for per_lattice with MC_MSC64; MC_E_INVAL for a NULL
  * path.                                                                    */

@@ -176,7 +176,7 @@ hipError_t launch_measure_msc64(const Geom &g, const uint64_t *words, const int8
 bool half_supported(const Geom &g);
 hipError_t launch_half(const SweepCall &c, int8_t *spins, uint64_t sweep, int phase, int64_t *EM, hipStream_t s);
 // every sweep of a call with each int8 lattice whole in a workgroup (k_whole.hip)
-bool whole_supported(const Geom &g);
+bool whole_supported(const Geom &g, bool hasJ, int nsweeps);
 hipError_t launch_whole(const SweepCall &c, int8_t *spins, uint64_t sweep0, int nsweeps, int64_t *EM,
                         int64_t em_stride, hipStream_t s);
 // generic in-place half-sweep, any even geometry, int8

@@ -135,6 +135,33 @@ __device__ __forceinline__ WordGeo word_geo(const WholeArgs &a, uint32_t w)
     return g;
 }
 
+// Rows of 32 sites, BITS = 32: an item is rows 2w and 2w + 1, of one plane.
+__device__ __forceinline__ WordGeo word_geo_rows32(const WholeArgs &a, uint32_t w)
+{
+    WordGeo g;
+    const uint32_t row = 2u * w, z = quotient28(row, a.Ly, a.mul_ly), y = row - z * a.Ly;
+    g.w = w;
+    g.odd = (z & 1u) ? 0x0000FFFFu : 0xFFFF0000u;
+    g.first = 0x00010001u;
+    g.last = 0x80008000u;
+    g.top = y + 2u == a.Ly ? 0xFFFF0000u : 0u;
+    g.bottom = y == 0u ? 0x0000FFFFu : 0u;
+    g.valid = ~0u;
+    return g;
+}
+
+// A thread's items in that case: any number of them, nothing kept.
+struct Rows32Items {
+    const WholeArgs &a;
+    uint32_t tid, nt;
+    __device__ __forceinline__ WordGeo operator[](int k) const { return word_geo_rows32(a, tid + k * nt); }
+};
+
+struct Rows32Mine {
+    uint32_t tid, nt, items;
+    __device__ __forceinline__ bool operator[](int k) const { return tid + k * nt < items; }
+};
+
 __device__ __forceinline__ uint32_t bit_mux(uint32_t sel, uint32_t hi, uint32_t lo)
 {
     return MCS_BOP3(sel, hi, lo, (MCS_A & MCS_B) | (~MCS_A & MCS_C));
@@ -212,12 +239,17 @@ __device__ __forceinline__ void store_pairs(int8_t *p, uint32_t ev, uint32_t od)
     }
 }
 
-// K: items of BITS sites of a colour per thread
+// K: items of BITS sites of a colour per thread, what their sites share kept in
+// registers; 0: as many as there are, of rows of 32 sites without couplings, what
+// they share found again in every half-sweep
 template <int DIMS, int RULE, bool HASJ, int K, bool ALIGNED, int BITS>
 __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
 {
     constexpr bool HB = RULE != kMetropolis;
     constexpr int Z = 2 * DIMS;
+    constexpr bool LOOP = K == 0;
+    static_assert(!LOOP || (!HASJ && ALIGNED && BITS == 32), "rows of 32 sites");
+    constexpr int KA = LOOP ? 1 : K;
     using item_t = typename WholeItem<BITS>::type;
     extern __shared__ uint32_t sm[];  // spins [2][stride], then couplings [2][Z][stride]
     __shared__ uint32_t tlow[8];
@@ -235,14 +267,25 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
     if (tid < 8) tlow[tid] = a.low[tid];
     if (tid < 2) sums[tid] = 0ull;
     int8_t *src = a.spins + (int64_t)l * N;
-    WordGeo g[K];
-    bool mine[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
+    struct Kept {
+        WordGeo g[KA];
+        bool mine[KA];
+    } kept;
+    auto &&g = [&]() -> decltype(auto) {
+        if constexpr (LOOP) return Rows32Items{a, tid, nt};
+        else return (kept.g);
+    }();
+    auto &&mine = [&]() -> decltype(auto) {
+        if constexpr (LOOP) return Rows32Mine{tid, nt, items};
+        else return (kept.mine);
+    }();
+    const int nk = LOOP ? (int)((items + nt - 1) / nt) : K;
+#pragma unroll KA
+    for (int k = 0; k < nk; ++k) {
         const uint32_t w = tid + k * nt;
-        mine[k] = w < items;
+        if constexpr (!LOOP) mine[k] = w < items;
         if (!mine[k]) continue;
-        g[k] = word_geo<DIMS, BITS>(a, w);
+        if constexpr (!LOOP) g[k] = word_geo<DIMS, BITS>(a, w);
         uint32_t ev, od;
         pack_pairs<BITS>(src, w, a.half, ev, od);
         put(S, w, bit_mux(g[k].odd, od, ev));
@@ -258,7 +301,7 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
     }
     __syncthreads();
     if (HASJ) {
-        uint32_t j0[2][K];
+        uint32_t j0[2][KA];
 #pragma unroll
         for (int k = 0; k < K; ++k)
             if (mine[k])
@@ -315,8 +358,8 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
             uint32_t *own = S + c * stride;
             uint32_t *oth = S + (1 - c) * stride;
             uint32_t count = 0;  // down spins << 16 | unsatisfied bonds, of this thread's words
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
+#pragma unroll KA
+            for (int k = 0; k < nk; ++k) {
                 if (!mine[k]) continue;
                 const uint32_t w = g[k].w;
                 uint32_t n[6];
@@ -383,9 +426,16 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
                 }
             }
             if (c == 1 && a.EM) {
-                const uint32_t v = (uint32_t)__builtin_amdgcn_readlane(wave_sum_last((int)count), 63);
-                if ((tid & 63u) == 0u)
-                    atomicAdd(&sums[t & 1], (unsigned long long)(v & 0xFFFFu) | (unsigned long long)(v >> 16) << 32);
+                uint32_t u, dn;
+                if constexpr (LOOP) {  // up to eight items a thread: more than 16 bits in a wave
+                    u = (uint32_t)__builtin_amdgcn_readlane(wave_sum_last((int)(count & 0xFFFFu)), 63);
+                    dn = (uint32_t)__builtin_amdgcn_readlane(wave_sum_last((int)(count >> 16)), 63);
+                } else {
+                    const uint32_t v = (uint32_t)__builtin_amdgcn_readlane(wave_sum_last((int)count), 63);
+                    u = v & 0xFFFFu;
+                    dn = v >> 16;
+                }
+                if ((tid & 63u) == 0u) atomicAdd(&sums[t & 1], (unsigned long long)u | (unsigned long long)dn << 32);
             }
             // the sums of the sweep before: complete at its end, and next added
             // to after this half-sweep's barrier
@@ -395,8 +445,8 @@ __global__ __launch_bounds__(1024) void k_whole(WholeArgs a)
     }
     if (a.EM) publish(a.nsweeps - 1);
     // back to columns: even in S[0], odd in S[1]
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
+#pragma unroll KA
+    for (int k = 0; k < nk; ++k) {
         if (!mine[k]) continue;
         const uint32_t w = g[k].w, s0 = item(S)[w], s1 = item(S + stride)[w];
         const uint32_t ev = bit_mux(g[k].odd, s1, s0), od = bit_mux(g[k].odd, s0, s1);
@@ -423,8 +473,25 @@ static size_t whole_lds_bytes(const Geom &g, bool hasJ)
 }
 
 // Two words per thread: the sums of a wave fit their 16 bits, and above 2^17
-// sites one workgroup takes longer than two launches over the whole chip.
-bool whole_supported(const Geom &g) { return g.N <= (1 << 17); }
+// sites one workgroup takes longer than two launches over the whole chip, unless
+// there are lattices for many of its CUs (rows of 32 sites, up to 2^19 of them;
+// the couplings of more than 3 x 2^16 don't fit LDS).  us of a call, modelled: a
+// workgroup's lattice 46 per 10^6 sites to load and store (couplings as much
+// again) and 1.5 + 59 per sweep, on each of 256 CUs at once; half-sweeps 8.5 +
+// 0.95 per sweep over all lattices' sites.  Measured, whole (half-sweeps), per
+// sweep of 20 at 16, 64 and 256 lattices: 32^2 x 160 11.7, 12.2, 13.5 (11.0, 18.8,
+// 49), 32 x 64 x 256 34, 35, 39 (16.5, 43, 130), 32 x 16384 heat-bath 31, 32, 36
+// (14.5, 33, 103), 32 x 5440 +-J 10.3, 10.6, 12.0 (11.6, 21, 61); one sweep of 64
+// and 256 of 32 x 64 x 256 78, 109 with the call (53, 134).
+bool whole_supported(const Geom &g, bool hasJ, int nsweeps)
+{
+    if (g.N <= (1 << 17)) return true;
+    if (g.Lx != 32 || (hasJ ? g.dims != 2 || g.N > 3 * (1 << 16) : g.N > (1 << 19))) return false;
+    constexpr int kCUs = 256;
+    const double M = 1e-6 * (double)g.N, n = nsweeps;
+    const double whole = (g.count + kCUs - 1) / kCUs * (46.0 * M * (hasJ ? 2.0 : 1.0) + n * (1.5 + 59.0 * M));
+    return whole < n * (8.5 + 0.95 * M * g.count);
+}
 
 template <int DIMS, int RULE, bool HASJ, int K, bool ALIGNED, int BITS>
 static hipError_t launch_whole_a(const WholeArgs &a, int count, size_t lds, hipStream_t s)
@@ -461,8 +528,11 @@ template <int DIMS, int RULE, bool HASJ>
 static hipError_t launch_whole_k(const WholeArgs &a, int count, size_t lds, hipStream_t s)
 {
     if (whole_halves(a.words, count)) return launch_whole_t<DIMS, RULE, HASJ, 1, 16>(a, count, lds, s);
-    return a.words <= 1024u ? launch_whole_t<DIMS, RULE, HASJ, 1, 32>(a, count, lds, s)
-                            : launch_whole_t<DIMS, RULE, HASJ, 2, 32>(a, count, lds, s);
+    if (a.words <= 1024u) return launch_whole_t<DIMS, RULE, HASJ, 1, 32>(a, count, lds, s);
+    if (a.words <= 2048u) return launch_whole_t<DIMS, RULE, HASJ, 2, 32>(a, count, lds, s);
+    if constexpr (!HASJ) return launch_whole_a<DIMS, RULE, false, 0, true, 32>(a, count, lds, s);
+    else if constexpr (DIMS == 2) return launch_whole_a<2, RULE, true, 3, true, 32>(a, count, lds, s);
+    else return hipErrorInvalidValue;
 }
 
 template <int D>

@@ -358,7 +358,7 @@ int run_sweeps(mc_ctx *ctx, const SweepCall &c, int layout, void *spins, uint64_
         [[fallthrough]];
     case MC_PATH_SMALL_BITS:
     case MC_PATH_SMALL:
-        if (!whole_supported(c.g)) break;
+        if (!whole_supported(c.g, c.J != nullptr, nsweeps)) break;
         return device_check(ctx, launch_whole(c, (int8_t *)spins, sweep0, nsweeps, EM, em_stride, s),
                             "mc_sweep whole-lattice launch");
     case MC_PATH_MSC64: {

@@ -56,3 +56,18 @@ def test_threshold_next_to_one(ctx, L):
     W, n = 4096, 4 if L < 128 else 1
     plain = _muca_us(ctx, L, W, _slope(L, 0.4), n, True)
     assert _muca_us(ctx, L, W, -3e-10 * np.arange(L * L // 2 + 1), n, True) < 1.8 * plain
+
+
+# us per sweep of 256 lattices, whole 13.5 and 12.0, half by half 49 and 61
+@pytest.mark.parametrize("shape,J", [((32, 32, 160), False), ((32, 5440), True)])
+def test_many_wide_lattices(ctx, shape, J):
+    n, count = 20, 256
+    g = mcs.make_geom(len(shape), shape, count=count)
+    lat = mcs.lattice_tensor(g)
+    ctx.init(g, lat, mcs.HOT, 3)
+    Jd = None
+    if J:
+        Jd = torch.empty(g.dims * g.N, dtype=torch.int8, device="cuda")
+        ctx.couplings(g, Jd, 5)
+    EM = torch.empty((n, count, 2), dtype=torch.int64, device="cuda")
+    assert _us(lambda: ctx.sweep(g, lat, 0.3, 3, n, J=Jd, EM=EM)) / n < 25.0
