@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <vector>
 
 #include "internal.hpp"
@@ -219,25 +220,26 @@ int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of,
         row = std::max(row, pair[(size_t)i].cut + 1);
     }
     const PtLayout lay = pt_layout(a, row);
-    std::vector<char> up(lay.E_at);
-    Thr *thr = (Thr *)(up.data() + lay.thr);
+    // (not cleared first: a row per pair of many temperatures is 131 MB at L = 128)
+    const std::unique_ptr<char[]> up(new char[lay.E_at]);
+    Thr *thr = (Thr *)(up.get() + lay.thr);
     for (int i = 0; i < nT; ++i) {
         const SweepTables t = build_tables(a->beta[i]);
         thr[2 * i] = t.met[1];
         thr[2 * i + 1] = t.met[2];
     }
     for (int i = 0; i + 1 < nT; ++i) {
-        uint64_t *x = (uint64_t *)(up.data() + lay.xtab) + (size_t)i * (size_t)row;
+        uint64_t *x = (uint64_t *)(up.get() + lay.xtab) + (size_t)i * (size_t)row;
         const PtPair p = pair[(size_t)i];
         x[0] = a->round0 << kPtZeroBits | (uint64_t)p.zero;
         for (int64_t m = 1; m <= p.cut; ++m)
             x[m] = (uint64_t)std::ceil(std::ldexp(std::exp((a->beta[i] - a->beta[i + 1]) * (double)(4 * m)), 32));
         for (int64_t m = p.cut + 1; m < row; ++m) x[m] = m < p.zero ? 1u : 0u;
     }
-    std::memcpy(up.data() + lay.temp_of, temp_of, (size_t)count * 4);
-    std::memcpy(up.data() + lay.replica_at, replica_at, (size_t)count * 4);
-    std::memcpy(up.data() + lay.accepted, accepted, (size_t)nS * (nT - 1) * 8);
-    hipError_t e = hipMemcpyAsync(w, up.data(), up.size(), hipMemcpyHostToDevice, s);
+    std::memcpy(up.get() + lay.temp_of, temp_of, (size_t)count * 4);
+    std::memcpy(up.get() + lay.replica_at, replica_at, (size_t)count * 4);
+    std::memcpy(up.get() + lay.accepted, accepted, (size_t)nS * (nT - 1) * 8);
+    hipError_t e = hipMemcpyAsync(w, up.get(), lay.E_at, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return device_check(ctx, e, "mc_pt_run setup");
 
     PtSweepArgs sw{};
@@ -303,7 +305,7 @@ int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of,
     }
     if (a->rounds > 0) e = hipGraphLaunch(ctx->pt_graph.exec, s);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(up.data() + lay.temp_of, w + lay.temp_of, lay.E_at - lay.temp_of, hipMemcpyDeviceToHost, s);
+        e = hipMemcpyAsync(up.get() + lay.temp_of, w + lay.temp_of, lay.E_at - lay.temp_of, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess && E_at && a->rounds > 0)
         e = hipMemcpyAsync(E_at, w + lay.E_at, (size_t)a->rounds * count * 8, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -311,9 +313,9 @@ int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of,
         ctx->pt_graph.reset();
         return device_check(ctx, e, "mc_pt_run");
     }
-    std::memcpy(temp_of, up.data() + lay.temp_of, (size_t)count * 4);
-    std::memcpy(replica_at, up.data() + lay.replica_at, (size_t)count * 4);
-    std::memcpy(accepted, up.data() + lay.accepted, (size_t)nS * (nT - 1) * 8);
+    std::memcpy(temp_of, up.get() + lay.temp_of, (size_t)count * 4);
+    std::memcpy(replica_at, up.get() + lay.replica_at, (size_t)count * 4);
+    std::memcpy(accepted, up.get() + lay.accepted, (size_t)nS * (nT - 1) * 8);
     return MC_OK;
 }
 
