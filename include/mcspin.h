@@ -241,7 +241,7 @@ int mc_measure(mc_ctx *ctx, const mc_geom *geom, const void *spins, const int8_t
  * Lx a multiple of 64, bit-packed tiles in LDS, several sweeps per launch;
  * 2D only for Metropolis without couplings; needs mc_sweep_workspace_bytes
  * of workspace; lattices of at most 2^15 sites of one temperature without a
- * set or tuned plan run whole in a workgroup instead), MC_PATH_SMALL_BITS
+ * set or tuned shape run whole in a workgroup instead), MC_PATH_SMALL_BITS
  * (small int8 lattices of 32-site rows) and MC_PATH_SMALL (other small int8
  * lattices): whole in one workgroup's LDS as bits, every sweep of a call in
  * one launch (few lattices of above 2^17 sites: half-sweeps), MC_PATH_MSC64
@@ -277,8 +277,12 @@ int mc_get_tile_plan(mc_ctx *ctx, const mc_geom *geom, int32_t *H, int32_t *K, i
  * mc_sweep with EM; their per-tile sums go to the second half of scratch_b
  * and are not added up) at inverse temperature beta, in the steady state of
  * a long call (packed rows in and out), on two caller-provided scratch
- * lattices (device, count * N bytes each; overwritten), and keeps the
- * fastest shape on the context.
+ * lattices (device, count * N bytes each; overwritten), and what a call
+ * without a shape runs (which chooses by its number of sweeps, and takes
+ * lattices of at most 2^15 sites whole).  Keeps the fastest shape on the
+ * context if it is more than 2 % faster than that; else calls go on choosing
+ * for themselves, mc_get_tile_plan reports what a long call chooses and
+ * mc_tuning_save leaves the geometry out.
  * Synchronises the stream.                                                 */
 int mc_tune_sweep(mc_ctx *ctx, const mc_geom *geom, void *scratch_a, void *scratch_b, double beta,
                   int32_t sweeps, void *stream);

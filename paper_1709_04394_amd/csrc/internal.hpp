@@ -25,6 +25,9 @@ struct TilePlan {
     int H = 16;
     int K = 2;
     int threads = 512;
+    // the tuner found the calls' own choice as fast as any fixed shape: a call
+    // chooses by its number of sweeps (these are the values of a long call)
+    bool by_call = false;
 };
 
 }  // namespace mcs

@@ -110,6 +110,13 @@ static TilePlan plan_for(mc_ctx *ctx, const Geom &g)
     return default_tile_plan(g);
 }
 
+// A shape set or tuned for every call, whatever its number of sweeps.
+static bool fixed_plan(mc_ctx *ctx, const Geom &g)
+{
+    auto it = ctx->tile_plans.find(plan_key(g));
+    return it != ctx->tile_plans.end() && !it->second.by_call;
+}
+
 // Launch shape of a call of n sweeps on 3D lattices without a set or tuned
 // plan: as in 2D (below), with 0.15 us for every 64 words (the class
 // multiplexers) and a tile's halo on both sides in y and z.  Measured (and
@@ -155,10 +162,8 @@ static TilePlan call_plan_3d(const Geom &g, int n)
 // 48, 2 (258 bands, so two on one CU) 25.3 (23), the chosen 49, 4 14.0 (13.9);
 // 8192^2, 32, 4 17.5 (17.0); 2048^2, 8, 6 4.7 (4.7); 1024^2, 4, 8 3.6 (3.6), the
 // nominal 4, 1 6.4 (8.1).
-static TilePlan call_plan(mc_ctx *ctx, const Geom &g, int n)
+static TilePlan call_plan_2d(const Geom &g, int n)
 {
-    if (ctx->tile_plans.count(plan_key(g))) return plan_for(ctx, g);
-    if (g.dims == 3) return call_plan_3d(g, n);
     constexpr int kCUs = 256;
     const int Wd = g.Lx / 64;
     TilePlan p = default_tile_plan(g);
@@ -193,6 +198,13 @@ static TilePlan call_plan(mc_ctx *ctx, const Geom &g, int n)
     }
     for (int H : {8, 16, 32, 64}) consider(H);
     return p;
+}
+
+static TilePlan untuned_plan(const Geom &g, int n) { return g.dims == 3 ? call_plan_3d(g, n) : call_plan_2d(g, n); }
+
+static TilePlan call_plan(mc_ctx *ctx, const Geom &g, int n)
+{
+    return fixed_plan(ctx, g) ? plan_for(ctx, g) : untuned_plan(g, n);
 }
 
 // Split n >= 1 sweeps into launches of at most K sweeps, sizes as equal as
@@ -316,15 +328,17 @@ static int betas_path(mc_ctx *ctx, const SweepCall &c, bool have_ws, size_t ws_b
     return sweep_path(ctx, c1, MC_INT8, false, 0);
 }
 
-// Of the fused tiles' lattices without a set or tuned plan, those of 2^15 sites
+// Of the fused tiles' lattices without a fixed plan, those of 2^15 sites
 // or fewer run whole in one workgroup: a launch per call instead of one per few
 // sweeps.  Tiles (whole), us per call of 10 sweeps with E, M, host time
 // included: 64^2 46 (32), 4096 of them 140 (56), 128^2 47 (34), 2048 of them 171
 // (93), 256 x 128 51 (40), 256^2 50 (56); 64 x 16 x 16 heat-bath 64 (38), 64 x
 // 32 x 32 64 (64).
+constexpr int64_t kWholeSites = 1 << 15;
+
 static bool whole_instead_of_tiles(mc_ctx *ctx, const SweepCall &c)
 {
-    return !c.per_lattice && c.g.N <= (1 << 15) && !ctx->tile_plans.count(plan_key(c.g));
+    return !c.per_lattice && c.g.N <= kWholeSites && !fixed_plan(ctx, c.g);
 }
 
 int run_sweeps_betas(mc_ctx *ctx, const SweepCall &c, int8_t *spins, uint64_t sweep0, int nsweeps, int64_t *EM,
@@ -496,6 +510,40 @@ int mc_tune_sweep_rule(mc_ctx *ctx, const mc_geom *geom, int32_t rule, void *scr
     TilePlan conv = default_tile_plan(g);
     hipError_t e = launch_init_int8(g, (int8_t *)scratch_a, 1, 1, 0, s);
     if (e == hipSuccess) e = launch(scratch_a, 0, scratch_b, 1, 0, 0, conv, false);
+    // ms per sweep: a warm-up, then the best of two timed runs of n sweeps
+    auto best_of_two = [&](int n, auto &&warm, auto &&run) {
+        float ms = 1e30f;
+        if (e == hipSuccess) e = warm();
+        for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {
+            e = hipEventRecord(e0, s);
+            if (e == hipSuccess) e = run();
+            if (e == hipSuccess) e = hipEventRecord(e1, s);
+            if (e == hipSuccess) e = hipEventSynchronize(e1);
+            float t = 0;
+            if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
+            ms = std::min(ms, t / (float)n);
+        }
+        return ms;
+    };
+    // the steady state of a long measured call: packed -> packed launches
+    // between the two scratch buffers, measuring E, M
+    auto time_plan = [&](const TilePlan &p) {
+        const int Hy = three ? p.H : std::min(p.H, g.Ly), K = p.K;
+        const int64_t tiles = (int64_t)((g.Ly + Hy - 1) / Hy) * (three ? (g.Lz + Hy - 1) / Hy : 1);
+        if ((size_t)K * (size_t)g.count * (size_t)tiles * 16 > (size_t)g.count * (size_t)g.N / 2)
+            return 1e30f;  // tile sums larger than half of scratch_b
+        int n = std::max(sweeps, 2 * K);
+        n -= n % (2 * K);
+        return best_of_two(
+            n, [&] { return launch(scratch_b, 1, scratch_a, 1, 0, K, p, true); },
+            [&] {
+                hipError_t r = hipSuccess;
+                for (int i = 0; i < n / K && r == hipSuccess; ++i)
+                    r = launch((i & 1) ? scratch_b : scratch_a, 1, (i & 1) ? scratch_a : scratch_b, 1,
+                               (uint64_t)i * K, K, p, true);
+                return r;
+            });
+    };
     TilePlan best = default_tile_plan(g);
     float best_ms = 1e30f;
     std::vector<int> Hs, Ks, Ts;
@@ -517,36 +565,31 @@ int mc_tune_sweep_rule(mc_ctx *ctx, const mc_geom *geom, int32_t rule, void *scr
                 p.K = K;
                 p.threads = T;
                 if (!plan_ok(g, p) || e != hipSuccess) continue;
-                const int Hy = std::min(p.H, g.Ly);
-                const int64_t tiles =
-                    three ? (int64_t)((g.Ly + H - 1) / H) * ((g.Lz + H - 1) / H) : (int64_t)((g.Ly + Hy - 1) / Hy);
-                if ((size_t)K * (size_t)g.count * (size_t)tiles * 16 > (size_t)g.count * (size_t)g.N / 2)
-                    continue;  // tile sums larger than half of scratch_b
-                int n = std::max(sweeps, 2 * K);
-                n -= n % (2 * K);
-                // the steady state of a long measured call: packed -> packed
-                // launches between the two scratch buffers, measuring E, M; a
-                // warm-up launch, then the best of two timed runs
-                e = launch(scratch_b, 1, scratch_a, 1, 0, K, p, true);
-                float ms = 1e30f;
-                for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {
-                    e = hipEventRecord(e0, s);
-                    for (int i = 0; i < n / K && e == hipSuccess; ++i)
-                        e = launch((i & 1) ? scratch_b : scratch_a, 1, (i & 1) ? scratch_a : scratch_b, 1,
-                                   (uint64_t)i * K, K, p, true);
-                    if (e == hipSuccess) e = hipEventRecord(e1, s);
-                    if (e == hipSuccess) e = hipEventSynchronize(e1);
-                    float t = 0;
-                    if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
-                    ms = std::min(ms, t / (float)n);
-                }
-                if (e != hipSuccess) break;
-                if (ms < best_ms) {
+                const float ms = time_plan(p);
+                if (e == hipSuccess && ms < best_ms) {
                     best_ms = ms;
                     best = p;
                 }
             }
     }
+    // What an untuned long call runs: its own shape, or the lattices whole.  A
+    // fixed shape takes its place only where it is more than 2 % faster, which the
+    // best of some hundred timings is by chance; else calls go on choosing by
+    // their number of sweeps.
+    TilePlan own = untuned_plan(g, 1000);
+    own.by_call = true;
+    float own_ms = 1e30f;
+    if (e == hipSuccess && g.N <= kWholeSites) {
+        // (E, M) rows in the unused half of scratch_b
+        const int n = (int)std::min<int64_t>(std::max(sweeps, 8), g.N / 32);
+        int64_t *EM = (int64_t *)((char *)scratch_b + (size_t)g.count * (size_t)g.N / 2);
+        auto whole = [&] { return launch_whole(c, (int8_t *)scratch_a, 0, n, EM, 2 * (int64_t)g.count, s); };
+        e = launch_init_int8(g, (int8_t *)scratch_a, 1, 1, 0, s);
+        own_ms = best_of_two(n, whole, whole);
+    } else if (e == hipSuccess) {
+        own_ms = time_plan(own);
+    }
+    if (own_ms <= 1.02f * best_ms) best = own;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (e != hipSuccess) return device_check(ctx, e, "mc_tune_sweep");

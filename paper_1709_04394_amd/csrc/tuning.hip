@@ -69,6 +69,7 @@ int mc_tuning_save(mc_ctx *ctx, const char *path)
     if (!f) return fail(ctx, MC_E_IO, "cannot write %s: %s", tmp.c_str(), std::strerror(errno));
     bool ok = std::fprintf(f, "%s\n", kHeader) > 0;
     for (const auto &kv : ctx->tile_plans) {
+        if (kv.second.by_call) continue;  // as without an entry
         int d, lx, ly, lz, n;
         std::tie(d, lx, ly, lz, n) = kv.first;
         ok = ok && std::fprintf(f, "tile %d %d %d %d %d %d %d %d\n", d, lx, ly, lz, n, kv.second.H, kv.second.K,
