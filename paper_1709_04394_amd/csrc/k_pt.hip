@@ -76,10 +76,7 @@ __global__ __launch_bounds__(1024) void k_pt_exchange(PtExchangeArgs a)
         // d <= 0; energies of the even torus differ by multiples of 4
         bool acc = d <= 0;
         if (!acc) {
-            // beyond the row the threshold is 1, then 0
-            const uint64_t *x = a.xtab + (int64_t)i * a.row;
-            const int m = d >> 2;
-            const uint64_t T = m < a.row ? x[m] : m < (int)(x[0] & ((1u << kPtZeroBits) - 1u)) ? 1u : 0u;
+            const uint64_t T = pt_threshold(a.xtab + (int64_t)i * a.row, a.row, d >> 2);
             const uint4 r = philox(make_uint4((uint32_t)i >> 2, (uint32_t)s, (uint32_t)round,
                                               ctr_w3(kTagExchange, 0, round)),
                                    a.seed_lo, a.seed_hi);

@@ -2,11 +2,11 @@
 #pragma once
 
 #include "common.hpp"
+#include "pt_rows.hpp"
 
 namespace mcs {
 
 constexpr int kPtMaxTemps = 1024;  // temperatures per set: one exchange workgroup
-constexpr int kPtZeroBits = 24;    // low bits of a pair's entry 0: first m of threshold 0; above: first round
 
 struct PtSweepArgs {
     int8_t *spins;              // [count][L^2], lattice l = set s, replica r at l = s n_temps + r

@@ -127,29 +127,6 @@ PtLayout pt_layout(const mc_pt_args *a, int64_t row)
     return l;
 }
 
-// The exchange threshold ceil(exp(x) 2^32), x = (beta_i - beta_{i+1}) 4m < 0, is
-// 1 from x = -22.5 (exp(x) 2^32 < 0.73) until exp(x) is 0: the entries up to
-// `cut`, and the first m whose threshold is 0.
-struct PtPair {
-    int64_t cut, zero;
-};
-
-PtPair pt_pair(double b0, double b1, int64_t mmax)
-{
-    const double d = b0 - b1;
-    auto first_below = [&](double x) {  // first m with d 4m < x, at most mmax + 1
-        const double m = std::floor(x / (4.0 * d));
-        int64_t k = m < 0.0 ? 0 : m > (double)mmax ? mmax + 1 : (int64_t)m;
-        while (k <= mmax && !(d * (double)(4 * k) < x)) ++k;
-        return k;
-    };
-    PtPair p;
-    p.cut = std::min(first_below(-22.5), mmax);
-    p.zero = first_below(-744.0);
-    while (p.zero <= mmax && std::exp(d * (double)(4 * p.zero)) != 0.0) ++p.zero;
-    return p;
-}
-
 int check_pt(mc_ctx *ctx, const mc_pt_args *a)
 {
     if (!a) return fail(ctx, MC_E_INVAL, "args is NULL");
@@ -228,14 +205,9 @@ int mc_pt_run(mc_ctx *ctx, const mc_pt_args *a, int8_t *spins, int32_t *temp_of,
         thr[2 * i] = t.met[1];
         thr[2 * i + 1] = t.met[2];
     }
-    for (int i = 0; i + 1 < nT; ++i) {
-        uint64_t *x = (uint64_t *)(up.get() + lay.xtab) + (size_t)i * (size_t)row;
-        const PtPair p = pair[(size_t)i];
-        x[0] = a->round0 << kPtZeroBits | (uint64_t)p.zero;
-        for (int64_t m = 1; m <= p.cut; ++m)
-            x[m] = (uint64_t)std::ceil(std::ldexp(std::exp((a->beta[i] - a->beta[i + 1]) * (double)(4 * m)), 32));
-        for (int64_t m = p.cut + 1; m < row; ++m) x[m] = m < p.zero ? 1u : 0u;
-    }
+    for (int i = 0; i + 1 < nT; ++i)
+        pt_row(a->beta[i], a->beta[i + 1], pair[(size_t)i], row, a->round0,
+               (uint64_t *)(up.get() + lay.xtab) + (size_t)i * (size_t)row);
     std::memcpy(up.get() + lay.temp_of, temp_of, (size_t)count * 4);
     std::memcpy(up.get() + lay.replica_at, replica_at, (size_t)count * 4);
     std::memcpy(up.get() + lay.accepted, accepted, (size_t)nS * (nT - 1) * 8);
