@@ -37,10 +37,12 @@ VALU_FILE = os.path.join(ROOT, "profiles", "k_tile2d_L4096x3_valu.txt")
 # every 4 cycles (16 lanes per cycle), at 2.4 GHz
 VALU_PEAK_WAVE_INSTS = 256 * 4 * 2.4e9 / 4
 # the dominant kernel's source files, hashed together in this order
-KERNEL_SRC = [os.path.join(ROOT, "paper_1709_04394_amd", "csrc", f) for f in ("k_tile2d.hip", "metro2d.hpp", "em_slots.hpp")]
+KERNEL_SRC = [os.path.join(ROOT, "paper_1709_04394_amd", "csrc", f) for f in
+              ("k_tile2d.hip", "metro2d.hpp", "em_slots.hpp", "spin_bytes.hpp", "common.hpp")]
 MLP_PEAK_TFLOPS = 256 * 64 * 2 * 2.4e9 / 1e12
-# bands of 16 rows, 4 sweeps per launch, 512 threads: the autotuner's usual
-# pick on this workload (it alternates with 3 sweeps per launch within 1 %)
+# bands of 16 rows, 2 sweeps per launch, 512 threads: the shape the committed
+# counter summaries were taken with (a call without a shape takes bands of 49
+# rows, 4 sweeps per launch, 1024 threads, and is 10 % faster: --tune)
 PROFILED_PLAN = "16,2,512"
 
 

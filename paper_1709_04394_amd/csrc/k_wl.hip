@@ -42,9 +42,9 @@ __device__ __forceinline__ uint64_t wl_threshold(uint64_t x, const double *xt)
 // the estimates is below D(r32) = -ln(r32 2^-32) 2^32, which depends on the
 // random number alone and is prepared off the walker's chain in FP32.  Where
 // the difference comes within kWlMargin of D, which covers both conversions'
-// and the logarithm's rounding several times over (differences that can be
-// near a D are below 23 2^32: 2^13.6 from the conversion, 2^14 from the
-// logarithm), the exact test decides; that is about one update in 2^15.
+// and the logarithm's rounding twice over (differences that can be near a D are
+// below 23 2^32: 2^13.6 from the conversion, 2^14 from the logarithm), the exact
+// test decides; that is about one update in 2^15.
 constexpr float kWlMargin = 65536.0f;
 
 __device__ __forceinline__ float wl_bound(uint32_t r)

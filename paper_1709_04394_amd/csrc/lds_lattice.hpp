@@ -338,7 +338,7 @@ __device__ void sweep_lds_words(uint32_t *lds, const LdsLattices &a, Thr u4, Thr
                     tq[at] = make_uint4(wsg, blk, pend, c8);
                 }
                 qn += (uint32_t)__popcll(m);
-                // at least 64 words wait: settle all (the queue holds 128, a task adds up to 64)
+                // more than 64 words wait: settle all (the queue holds 128, a task adds up to 64)
                 if (qn > 64u || t0 + nt >= tasks) {
                     settle_lds_ties<PER_LAT>(lds, a, tq, qn, (uint32_t)sweep, w3lo, u4.low, u8.low, t4, t8);
                     qn = 0;

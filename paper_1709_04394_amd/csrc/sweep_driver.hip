@@ -56,7 +56,7 @@ TilePlan default_tile_plan(const Geom &g)
         // shrinking half-sweeps best; with several tiles per CU narrower
         // workgroups run side by side on a CU instead of one after another
         // (1024 threads leave room for one workgroup per CU): 256^3 x 4 at
-        // 256 threads takes 39 us per sweep against 62 us at 1024.
+        // 256 threads takes 25 us per sweep against 39 us at 1024.
         p.H = std::min(16, std::min(g.Ly, g.Lz));
         p.K = 2;
         while (p.K > 1 && tile3d_lds_bytes(g.Lx, p.H, p.K, true) > 98304) --p.K;
@@ -118,11 +118,14 @@ static bool fixed_plan(mc_ctx *ctx, const Geom &g)
 }
 
 // Launch shape of a call of n sweeps on 3D lattices without a set or tuned
-// plan: as in 2D (below), with 0.15 us for every 64 words (the class
-// multiplexers) and a tile's halo on both sides in y and z.  Measured (and
-// modelled), us per sweep, heat-bath: 256^3 x 4, H = 16, K = 2 32 (33); 256^3
-// 12.3 (12); 128^3, the chosen 8, 3 6.2 (6.1), the nominal 16, 2 (64 tiles) 9.2
-// (8.8); 64^3, 4, 4 4.9 (4.6), 16, 2 7.6 (7.1).
+// plan: as in 2D (below), with 0.15 us for every 64 words and a tile's halo on
+// both sides in y and z, for both rules.  Measured (and modelled), us per sweep of
+// 60, heat-bath: 256^3 x 4, the chosen H = 16, K = 1 25.9 (30.2), the nominal 16, 2
+// 25.1 (32.9); 256^3, 16, 2 10.8 (12.3); 128^3, the chosen 8, 3 5.4 (6.1), the
+// nominal 16, 2 (64 tiles) 8.1 (8.8); 64^3, the chosen 4, 4 4.3 (4.6), 16, 2 6.6
+// (7.1); Metropolis within 3 % of these.  The coefficients are of an earlier form
+// of the kernel: the times are 7 to 24 % below the model's, the order of the
+// shapes is the model's but for the first pair (3 %).
 static TilePlan call_plan_3d(const Geom &g, int n)
 {
     constexpr int kCUs = 256;
@@ -158,10 +161,10 @@ static TilePlan call_plan_3d(const Geom &g, int n)
 // half-sweep 1 us (one word's latency, ties, barrier) plus 0.087 us of VALU
 // issue for every 64 words of the fullest CU, which has ceil(bands / 256) bands
 // of H + 2K - 1 rows on average with the redone halo.  Measured (and modelled),
-// us per sweep of long calls: 4096^2 x 3, H = 16, K = 2 15.5 (15.5), the nominal
-// 48, 2 (258 bands, so two on one CU) 25.3 (23), the chosen 49, 4 14.0 (13.9);
-// 8192^2, 32, 4 17.5 (17.0); 2048^2, 8, 6 4.7 (4.7); 1024^2, 4, 8 3.6 (3.6), the
-// nominal 4, 1 6.4 (8.1).
+// us per sweep of 200: 4096^2 x 3, H = 16, K = 2 14.4 (15.5), the nominal 48, 2
+// (258 bands, so two on one CU) 24.1 (23), the chosen 49, 4 13.4 (13.2); 8192^2, the
+// chosen 32, 3 16.3 (16.9); 4096^2, 16, 4 7.4 (7.5); 2048^2, 8, 6 4.4 (4.7); 1024^2,
+// 4, 8 3.4 (3.6), the nominal 4, 1 6.5 (8.1).
 static TilePlan call_plan_2d(const Geom &g, int n)
 {
     constexpr int kCUs = 256;
@@ -331,9 +334,9 @@ static int betas_path(mc_ctx *ctx, const SweepCall &c, bool have_ws, size_t ws_b
 // Of the fused tiles' lattices without a fixed plan, those of 2^15 sites
 // or fewer run whole in one workgroup: a launch per call instead of one per few
 // sweeps.  Tiles (whole), us per call of 10 sweeps with E, M, host time
-// included: 64^2 46 (32), 4096 of them 140 (56), 128^2 47 (34), 2048 of them 171
-// (93), 256 x 128 51 (40), 256^2 50 (56); 64 x 16 x 16 heat-bath 64 (38), 64 x
-// 32 x 32 64 (64).
+// included: 64^2 46 (29), 4096 of them 141 (60), 128^2 46 (34), 2048 of them 170
+// (92), 256 x 128 49 (41), 256^2 49 (49); 64 x 16 x 16 heat-bath 62 (37), 64 x
+// 32 x 16 62 (45), 64 x 32 x 32 60 (60).
 constexpr int64_t kWholeSites = 1 << 15;
 
 static bool whole_instead_of_tiles(mc_ctx *ctx, const SweepCall &c)

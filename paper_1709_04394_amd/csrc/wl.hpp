@@ -7,7 +7,7 @@ namespace mcs {
 
 constexpr int kWlExpN = 23;                    // exp(-n), n = 0..22; n >= 23 gives the threshold 1
 constexpr int kWlTab = kWlExpN + 4 * 256;       // exp(-n), then the factors of the four bytes
-constexpr int kWlMaxWidth = 192;                // levels per window (estimates of 64 walkers in LDS)
+constexpr int kWlMaxWidth = 192;                // levels per window (estimates and counts of 16 walkers in LDS)
 
 struct WlArgs {
     int8_t *spins;          // [W][L*L] walker lattices (in/out)
